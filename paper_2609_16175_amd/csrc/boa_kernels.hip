@@ -604,35 +604,38 @@ struct RangeTest {
     uint32_t fspan[BOA_MAX_M];
     uint32_t phi0;
 
-    // query qi's m ranges (row-major nq x m x 2 cells)
+    // query qi's m ranges (row-major nq x m x 2 cells): lane j takes column
+    // j's, in one load, and the lanes' bounds are then read by every lane
     __device__ __forceinline__ void set(const int32_t *ranges, uint32_t qi, int m, uint32_t f32_mask)
     {
-        phi0 = 0;
+        const int lane = lane_id();
+        int32_t l = 0;
+        uint32_t s = 0xFFFFFFFFu;   // (padding cells pass)
+        bool none = false;
+        if (lane < m) {
+            const int32_t *r = ranges + ((size_t)qi * m + lane) * 2;
+            int32_t lo = r[0], hi = r[1];
+            if ((f32_mask >> lane) & 1u) {
+                none = ((uint32_t)lo & 0x7FFFFFFFu) > 0x7F800000u || ((uint32_t)hi & 0x7FFFFFFFu) > 0x7F800000u;
+                lo = f32_ord((uint32_t)lo);
+                hi = f32_ord((uint32_t)hi);
+            }
+            none |= lo > hi;
+            if (!none) {
+                l = lo;
+                s = (uint32_t)hi - (uint32_t)lo;
+            }
+        }
+        phi0 = (uint32_t)__popcll(__ballot(none));
 #pragma unroll
         for (int j = 0; j < BOA_MAX_M; ++j) {
-            int32_t l = 0;
-            uint32_t s = 0xFFFFFFFFu;   // (padding cells pass)
-            if (j < m) {
-                int32_t lo = ranges[((size_t)qi * m + j) * 2 + 0];
-                int32_t hi = ranges[((size_t)qi * m + j) * 2 + 1];
-                bool none = false;
-                if ((f32_mask >> j) & 1u) {
-                    none = ((uint32_t)lo & 0x7FFFFFFFu) > 0x7F800000u || ((uint32_t)hi & 0x7FFFFFFFu) > 0x7F800000u;
-                    lo = f32_ord((uint32_t)lo);
-                    hi = f32_ord((uint32_t)hi);
-                }
-                if (none || lo > hi) {
-                    phi0 += 1;
-                } else {
-                    l = lo;
-                    s = (uint32_t)hi - (uint32_t)lo;
-                }
-            }
+            int32_t lj = __builtin_amdgcn_readlane(l, j);
+            uint32_t sj = (uint32_t)__builtin_amdgcn_readlane((int)s, j);
             // (held in vector registers: kept uniform they would be spilled
             // scalars, reloaded at every use)
-            asm volatile("" : "+v"(l), "+v"(s));
-            flo[j] = l;
-            fspan[j] = s;
+            asm volatile("" : "+v"(lj), "+v"(sj));
+            flo[j] = lj;
+            fspan[j] = sj;
         }
     }
 
@@ -698,26 +701,32 @@ __device__ __forceinline__ uint32_t mix_id(uint32_t v, uint32_t B)
     return __umul24(h, 0xEBCA6Bu) & mask;
 }
 
-// Bit 15 of each 16-bit half of the result is set when that half of w is
-// zero (the masked add sets bit 15 of a half exactly when its low 15 bits
-// are not all zero, and no carry crosses into the other half).
-__device__ __forceinline__ uint32_t zero_halves(uint32_t w)
+// smaller of each pair of 16-bit halves (one packed instruction; written as
+// vector arithmetic the compiler splits it into scalar halves)
+__device__ __forceinline__ uint32_t pk_min_u16(uint32_t a, uint32_t b)
 {
-    const uint32_t t = (w & 0x7FFF7FFFu) + 0x7FFF7FFFu;
-    return ~(t | w) & 0x80008000u;
+    uint32_t r;
+    asm("v_pk_min_u16 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
 }
 
+// whether one of the bucket's eight halves is e
 __device__ __forceinline__ bool has16(const uint4 &b, uint32_t e)
 {
     const uint32_t ee = e * 0x00010001u;
-    return (zero_halves(b.x ^ ee) | zero_halves(b.y ^ ee) | zero_halves(b.z ^ ee) | zero_halves(b.w ^ ee)) != 0u;
+    const uint32_t m = pk_min_u16(pk_min_u16(b.x ^ ee, b.y ^ ee), pk_min_u16(b.z ^ ee, b.w ^ ee));
+    return (m & 0xFFFFu) == 0u || m < 0x10000u;
 }
 
-// free slots (0xFFFF halves) of a bucket
-__device__ __forceinline__ uint32_t empties16(const uint4 &b)
+// A bucket fills from its first half-word on and entries are never removed,
+// so the free slots (0xFFFF) are a suffix: a word has a free slot when its
+// upper half is one.
+__device__ __forceinline__ bool word_free(uint32_t w) { return w >= 0xFFFF0000u; }
+// wholly free words of a bucket (how empty it is, to two slots)
+__device__ __forceinline__ uint32_t free_words(const uint4 &b)
 {
-    return (uint32_t)__popc(zero_halves(~b.x) | (zero_halves(~b.y) >> 1) | (zero_halves(~b.z) >> 2) |
-                            (zero_halves(~b.w) >> 3));
+    return (b.x == 0xFFFFFFFFu ? 1u : 0u) + (b.y == 0xFFFFFFFFu ? 1u : 0u) + (b.z == 0xFFFFFFFFu ? 1u : 0u) +
+           (b.w == 0xFFFFFFFFu ? 1u : 0u);
 }
 
 // 1: v was not in the set and now is (in LDS); 0: v was already there;
@@ -734,26 +743,21 @@ __device__ __forceinline__ int visit_lds(const Visited &s, uint32_t v)
     for (int attempt = 0; attempt < 256; ++attempt) {
         // both buckets read before either is tested: one LDS round trip
         const uint4 B1 = bk[b1], B2 = bk[b2];
-        if (has16(B1, e1) | (alt_ok && has16(B2, e2))) return 0;
-        const uint32_t n1 = empties16(B1), n2 = alt_ok ? empties16(B2) : 0u;
-        if (n1 == 0u && n2 == 0u) return -1;
-        const bool use1 = n1 >= n2;
+        if (has16(B1, e1) || (alt_ok && has16(B2, e2))) return 0;
+        const bool room1 = word_free(B1.w), room2 = alt_ok && word_free(B2.w);
+        if (!room1 && !room2) return -1;
+        // the emptier bucket, the home bucket when they are equally so
+        const bool use1 = room1 && (!room2 || free_words(B1) >= free_words(B2));
         const uint4 Bc = use1 ? B1 : B2;
         const uint32_t e = use1 ? e1 : e2;
         const uint32_t bi = use1 ? b1 : b2;
-        // first (lowest) free half-word: the lowest word with a free half,
-        // its low half when that one is free
-        const uint32_t w[4] = {Bc.x, Bc.y, Bc.z, Bc.w};
-        uint32_t wi = 0, old = 0, neu = 0;
-#pragma unroll
-        for (int q = 3; q >= 0; --q) {
-            const uint32_t zq = zero_halves(~w[q]);
-            if (zq) {
-                wi = q;
-                old = w[q];
-                neu = (zq & 0x8000u) ? ((w[q] & 0xFFFF0000u) | e) : ((w[q] & 0x0000FFFFu) | (e << 16));
-            }
-        }
+        // the first free half: in the first word with one, its low half when
+        // that one is free
+        uint32_t wi = 3, old = Bc.w;
+        if (word_free(Bc.z)) { wi = 2; old = Bc.z; }
+        if (word_free(Bc.y)) { wi = 1; old = Bc.y; }
+        if (word_free(Bc.x)) { wi = 0; old = Bc.x; }
+        const uint32_t neu = old == 0xFFFFFFFFu ? (0xFFFF0000u | e) : ((old & 0xFFFFu) | (e << 16));
         if (atomicCAS(&s.words[bi * 4u + wi], old, neu) == old) return 1;
         // another lane changed that word: look again
     }
@@ -793,6 +797,256 @@ __device__ __forceinline__ void clear_bits(const Visited &s, uint32_t n_log, int
 }
 
 // ---------------------------------------------------------------------------
+// The worklist of Alg. 2, held by one wave: a sorted list in LDS and up to 64
+// pending keys, one per lane, not yet merged into it.
+//
+// The worklist at any time is the Lcap smallest keys entered so far, so it is
+// the same whenever the merge into the sorted list happens, and a key that
+// has Lcap smaller ones can be dropped at any later time. The next node to
+// expand is the smallest unexpanded key of both parts, provided fewer than L
+// keys are smaller (else every entry among the first L is expanded and the
+// phase has converged). So the pending keys are merged only when the next
+// batch does not fit the 64 lanes, or when that count cannot be told without
+// it. A merge (sort by counting, search, rebuild of up to Lcap entries) costs
+// several times a selection, and at widths of 100 and more it is needed once
+// in 4 to 15 expansions instead of at every one.
+
+// smallest of 64 lanes' values, in lane 63 (DPP steps inside rows of 16, then
+// across the rows; a lane without a source keeps its own value)
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp_min(uint32_t v)
+{
+    const uint32_t o = (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, CTRL, 0xF, 0xF, false);
+    return o < v ? o : v;
+}
+__device__ __forceinline__ uint32_t wave_min32(uint32_t v)
+{
+    v = dpp_min<0x111>(v);   // row_shr:1, 2, 4, 8
+    v = dpp_min<0x112>(v);
+    v = dpp_min<0x114>(v);
+    v = dpp_min<0x118>(v);
+    v = dpp_min<0x142>(v);   // row_bcast:15, 31
+    v = dpp_min<0x143>(v);
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+// The smallest key without the expanded flag (KEY_NONE, which has it set, if
+// there is none). The upper halves decide unless they tie.
+__device__ __forceinline__ uint64_t wave_min_open(uint64_t key)
+{
+    const uint32_t hi = (key & 1ull) ? 0xFFFFFFFFu : (uint32_t)(key >> 32);
+    const uint32_t m = wave_min32(hi);
+    if (m == 0xFFFFFFFFu) return KEY_NONE;
+    const uint64_t eq = __ballot(hi == m);
+    uint32_t lo;
+    if ((eq & (eq - 1ull)) == 0ull)
+        lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)key, __ffsll((unsigned long long)eq) - 1);
+    else
+        lo = wave_min32(hi == m ? (uint32_t)key : 0xFFFFFFFFu);
+    return ((uint64_t)m << 32) | lo;
+}
+
+static constexpr int NEXT_NONE = 0, NEXT_FOUND = 1, NEXT_MERGE = 2;
+
+struct WaveList {
+    uint64_t *beam;      // sorted entries [0, len), KEY_NONE up to the next power of two
+    uint64_t *nkey;      // 64
+    uint64_t *posbm;     // output-slot bitmap of a merge
+    uint32_t len, L, Lcap;
+    uint64_t thr;        // with len == Lcap: the last entry, which a new key must beat
+    uint32_t pn;         // pending keys: lanes [0, pn) of pend, KEY_NONE in the others
+    uint64_t pend;
+    uint64_t pmin;       // the smallest unexpanded one
+    // window on the sorted list: win = beam[wb + lane], wmask its unexpanded
+    // lanes; every entry below wb and below the first set bit is expanded
+    uint32_t wb;
+    uint64_t win, wmask;
+
+    __device__ __forceinline__ uint32_t limit() const { return min(len, L); }
+    __device__ __forceinline__ void clear(int Lb, int lane)
+    {
+        for (int i = lane; i < Lb; i += 64) beam[i] = KEY_NONE;
+        len = 0;
+    }
+    // start of a phase on a list without pending keys
+    __device__ __forceinline__ void begin(int L_, int Lcap_, int lane)
+    {
+        L = (uint32_t)L_;
+        Lcap = (uint32_t)Lcap_;
+        len = bcast0(len);
+        pn = 0;
+        pend = KEY_NONE;
+        pmin = KEY_NONE;
+        set_thr();
+        scan(0, lane);
+    }
+    __device__ __forceinline__ void set_thr()
+    {
+        thr = len == Lcap ? readlane64(beam[Lcap - 1u], 0) : KEY_NONE;
+    }
+    __device__ __forceinline__ void scan(uint32_t from, int lane)
+    {
+        const uint32_t lim = limit();
+        wmask = 0ull;
+        for (wb = from; wb < lim; wb += 64) {
+            const uint32_t i = wb + lane;
+            win = i < lim ? beam[i] : 1ull;
+            wmask = __ballot(!(win & 1ull));
+            if (wmask) break;
+        }
+    }
+    // first unexpanded sorted entry (its index: the limit if there is none)
+    __device__ __forceinline__ uint32_t first_index() const
+    {
+        return wmask ? wb + (uint32_t)__ffsll((unsigned long long)wmask) - 1u : limit();
+    }
+    __device__ __forceinline__ uint64_t first_key() const
+    {
+        return wmask ? readlane64(win, __ffsll((unsigned long long)wmask) - 1) : KEY_NONE;
+    }
+    // new keys that can still enter
+    __device__ __forceinline__ uint64_t filter(uint64_t key) const { return key < thr ? key : KEY_NONE; }
+
+    // The next node to expand (its key in x), marked as expanded in its place:
+    // the pending keys, the sorted list, or the caller's new keys nk (not yet
+    // added). NEXT_NONE: converged. NEXT_MERGE: not known before a merge.
+    __device__ __forceinline__ int next(uint64_t &nk, uint64_t &x, int lane)
+    {
+        const uint64_t m = wave_min_open(nk);
+        const uint64_t s = first_key();
+        x = s < pmin ? s : pmin;
+        x = m < x ? m : x;
+        if (x == KEY_NONE) return NEXT_NONE;
+        const uint32_t j = first_index();
+        if (j + pn >= L) {
+            // smaller keys: j sorted ones (an upper bound unless the node is
+            // the sorted list's own) and the expanded pending ones
+            const uint32_t below = j + (uint32_t)__popcll(__ballot(pend < x));
+            if (below >= L) return x == s ? NEXT_NONE : NEXT_MERGE;
+        }
+        if (x == s) {
+            const int l = __ffsll((unsigned long long)wmask) - 1;
+            wave_sync();
+            if (lane == 0) beam[wb + (uint32_t)l] = x | 1ull;
+            wave_sync();
+            wmask &= wmask - 1ull;
+            if (!wmask) scan(wb + 64u, lane);
+        }
+        if (pend == x) pend |= 1ull;
+        if (nk == x) nk |= 1ull;
+        return NEXT_FOUND;
+    }
+    // Enter the new keys (one per lane, KEY_NONE elsewhere; none kept after),
+    // merging the pending ones first if they do not fit beside them; flush:
+    // merge in any case (pn > 0 afterwards: flush again).
+    __device__ __forceinline__ void add(uint64_t &nk, bool flush, int lane)
+    {
+        bool full = false;
+        for (;;) {
+            const uint64_t am = __ballot(nk != KEY_NONE);
+            const uint32_t cnt = (uint32_t)__popcll(am);
+            if (!full && (pn + cnt > 64u || (flush && cnt == 0u))) {
+                merge(lane);
+                nk = filter(nk);
+                full = true;
+                continue;
+            }
+            if (cnt != 0u) {
+                if (nk != KEY_NONE) nkey[pn + lanes_below(am)] = nk;
+                wave_sync();
+                if ((uint32_t)lane - pn < cnt) pend = nkey[lane];
+                wave_sync();
+                pn += cnt;
+                nk = KEY_NONE;
+                if (flush && !full) continue;
+            }
+            pmin = wave_min_open(pend);
+            return;
+        }
+    }
+    // merge the pending keys into the sorted list
+    __device__ __forceinline__ void merge(int lane)
+    {
+        uint64_t key = filter(pend);
+        pn = 0;
+        pend = KEY_NONE;
+        const uint64_t keep = __ballot(key != KEY_NONE);
+        const uint32_t kept = __popcll(keep);
+        if (kept == 0) return;
+        const uint32_t cursor = first_index();
+        // sort the keys: each one's rank is the number of keys below it (they
+        // are distinct), read back from LDS as broadcasts, two keys per read;
+        // the other lanes' KEY_NONE after them, so that reads past the keys
+        // compare false
+        nkey[key != KEY_NONE ? lanes_below(keep) : kept + lanes_below(~keep)] = key;
+        wave_sync();
+        uint32_t rank = 0;
+        {
+            // eight keys per step: four independent LDS reads in flight
+            const ulonglong2 *nk2 = reinterpret_cast<const ulonglong2 *>(nkey);
+            for (uint32_t i = 0; i < kept; i += 8) {
+                const ulonglong2 a0 = nk2[(i >> 1) + 0], a1 = nk2[(i >> 1) + 1];
+                const ulonglong2 a2 = nk2[(i >> 1) + 2], a3 = nk2[(i >> 1) + 3];
+                rank += (a0.x < key ? 1u : 0u) + (a0.y < key ? 1u : 0u);
+                rank += (a1.x < key ? 1u : 0u) + (a1.y < key ? 1u : 0u);
+                rank += (a2.x < key ? 1u : 0u) + (a2.y < key ? 1u : 0u);
+                rank += (a3.x < key ? 1u : 0u) + (a3.y < key ? 1u : 0u);
+            }
+        }
+        wave_sync();
+        if (key != KEY_NONE) nkey[rank] = key;
+        wave_sync();
+        key = lane < (int)kept ? nkey[lane] : KEY_NONE;
+        // rank of each new key in the list and its output slot
+        uint32_t f = 0xFFFFFFFFu;
+        uint32_t pos = 0;
+        if (lane < (int)kept) {
+            pos = lower_bound64_p2(beam, (uint32_t)beam_slots((int32_t)len), key);
+            f = pos + lane;
+        }
+        const uint32_t p0 = bcast0(pos);
+        const uint32_t newlen = min(Lcap, len + kept);
+        const uint32_t w_lo = bcast0(p0 >> 6), w_hi = bcast0((newlen - 1u) >> 6);
+        for (uint32_t w = w_lo + lane; w <= w_hi; w += 64) posbm[w] = 0ull;
+        wave_sync();
+        const bool placed = f < Lcap;
+        if (placed) atomicOr(reinterpret_cast<unsigned long long *>(&posbm[f >> 6]), 1ull << (f & 63u));
+        const uint32_t n_placed = __popcll(__ballot(placed));
+        wave_sync();
+        // rebuild [p0, newlen) from the last 64-slot chunk down
+        uint64_t word = posbm[w_hi];
+        uint32_t below = n_placed - (uint32_t)__popcll(word);   // new keys before the chunk
+        for (int w = (int)w_hi; w >= (int)w_lo; --w) {
+            const uint32_t o = ((uint32_t)w << 6) + lane;
+            const bool act = o >= p0 && o < newlen;
+            const bool isnew = (word >> lane) & 1ull;
+            const uint32_t cnt = below + (uint32_t)__popcll(word & ((1ull << lane) - 1ull));
+            uint64_t val = 0;
+            if (act) val = isnew ? nkey[cnt] : beam[o - cnt];
+            wave_sync();
+            if (act) beam[o] = val;
+            if (w > (int)w_lo) {
+                word = posbm[w - 1];
+                below -= (uint32_t)__popcll(word);
+            }
+            wave_sync();
+        }
+        len = bcast0(newlen);
+        set_thr();
+        scan(min(p0, cursor), lane);
+    }
+};
+
+// ---------------------------------------------------------------------------
+
+// The launch's arguments where they are needed once per query or phase: read
+// again from the kernel's argument segment (a scalar load) instead of being
+// held in scalar registers across the search, which spill.
+__device__ __forceinline__ const PhaseArgs &cold_args()
+{
+    auto p = (const PhaseArgs __attribute__((address_space(4))) *)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return *(const PhaseArgs *)p;
+}
 
 template <class Scorer>
 __global__ void __launch_bounds__(256) phase_kernel(PhaseArgs a)
@@ -820,13 +1074,12 @@ __global__ void __launch_bounds__(256) phase_kernel(PhaseArgs a)
 
     const IndexView ix = a.ix;
     int R = ix.R;   // (made opaque once per expansion, see there)
-    const int d = ix.d, m = ix.m;
+    const int d = ix.d;
     // row gathers ahead of the visited test (scorers that have them, rows they cover)
     const bool spec = Scorer::kSpec && R <= Scorer::kSpecMaxR;
 
     const uint32_t n_in = bcast0(*a.n_active);
     if (n_in <= a.tau_count) return;   // the loop of Alg. 1 has stopped
-    const uint32_t nA = a.t_end < n_in ? a.t_end : n_in;
 
     Visited vs;
     vs.words = htab;
@@ -850,30 +1103,54 @@ __global__ void __launch_bounds__(256) phase_kernel(PhaseArgs a)
     auto load_attrs = [&](uint32_t id, int4 &w0, int4 &w1) { load_attr_record(ix, id, w0, w1); };
     RangeTest rt;
     auto count_phi = [&](const int4 &w0, const int4 &w1) -> uint32_t { return rt.phi(w0, w1, ix.m_pad); };
+    // keys of the c candidates listed in cid[0, c), one per lane. Attribute
+    // records first, then the vectors, so that both gathers are in flight
+    // together; phi is counted afterwards. This lane's candidate (for its
+    // attribute record) and the scorer's first round of ids are LDS reads
+    // issued together.
+    auto score_listed = [&](uint32_t c) -> uint64_t {
+        if (c == 0) return KEY_NONE;
+        wave_sync();
+        const uint32_t my_id = cid[lane];
+        typename Scorer::Ids ids0;
+        sc.read_ids(cid, (int)c, 0, lane, ids0);
+        int4 w0 = make_int4(0, 0, 0, 0), w1 = make_int4(0, 0, 0, 0);
+        if (lane < (int)c) load_attrs(my_id, w0, w1);
+        sc.score(ix.vectors, d, cid, (int)c, cd, lane, ids0);
+        const uint32_t phi = count_phi(w0, w1);
+        wave_sync();
+        return lane < (int)c ? make_key(phi, cd[lane], cid[lane]) : KEY_NONE;
+    };
+    WaveList wl;
+    wl.beam = beam;
+    wl.nkey = nkey;
+    wl.posbm = posbm;
+    wl.len = 0;
 #ifdef BOA_STAGE_PROFILE
     uint64_t prof_acc[BOA_PROF_SLOTS] = {};
 #endif
     for (;;) {
+        const PhaseArgs &aq = cold_args();
         uint32_t t = 0;
-        if (lane == 0) t = atomicAdd(a.queue, 1u);
-        t = bcast0(t) + a.t_begin;
-        if (t >= nA) break;
-        const uint32_t qi = bcast0(a.active[t]);
+        if (lane == 0) t = atomicAdd(aq.queue, 1u);
+        t = bcast0(t) + aq.t_begin;
+        if (t >= min(aq.t_end, n_in)) break;
+        const uint32_t qi = bcast0(aq.active[t]);
 
-        sc.load_query(a.queries, qi, d, lane);
-        rt.set(a.ranges, qi, m, ix.f32_mask);
+        sc.load_query(aq.queries, qi, d, lane);
+        rt.set(aq.ranges, qi, aq.ix.m, aq.ix.f32_mask);
         // the phases of this launch: each restarts the search from the entry
         // point at its own width (Alg. 1 calls Alg. 2 afresh)
         // search state; in the warm-start mode it carries over from phase to
         // phase (the worklist, its expanded flags and the visited set)
         bool spill = false;
-        uint32_t len = 0;
-        for (int p = a.p_begin; p < a.p_end; ++p) {
-        const int L = a.sched[p];
+        for (int p = aq.p_begin; p < cold_args().p_end; ++p) {
+        const PhaseArgs &ap = cold_args();
+        const int L = ap.sched[p];
         // warm start: the list keeps up to the next phase's width while only
         // its first L entries are expanded (the last phase keeps L)
-        const int Lcap = (a.warm && p + 1 < a.p_end) ? a.sched[p + 1] : L;
-        const bool fresh = !a.warm || p == a.p_begin;
+        const int Lcap = (ap.warm && p + 1 < ap.p_end) ? ap.sched[p + 1] : L;
+        const bool fresh = !ap.warm || p == ap.p_begin;
         if (fresh) {
             // the bitmap starts with no bit set, the table with every slot
             // free, the worklist with every slot past its (zero) length KEY_NONE
@@ -881,10 +1158,10 @@ __global__ void __launch_bounds__(256) phase_kernel(PhaseArgs a)
             const uint4 z = make_uint4(f, f, f, f);
             uint4 *h4 = reinterpret_cast<uint4 *>(htab);
             for (uint32_t i = lane; i < table_words >> 2; i += 64) h4[i] = z;
-            for (int i = lane; i < Lb; i += 64) beam[i] = KEY_NONE;
+            wl.clear(Lb, lane);
             spill = false;
-            len = 0;
         }
+        spill = bcast0(spill ? 1u : 0u) != 0u;
         wave_sync();
 
         // test-and-insert of this lane's neighbour: 1 new, 0 seen (or padding)
@@ -918,26 +1195,24 @@ __global__ void __launch_bounds__(256) phase_kernel(PhaseArgs a)
             }
             return vst;
         };
-        uint32_t E = 0, S = 0;
-        int expanded_j = -1;
+        uint32_t E = 0, S = bcast0(fresh ? 1u : 0u);
+        wl.begin(L, Lcap, lane);
         // adjacency row already in flight for the node expected next
         uint32_t pf_id = BOA_PAD;
-        uint64_t pf_key = KEY_NONE;
         uint32_t pf_row = BOA_PAD;
+        // keys of the last expansion's new nodes, not yet in the worklist
+        uint64_t nk = KEY_NONE;
 
-        // the entry point is scored and entered before the first expansion
-        // (a warm phase continues with nothing new to score)
-        uint32_t c = fresh ? 1u : 0u;
-        if (fresh && lane == 0) {
-            if (a.vis_bitmap) htab[ix.entry >> 5] |= 1u << (ix.entry & 31u);
-            else visit_lds(vs, ix.entry);
-            cid[0] = ix.entry;
+        // the entry point is scored before the first expansion (a warm phase
+        // continues with nothing new to score)
+        if (fresh) {
+            if (lane == 0) {
+                if (a.vis_bitmap) htab[ix.entry >> 5] |= 1u << (ix.entry & 31u);
+                else visit_lds(vs, ix.entry);
+                cid[0] = ix.entry;
+            }
+            nk = score_listed(1u);
         }
-        // row-gather scorers: the keys of the last expansion's new
-        // neighbours (one per row position, KEY_NONE elsewhere), scored in
-        // that expansion and entered at the top of the next iteration
-        uint32_t spec_c = 0;
-        uint64_t spec_key = KEY_NONE;
 
         for (;;) {
             // Row-gather scorers re-read the row length as an opaque (uniform)
@@ -953,150 +1228,19 @@ __global__ void __launch_bounds__(256) phase_kernel(PhaseArgs a)
                 asm volatile("" : "+v"(r));
                 R = __builtin_amdgcn_readfirstlane(r);
             }
-            uint32_t scan_from = (uint32_t)(expanded_j + 1);
-            // ---- score the c new candidates listed in cid[0, c)
-            PROF_T(t_score0);
-            if (c > 0 || spec_c > 0) {
-                wave_sync();
-                uint64_t key = KEY_NONE;
-                if (Scorer::kSpec && spec_c > 0) {
-                    S += spec_c;
-                    key = spec_key;
-                    spec_c = 0;
-                } else {
-                    S += c;
-                    // attribute records first, then the vectors, so that both
-                    // gathers are in flight together; phi is counted afterwards.
-                    // This lane's candidate (for its attribute record) and the
-                    // scorer's first round of ids: LDS reads issued together
-                    const uint32_t my_id = cid[lane];
-                    typename Scorer::Ids ids0;
-                    sc.read_ids(cid, (int)c, 0, lane, ids0);
-                    int4 w0 = make_int4(0, 0, 0, 0), w1 = make_int4(0, 0, 0, 0);
-                    if (lane < (int)c) load_attrs(my_id, w0, w1);
-                    sc.score(a.ix.vectors, d, cid, (int)c, cd, lane, ids0);
-                    const uint32_t phi = count_phi(w0, w1);
-                    wave_sync();
-                    if (lane < (int)c) key = make_key(phi, cd[lane], cid[lane]);
-                    c = 0;
-                }
-                PROF_T(t_score1);
-                PROF_ADD(2, t_score1 - t_score0);
-                if (len == (uint32_t)Lcap && key >= beam[Lcap - 1]) key = KEY_NONE;  // cannot enter
-                const uint64_t keep = __ballot(key != KEY_NONE);
-                const uint32_t kept = __popcll(keep);
-                if (kept > 0) {
-                    // sort the survivors: each one's rank is the number of
-                    // survivors below it (keys are distinct), read back from
-                    // LDS as broadcasts, two keys per read
-                    // survivors first, the other lanes' KEY_NONE after them, so
-                    // that reads past the survivors compare false
-                    nkey[key != KEY_NONE ? lanes_below(keep) : kept + lanes_below(~keep)] = key;
-                    wave_sync();
-                    uint32_t rank = 0;
-                    {
-                        // eight keys per step: four independent LDS reads in flight
-                        const ulonglong2 *nk2 = reinterpret_cast<const ulonglong2 *>(nkey);
-                        for (uint32_t i = 0; i < kept; i += 8) {
-                            const ulonglong2 a0 = nk2[(i >> 1) + 0], a1 = nk2[(i >> 1) + 1];
-                            const ulonglong2 a2 = nk2[(i >> 1) + 2], a3 = nk2[(i >> 1) + 3];
-                            rank += (a0.x < key ? 1u : 0u) + (a0.y < key ? 1u : 0u);
-                            rank += (a1.x < key ? 1u : 0u) + (a1.y < key ? 1u : 0u);
-                            rank += (a2.x < key ? 1u : 0u) + (a2.y < key ? 1u : 0u);
-                            rank += (a3.x < key ? 1u : 0u) + (a3.y < key ? 1u : 0u);
-                        }
-                    }
-                    wave_sync();
-                    if (key != KEY_NONE) nkey[rank] = key;
-                    wave_sync();
-                    key = lane < (int)kept ? nkey[lane] : KEY_NONE;
-                    // the next node is the smaller of the best new key and the
-                    // entry predicted at selection: start its row load now
-                    {
-                        const uint64_t k0 = __shfl(key, 0);
-                        if (k0 < pf_key) {
-                            pf_key = k0;
-                            pf_id = key_id(k0);
-                            pf_row = ix.adj[(size_t)pf_id * R + (lane < R ? lane : R - 1)];
-                            PROF_ADD(9, 1);
-                        }
-                    }
-                    PROF_T(t_sort1);
-                    PROF_ADD(3, t_sort1 - t_score1);
-                    // rank of each new key in the worklist and its output slot
-                    uint32_t f = 0xFFFFFFFFu;
-                    uint32_t pos = 0;
-                    if (lane < (int)kept) {
-                        pos = lower_bound64_p2(beam, (uint32_t)beam_slots((int32_t)len), key);
-                        f = pos + lane;
-                    }
-                    const uint32_t p0 = bcast0(pos);
-                    const uint32_t newlen = min((uint32_t)Lcap, len + kept);
-                    const uint32_t w_lo = bcast0(p0 >> 6), w_hi = bcast0((newlen - 1u) >> 6);
-                    for (uint32_t w = w_lo + lane; w <= w_hi; w += 64) posbm[w] = 0ull;
-                    wave_sync();
-                    const bool placed = f < (uint32_t)Lcap;
-                    if (placed) atomicOr(reinterpret_cast<unsigned long long *>(&posbm[f >> 6]),
-                                         1ull << (f & 63u));
-                    const uint32_t n_placed = __popcll(__ballot(placed));
-                    wave_sync();
-                    PROF_T(t_rank1);
-                    PROF_ADD(4, t_rank1 - t_sort1);
-                    PROF_ADD(7, w_hi - w_lo + 1);
-                    // rebuild [p0, newlen) from the last 64-slot chunk down
-                    uint64_t word = posbm[w_hi];
-                    uint32_t below = n_placed - (uint32_t)__popcll(word);   // new keys before chunk
-                    for (int w = (int)w_hi; w >= (int)w_lo; --w) {
-                        const uint32_t o = ((uint32_t)w << 6) + lane;
-                        const bool act = o >= p0 && o < newlen;
-                        const bool isnew = (word >> lane) & 1ull;
-                        const uint32_t cnt = below + (uint32_t)__popcll(word & ((1ull << lane) - 1ull));
-                        uint64_t val = 0;
-                        if (act) val = isnew ? nkey[cnt] : beam[o - cnt];
-                        wave_sync();
-                        if (act) beam[o] = val;
-                        if (w > (int)w_lo) {
-                            word = posbm[w - 1];
-                            below -= (uint32_t)__popcll(word);
-                        }
-                        wave_sync();
-                    }
-                    len = newlen;
-                    if (p0 < scan_from) scan_from = p0;
-                    PROF_T(t_merge1);
-                    PROF_ADD(5, t_merge1 - t_rank1);
-                }
-            }
+            // ---- the nearest unexpanded node, also among the keys just scored
             PROF_T(t_sel0);
-
-            // ---- select the nearest unexpanded entry among the first L (and
-            // predict the one after it)
-            const uint32_t lim = min(len, (uint32_t)L);
-            int j = -1, j2 = -1;
-            uint64_t ku = 0, kn = KEY_NONE;   // their keys, taken from the lanes that read them
-            for (uint32_t b0 = scan_from; b0 < lim; b0 += 64) {
-                const uint32_t i = b0 + lane;
-                const uint64_t bk = i < lim ? beam[i] : 1ull;
-                const uint64_t mk = __ballot(!(bk & 1ull));
-                if (mk) {
-                    const int l1 = __ffsll((unsigned long long)mk) - 1;
-                    j = (int)b0 + l1;
-                    ku = readlane64(bk, l1);
-                    const uint64_t rest = mk & (mk - 1ull);
-                    if (rest) {
-                        const int l2 = __ffsll((unsigned long long)rest) - 1;
-                        j2 = (int)b0 + l2;
-                        kn = readlane64(bk, l2);
-                    }
-                    break;
-                }
-            }
-            if (j < 0) break;   // converged: every entry expanded
+            uint64_t ku;
+            const int found = wl.next(nk, ku, lane);
             PROF_T(t_sel1);
             PROF_ADD(0, t_sel1 - t_sel0);
-            expanded_j = j;
-            wave_sync();
-            if (lane == 0) beam[j] = ku | 1ull;
+            if (found != NEXT_FOUND) {
+                wl.add(nk, true, lane);
+                // converged (every entry among the first L expanded), and the
+                // list in order for what reads it
+                if (found == NEXT_NONE && wl.pn == 0) break;
+                continue;
+            }
             const uint32_t u = key_id(ku);
             E += 1;
 
@@ -1109,9 +1253,10 @@ __global__ void __launch_bounds__(256) phase_kernel(PhaseArgs a)
                 v = lane < R ? ix.adj[(size_t)u * R + lane] : BOA_PAD;
             }
             PROF_ADD(10, 1);
-#ifdef BOA_STAGE_PROFILE
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // row in hand, for the split below
-#endif
+            // (the row is waited for here, on every path: a wait that only one
+            // of the paths below needs would be placed where they join, and
+            // would hold the visited test back until the gathers are done)
+            asm volatile("" : "+v"(v));
             PROF_T(t_row);
             PROF_ADD(12, t_row - t_sel1);
 
@@ -1133,46 +1278,55 @@ __global__ void __launch_bounds__(256) phase_kernel(PhaseArgs a)
             PROF_ADD(13, t_vl - t_row);
             const bool is_new = vst > 0;
             const uint64_t nm = __ballot(is_new);
-            c = __popcll(nm);
+            const uint32_t c = __popcll(nm);
             PROF_ADD(14, c == 0 ? 1 : 0);
             if (!spec && is_new) cid[lanes_below(nm)] = v;
+            S += c;
+            // ---- the previous expansion's keys enter the worklist while the
+            // gathers are in flight
+            wl.add(nk, false, lane);
+            PROF_T(t_add);
+            PROF_ADD(3, t_add - t_vl);
             // the row of the entry expected next is requested only now: a
             // load issued before the visited test would be waited for there
             // (loads retire in order), while from here it overlaps the gathers.
             // It is requested on every path (the entry's row when nothing is
             // predicted), so that waiting for the gathers is one fixed count.
-            pf_key = kn;
             {
                 // (every lane loads, lanes past R from the row's last slot:
                 // a load under a branch would leave the count unknown; the
                 // row is masked where it is used, since a select here would
                 // wait for the load at once)
-                const uint32_t pid = j2 >= 0 ? key_id(kn) : ix.entry;
-                pf_id = j2 >= 0 ? pid : BOA_PAD;
+                const uint64_t kn = min(wl.first_key(), wl.pmin);
+                const uint32_t pid = kn != KEY_NONE ? key_id(kn) : ix.entry;
+                pf_id = kn != KEY_NONE ? pid : BOA_PAD;
                 pf_row = ix.adj[(size_t)pid * R + (lane < R ? lane : R - 1)];
             }
             PROF_T(t_vis1);
             PROF_ADD(1, t_vis1 - t_sel1);
             PROF_ADD(6, spill ? 1 : 0);
+            // ---- the new nodes' keys (one per lane)
             if (spec) {
-                // the gathered neighbours' distances, then the new ones' keys
                 const uint32_t phi = count_phi(aw0, aw1);
                 sc.score_row(rg, d, R, cd, lane);
                 wave_sync();
-                spec_key = is_new ? make_key(phi, cd[lane], v) : KEY_NONE;
-                spec_c = c;
-                c = 0;
-                PROF_T(t_spec1);
-                PROF_ADD(2, t_spec1 - t_vis1);
+                nk = is_new ? make_key(phi, cd[lane], v) : KEY_NONE;
+            } else {
+                nk = score_listed(c);
             }
+            nk = wl.filter(nk);
+            PROF_T(t_sc1);
+            PROF_ADD(2, t_sc1 - t_vis1);
         }
+        const uint32_t len = wl.len;
 
         // ---- epilogue: confidence (Eq. 3) over the phase's worklist (its
         // first L entries); the result is written by the last phase the
         // query runs in this launch
         wave_sync();
-        const uint32_t n_valid = lower_bound64(beam, min(len, (uint32_t)L), KEY_PHI1);
-        const int k = a.k;
+        const PhaseArgs &ae = cold_args();
+        const uint32_t n_valid = bcast0(lower_bound64(beam, min(len, (uint32_t)L), KEY_PHI1));
+        const int k = ae.k;
         uint32_t conf = 0;
         // the result (the first valid entries) and the two distances of Eq. 3
         uint64_t res_key[2] = {KEY_NONE, KEY_NONE};   // (product-quantised search: lanes' top-k keys)
@@ -1185,7 +1339,7 @@ __global__ void __launch_bounds__(256) phase_kernel(PhaseArgs a)
                 const uint32_t e = b0 + lane;
                 if (e < n_valid) {
                     const uint32_t id = key_id(beam[e]);
-                    const float dx = exact_dist_lane(a.ix.vectors, a.queries, qi, id, d, a.vec_u8 != 0);
+                    const float dx = exact_dist_lane(ae.ix.vectors, ae.queries, qi, id, d, ae.vec_u8 != 0);
                     rrk[e] = ((uint64_t)__float_as_uint(dx) << 32) | id;
                 }
             }
@@ -1214,20 +1368,23 @@ __global__ void __launch_bounds__(256) phase_kernel(PhaseArgs a)
             double dk = sqrt((double)d_k);
             double dmax = sqrt((double)d_max);
             double gamma = dmax == 0.0 ? 0.0 : (dmax - dk) / dmax;
-            conf = gamma <= a.eps ? 1u : 0u;
+            // (uniform, also for the compiler: a phase loop that lanes could
+            // leave one by one would put every value it carries in vector
+            // registers and every test on them under an execution mask)
+            conf = bcast0(gamma <= ae.eps ? 1u : 0u);
         }
-        const bool last = conf != 0u || p + 1 == a.p_end;
+        const bool last = conf != 0u || p + 1 == ae.p_end;
         if (lane == 0) {
-            const size_t ps = (size_t)p * a.nq + qi;
-            if (a.qstat) {   // per-phase statistics (absent in the allocation-free search)
-                a.qstat[ps] = (uint8_t)(1u + conf + (spill ? 4u : 0u));
-                a.qE[ps] = E;
-                a.qS[ps] = S;
+            const size_t ps = (size_t)p * ae.nq + qi;
+            if (ae.qstat) {   // per-phase statistics (absent in the allocation-free search)
+                ae.qstat[ps] = (uint8_t)(1u + conf + (spill ? 4u : 0u));
+                ae.qE[ps] = E;
+                ae.qS[ps] = S;
             }
-            if (a.user_E) a.user_E[qi] += E;
-            if (a.user_S) a.user_S[qi] += S;
-            if (a.write_conf) a.conf[t] = (uint8_t)conf;
-            if (last) a.final_L[qi] = L;
+            if (ae.user_E) ae.user_E[qi] += E;
+            if (ae.user_S) ae.user_S[qi] += S;
+            if (ae.write_conf) ae.conf[t] = (uint8_t)conf;
+            if (last) ae.final_L[qi] = L;
         }
         if (last) {
             for (int q = lane; q < k; q += 64) {
@@ -1244,8 +1401,8 @@ __global__ void __launch_bounds__(256) phase_kernel(PhaseArgs a)
                         dd = key_dist(kk);
                     }
                 }
-                a.ids[(size_t)qi * k + q] = id;
-                a.dists[(size_t)qi * k + q] = dd;
+                ae.ids[(size_t)qi * k + q] = id;
+                ae.dists[(size_t)qi * k + q] = dd;
             }
         }
         wave_sync();
