@@ -552,8 +552,9 @@ int stage_profile_end(unsigned long long *prof, size_t pn, int L, int waves, hip
     return BOA_OK;
 }
 
-// the same for the two-wave escalation launch (one row per block)
-int stage_profile_pair_end(unsigned long long *prof, size_t pn, int L, int blocks, hipStream_t st)
+// the same for a team launch (one row per block)
+int stage_profile_team_end(unsigned long long *prof, size_t pn, int L, int blocks, int h_slots, int64_t cap,
+                           hipStream_t st)
 {
     std::vector<unsigned long long> h(pn);
     HIP_TRY(hipMemcpyAsync(h.data(), prof, pn * 8, hipMemcpyDeviceToHost, st));
@@ -562,12 +563,10 @@ int stage_profile_pair_end(unsigned long long *prof, size_t pn, int L, int block
     for (size_t i = 0; i < pn; ++i) tot[i % BOA_PROF_SLOTS] += (double)h[i];
     const double ne = tot[10] > 0 ? tot[10] : 1;
     std::fprintf(stderr,
-                 "[stage-profile] two-wave escalation L=%d blocks=%d expansions=%.0f cycles/expansion: "
-                 "iteration %.0f | worklist wave: merge and select %.0f, wait %.0f | gather wave: guessed "
-                 "expansion %.0f, wait %.0f, hand-over %.0f | guesses: hit %.3f miss %.3f none %.3f, of a new "
-                 "key %.3f; no entry after the selected one %.3f\n",
-                 L, blocks, tot[10], tot[5] / ne, tot[0] / ne, tot[3] / ne, tot[1] / ne, tot[4] / ne, tot[2] / ne,
-                 tot[8] / ne, tot[9] / ne, tot[14] / ne, tot[13] / ne, tot[12] / ne);
+                 "[stage-profile] team launch L=%d blocks=%d of %lld table %d expansions=%.0f cycles/expansion: select "
+                 "%.0f enter %.0f name %.0f wait %.0f test %.0f | named ahead %.2f, keys ready %.2f\n",
+                 L, blocks, (long long)cap, h_slots, tot[10], tot[0] / ne, tot[3] / ne, tot[1] / ne, tot[2] / ne,
+                 tot[13] / ne, tot[8] / ne, tot[12] / ne);
     (void)hipFree(prof);
     return BOA_OK;
 }
@@ -633,6 +632,59 @@ PhasePlan plan_escalation(const boa_index *ix, int32_t L, int64_t S, int32_t for
     return dflt;
 }
 
+// A launch with a team of waves per query over up to S queries.
+struct TeamPlan {
+    // Blocks (queries) resident at once, and so many queries it serves (0: not
+    // available). Beyond that a second round begins, while a launch with one
+    // wave per query takes about as long for 100 queries as for 1,000: 777
+    // queries at width 500 (d = 100) take 1.33 ms in one round of teams, 2.23
+    // in two (512 at once), 2.36 with one wave each; 2,401 at width 512
+    // (d = 96) take 12.6 ms of search in five rounds and 9.5 with one wave.
+    int64_t capacity = 0;
+    int32_t blocks = 0, lds = 0, h_slots = 0, parts = 1;
+    uint32_t vis_words = 0;  // LDS words of the visited set; h_slots == 0: a bitmap over all ids
+};
+
+// Visited set of a team launch: the exact bitmap, or else the largest table,
+// with which all S queries are resident at once; else what holds most.
+TeamPlan plan_team(const boa_index *ix, int32_t L, int64_t S, int32_t forced_h)
+{
+    TeamPlan best;
+    const int sl = scorer_lds_bytes(ix->vec_dtype, ix->view.d, true, 0);
+    auto consider = [&](uint32_t words, int32_t h, int parts) -> bool {
+        const size_t lds = team_lds_bytes(L, parts, words, sl);
+        if (lds > ix->lds_per_block_hw) return false;
+        TeamPlan pl;
+        pl.lds = (int32_t)lds;
+        pl.h_slots = h;
+        pl.vis_words = words;
+        pl.parts = parts;
+        pl.capacity = (int64_t)team_occupancy(ix->vec_dtype, ix->view.d, parts, lds) * ix->num_cu;
+        pl.blocks = (int32_t)std::min<int64_t>(pl.capacity, std::max<int64_t>(S, 1));
+        if (pl.capacity > best.capacity) best = pl;
+        return pl.capacity > 0 && pl.capacity >= S;
+    };
+    const uint32_t bits = (uint32_t)(((ix->view.n + 31) / 32 + 3) & ~(int64_t)3);
+    const uint32_t lo = std::max<uint32_t>(1024u, min_table_slots(ix));
+    // Two waves share a row where one does not cover it in one round trip of
+    // gathers (rows of more than 32 entries, or of more than 256 bytes a
+    // vector) and the waves that takes still leave room for all queries: 239
+    // queries at width 512, R = 64, d = 128 float32: 2.95 instead of 3.56 ms;
+    // R = 16, d = 32: 0.51 instead of 0.49 ms.
+    const size_t row = (size_t)ix->view.d * (ix->vec_dtype == BOA_VEC_U8 ? 1 : 4);
+    for (int parts = ix->view.R > 32 || row > 256 ? 2 : 1; parts >= 1; --parts) {
+        if (forced_h > 0) {
+            if (consider((uint32_t)forced_h / 2u, forced_h, parts)) break;
+            continue;
+        }
+        if (consider(bits, 0, parts)) break;
+        bool found = false;
+        for (uint32_t h = 16384u; h >= lo && !found; h >>= 1) found = consider(h / 2u, (int32_t)h, parts);
+        if (found) break;
+    }
+    return best;
+}
+
 // Device memory one search works in: the index's grown-on-demand workspace
 // (boa_search) or a carve-out of the file-scope scratch array
 // (boa_search_noalloc).
@@ -658,7 +710,7 @@ struct Request {
     int32_t sched[BOA_MAX_PHASES];
     int32_t n_phases;
     bool plus, split, fused, warm;
-    bool pair;                // split escalation with two waves per query where it applies
+    bool team;                // teams of waves per query where they apply
     int32_t pq_m;             // > 0: product-quantised traversal with that many subspaces
     int32_t sub;              // BOA+ sub-batches (1 otherwise)
     int32_t n_counters;
@@ -704,7 +756,7 @@ int validate(const boa_index *ix, const void *queries, const int32_t *ranges, in
     rq.pq_m = p->pq ? ix->pq_m : 0;
     if (p->escalation_waves != 0 && p->escalation_waves != 1)
         return fail(BOA_EINVAL, "escalation_waves must be 0 or 1");
-    rq.pair = p->escalation_waves == 0 && rq.pq_m == 0;
+    rq.team = p->escalation_waves == 0 && rq.pq_m == 0;
     rq.sub = rq.plus ? std::min<int64_t>(p->sub_batches, std::max<int64_t>(nq, 1)) : 1;
     rq.n_counters = rq.n_phases * (rq.sub + 1) + 8;
     rq.tau_count = (uint32_t)std::floor(p->tau * (double)nq);
@@ -714,7 +766,7 @@ int validate(const boa_index *ix, const void *queries, const int32_t *ranges, in
 // Launch plans of every phase, and the number of wave slots (spill bitmaps)
 // the search may use at once.
 int plan_search(const boa_index *ix, const Request &rq, int64_t nq, int32_t forced_h, PhasePlan *plans,
-                uint64_t *slots_out)
+                TeamPlan *teams, uint64_t *slots_out)
 {
     uint64_t slots = 0;
     const int32_t Lw = rq.sched[rq.n_phases - 1];
@@ -733,6 +785,10 @@ int plan_search(const boa_index *ix, const Request &rq, int64_t nq, int32_t forc
             return fail(BOA_EUNSUPPORTED, "beamwidth too wide for the LDS budget");
         slots = std::max<uint64_t>(slots, (uint64_t)pl.blocks * pl.wpb);
         plans[ph] = pl;
+        if (rq.team) {
+            teams[ph] = plan_team(ix, widest ? Lw : rq.sched[ph], nq, forced_h);
+            slots = std::max<uint64_t>(slots, (uint64_t)teams[ph].blocks);
+        }
     }
     if (rq.split && rq.n_phases > 1) {
         // every grid the escalation launch may take (it has at most nq waves)
@@ -760,7 +816,7 @@ int cap_to_slots(PhasePlan &pl, uint64_t slots)
 }
 
 int run_search(boa_index *ix, const void *queries, const int32_t *ranges, int64_t nq, const boa_params *p,
-               const Request &rq, PhasePlan *plans, uint32_t *ids, float *dists, int32_t *final_L,
+               const Request &rq, PhasePlan *plans, const TeamPlan *teams, uint32_t *ids, float *dists, int32_t *final_L,
                uint32_t *expansions, uint32_t *scored, const Workspace &ws, hipStream_t st)
 {
     const int32_t n_phases = rq.n_phases;
@@ -823,10 +879,37 @@ int run_search(boa_index *ix, const void *queries, const int32_t *ranges, int64_
     base.vec_u8 = ix->vec_dtype == BOA_VEC_U8 ? 1 : 0;
     for (int32_t ph = 0; ph < n_phases; ++ph) base.sched[ph] = sched[ph];
     int ev = 0;
-    // one search launch, bracketed by HIP events when timing
-    auto launch = [&](const PhaseArgs &a, int blocks, hipStream_t s, bool wide, int phase) -> int {
+    // One search launch over at most `bound` queries (exact: their number),
+    // bracketed by HIP events when timing: by a team of waves per query where
+    // so few are served, by one wave per query otherwise. Where only the
+    // device knows the number, a launch of each kind.
+    auto launch = [&](PhaseArgs a, int blocks, hipStream_t s, bool wide, int phase, const TeamPlan &tp, int64_t bound,
+                      bool exact, uint64_t max_slots) -> int {
         if (ws.timing) HIP_TRY(hipEventRecord(ix->ev_start[ev], s));
-        HIP_TRY(launch_phase(a, ix->vec_dtype, blocks, s, wide));
+        const bool team = tp.capacity > 0 && (!exact || bound <= tp.capacity);
+        a.min_active = 0;
+        a.max_active = 0xFFFFFFFFu;
+        if (team) {
+            PhaseArgs e = a;
+            e.h_log2 = tp.h_slots ? ilog2((uint32_t)tp.h_slots) : 3;   // (unused with the bitmap)
+            e.vis_bitmap = tp.h_slots ? 0 : 1;
+            e.vis_words = tp.vis_words;
+            e.lds_per_wave = tp.lds;
+            e.waves_per_block = 1;
+            if (bound > tp.capacity) e.max_active = a.min_active = (uint32_t)tp.capacity;
+            const int64_t tb = std::min<int64_t>(std::min<int64_t>(tp.blocks, bound), (int64_t)max_slots);
+#ifdef BOA_STAGE_PROFILE
+            unsigned long long *tprof = nullptr;
+            const size_t tpn = (size_t)tb * BOA_PROF_SLOTS;
+            if (int rc2 = stage_profile_begin(&tprof, tpn, s)) return rc2;
+            e.prof = tprof;
+#endif
+            HIP_TRY(launch_team(e, ix->vec_dtype, tp.parts, (int)tb, s));
+#ifdef BOA_STAGE_PROFILE
+            if (int rc2 = stage_profile_team_end(tprof, tpn, a.L_alloc, (int)tb, tp.h_slots, tp.capacity, s)) return rc2;
+#endif
+        }
+        if (!team || bound > tp.capacity) HIP_TRY(launch_phase(a, ix->vec_dtype, blocks, s, wide));
         if (ws.timing) {
             HIP_TRY(hipEventRecord(ix->ev_end[ev], s));
             ix->launch_phase.push_back({phase, ev});
@@ -857,7 +940,7 @@ int run_search(boa_index *ix, const void *queries, const int32_t *ranges, int64_
         if (int rc2 = stage_profile_begin(&prof, pn, st)) return rc2;
         a.prof = prof;
 #endif
-        if (int rc = launch(a, pl.blocks, st, pl.wide, 0)) return rc;
+        if (int rc = launch(a, pl.blocks, st, pl.wide, 0, teams[0], nq, true, ws.slots)) return rc;
 #ifdef BOA_STAGE_PROFILE
         std::fprintf(stderr, "[stage-profile] fused launch%s: table %d slots, %d waves (all phases)\n",
                      rq.warm ? " (warm start)" : "", pl.h_slots, pl.blocks * pl.wpb);
@@ -881,7 +964,7 @@ int run_search(boa_index *ix, const void *queries, const int32_t *ranges, int64_
         a.lds_per_wave = p0.lds_per_wave;
         a.waves_per_block = p0.wpb;
         a.slot_base = 0;
-        if (int rc = launch(a, p0.blocks, st, false, 0)) return rc;
+        if (int rc = launch(a, p0.blocks, st, false, 0, teams[0], nq, true, ws.slots)) return rc;
         p0.launches = 1;
         if (n_phases > 1) {
             // ... then its survivors, compacted, through every later width
@@ -922,41 +1005,12 @@ int run_search(boa_index *ix, const void *queries, const int32_t *ranges, int64_
                 if (int rc2 = stage_profile_begin(&prof, pn, st)) return rc2;
                 e.prof = prof;
 #endif
-                // two waves per query where the bitmap plan applies and every
-                // survivor's block is still resident at once
-                bool pair = rq.pair && pe.vis_bitmap;
-                if (pair) {
-                    const size_t lds = pair_lds_bytes(Lw, e.vis_words,
-                                                      scorer_lds_bytes(ix->vec_dtype, ix->view.d, true, 0));
-                    const int occ = lds <= ix->lds_per_block_hw ? pair_occupancy(ix->vec_dtype, ix->view.d, lds) : 0;
-                    const int64_t cap = (int64_t)occ * ix->num_cu;
-                    pair = cap >= (int64_t)S;
-                    if (pair) {
-                        pe.blocks = (int32_t)S;
-                        pe.wpb = 2;
-                        e.lds_per_wave = (int32_t)lds;
-                        e.waves_per_block = 2;
-                    }
-                }
-                if (pair) {
-#ifdef BOA_STAGE_PROFILE
-                    unsigned long long *pprof = nullptr;
-                    const size_t ppn = (size_t)pe.blocks * BOA_PROF_SLOTS;
-                    if (int rc2 = stage_profile_begin(&pprof, ppn, st)) return rc2;
-                    e.prof = pprof;
-#endif
-                    if (ws.timing) HIP_TRY(hipEventRecord(ix->ev_start[ev], st));
-                    HIP_TRY(launch_pair(e, ix->vec_dtype, pe.blocks, st));
-                    if (ws.timing) {
-                        HIP_TRY(hipEventRecord(ix->ev_end[ev], st));
-                        ix->launch_phase.push_back({1, ev});
-                        ++ev;
-                    }
-#ifdef BOA_STAGE_PROFILE
-                    if (int rc2 = stage_profile_pair_end(pprof, ppn, Lw, (int)S, st)) return rc2;
-#endif
-                } else if (int rc = launch(e, pe.blocks, st, true, 1)) {
-                    return rc;
+                const TeamPlan te = rq.team ? plan_team(ix, Lw, S, p->lds_hash_slots) : TeamPlan();
+                if (int rc = launch(e, pe.blocks, st, true, 1, te, S, true, ws.slots)) return rc;
+                if (te.capacity > 0 && (int64_t)S <= te.capacity) {
+                    pe.h_slots = te.h_slots;
+                    pe.wpb = 1;
+                    pe.blocks = te.blocks;
                 }
 #ifdef BOA_STAGE_PROFILE
                 std::fprintf(stderr, "[stage-profile] split escalation: %u survivors, table %d slots, %d waves\n",
@@ -992,7 +1046,7 @@ int run_search(boa_index *ix, const void *queries, const int32_t *ranges, int64_
             if (int rc2 = stage_profile_begin(&prof, pn, st)) return rc2;
             a.prof = prof;
 #endif
-            if (int rc = launch(a, pl.blocks, st, false, ph)) return rc;
+            if (int rc = launch(a, pl.blocks, st, false, ph, teams[ph], nq, ph == 0, ws.slots)) return rc;
 #ifdef BOA_STAGE_PROFILE
             if (int rc2 = stage_profile_end(prof, pn, pl.L, pl.blocks * pl.wpb, st)) return rc2;
 #endif
@@ -1045,7 +1099,7 @@ int run_search(boa_index *ix, const void *queries, const int32_t *ranges, int64_
             a.slot_base = 0;
             const int64_t span = a.t_end - a.t_begin;
             const int blocks = (int)std::min<int64_t>(p0.blocks, (span + p0.wpb - 1) / p0.wpb);
-            if (int rc = launch(a, blocks, st, false, 0)) return rc;
+            if (int rc = launch(a, blocks, st, false, 0, teams[0], span, true, half_slots)) return rc;
             p0.launches += 1;
             AppendArgs ap{};
             ap.in = ws.active[0] + a.t_begin;
@@ -1073,7 +1127,8 @@ int run_search(boa_index *ix, const void *queries, const int32_t *ranges, int64_
                 e.lds_per_wave = pe.lds_per_wave;
                 e.waves_per_block = pe.wpb;
                 e.slot_base = (uint32_t)half_slots;   // disjoint spill bitmaps from stream 0
-                if (int rc = launch(e, pe.blocks, ix->aux, false, 1)) return rc;
+                if (int rc = launch(e, pe.blocks, ix->aux, false, 1, teams[1], std::min<int64_t>(nq, half * B), false, half_slots))
+                    return rc;
                 pe.launches += 1;
             }
         }
@@ -1092,7 +1147,7 @@ int run_search(boa_index *ix, const void *queries, const int32_t *ranges, int64_
             e.lds_per_wave = pe.lds_per_wave;
             e.waves_per_block = pe.wpb;
             e.slot_base = 0;
-            if (int rc = launch(e, pe.blocks, st, false, 1)) return rc;
+            if (int rc = launch(e, pe.blocks, st, false, 1, teams[1], nq - half * B, false, half_slots)) return rc;
             pe.launches += 1;
         }
         if (n_phases > 1) {
@@ -1163,8 +1218,9 @@ extern "C" int boa_search(boa_index *ix, const void *queries, const int32_t *ran
     if (cur_dev != ix->device) return fail(BOA_EINVAL, "index lives on another device than the current one");
 
     PhasePlan plans[BOA_MAX_PHASES];
+    TeamPlan teams[BOA_MAX_PHASES];
     uint64_t slots = 0;
-    if (int rc = plan_search(ix, rq, nq, p->lds_hash_slots, plans, &slots)) return rc;
+    if (int rc = plan_search(ix, rq, nq, p->lds_hash_slots, plans, teams, &slots)) return rc;
     if (int rc = ensure_workspace(ix, nq, rq.n_phases, rq.plus ? 2 * slots : slots, rq.n_counters, rq.plus))
         return rc;
     if (int rc = ensure_events(ix, (size_t)rq.n_phases * (rq.sub + 1))) return rc;
@@ -1187,7 +1243,7 @@ extern "C" int boa_search(boa_index *ix, const void *queries, const int32_t *ran
     ws.slots = ix->slots_cap;
     ws.pool = ix->pool;
     ws.timing = true;
-    return run_search(ix, queries, ranges, nq, p, rq, plans, ids, dists, final_L, expansions, scored, ws, st);
+    return run_search(ix, queries, ranges, nq, p, rq, plans, teams, ids, dists, final_L, expansions, scored, ws, st);
 }
 
 extern "C" int boa_search_noalloc(boa_index *ix, const void *queries, const int32_t *ranges, int64_t nq,
@@ -1207,8 +1263,9 @@ extern "C" int boa_search_noalloc(boa_index *ix, const void *queries, const int3
     if (int rc = scratch_for_device(cur_dev, &base)) return rc;
 
     PhasePlan plans[BOA_MAX_PHASES];
+    TeamPlan teams[BOA_MAX_PHASES];
     uint64_t slots = 0;
-    if (int rc = plan_search(ix, rq, nq, p->lds_hash_slots, plans, &slots)) return rc;
+    if (int rc = plan_search(ix, rq, nq, p->lds_hash_slots, plans, teams, &slots)) return rc;
 
     // carve the scratch: fixed-size pieces first (256-byte aligned), then
     // the spill bitmaps of as many wave slots as the rest holds
@@ -1238,7 +1295,7 @@ extern "C" int boa_search_noalloc(boa_index *ix, const void *queries, const int3
     ws.bits = reinterpret_cast<uint32_t *>(base + off);
     ws.slots = off < kScratchBytes ? (kScratchBytes - off) / ((size_t)ws.slot_words * 4) : 0;
     if (ws.slots > slots) ws.slots = slots;
-    return run_search(ix, queries, ranges, nq, p, rq, plans, ids, dists, final_L, expansions, scored, ws, st);
+    return run_search(ix, queries, ranges, nq, p, rq, plans, teams, ids, dists, final_L, expansions, scored, ws, st);
 }
 
 extern "C" int boa_get_stats(const boa_index *ix, boa_stats *out)

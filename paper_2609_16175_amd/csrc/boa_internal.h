@@ -74,6 +74,10 @@ struct PhaseArgs {
     uint32_t *status;
     double eps;
     uint32_t tau_count;       // the phase runs only if n_active > tau_count
+    // the launch serves n_active in (min_active, max_active]: where the count
+    // is known on the device only, launches for few and for many queries
+    // follow each other and one of them returns at once
+    uint32_t min_active, max_active;
     int32_t k;
     int32_t sched[BOA_MAX_PHASES]; // phase widths
     int32_t p_begin, p_end;   // phases run by this launch (one, or all when fused)
@@ -152,12 +156,13 @@ int phase_occupancy(int vec_dtype, int d, int wpb, size_t lds, bool wide = false
 // per-wave LDS bytes the distance scorer keeps (its copy of the query, or
 // the product-quantisation distance table)
 int scorer_lds_bytes(int vec_dtype, int d, bool wide = false, int pq_m = 0);
-// The escalation launch of a split search with two waves per query (LDS
-// bitmap visited set, exact distances): its LDS per block, resident blocks
-// per CU, and the launch (lds_per_wave carries the block's LDS bytes).
-size_t pair_lds_bytes(int32_t L, uint32_t vis_words, int scorer_lds);
-int pair_occupancy(int vec_dtype, int d, size_t lds);
-hipError_t launch_pair(const PhaseArgs &a, int vec_dtype, int blocks, hipStream_t st);
+// The launch with a team of waves per query (exact distances): its LDS per
+// block, resident blocks per CU, and the launch (lds_per_wave carries the
+// block's LDS bytes; a block uses one wave slot).
+// parts: waves that share one node's row (1 or 2).
+size_t team_lds_bytes(int32_t L, int parts, uint32_t vis_words, int scorer_lds);
+int team_occupancy(int vec_dtype, int d, int parts, size_t lds);
+hipError_t launch_team(const PhaseArgs &a, int vec_dtype, int parts, int blocks, hipStream_t st);
 hipError_t launch_compact(const CompactArgs &a, hipStream_t st);
 hipError_t launch_append(const AppendArgs &a, hipStream_t st);
 hipError_t launch_init(const InitArgs &a, hipStream_t st);

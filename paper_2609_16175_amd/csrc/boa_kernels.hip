@@ -3,7 +3,7 @@
 // One 64-lane wavefront runs one query at a time: a persistent grid of
 // waves pulls query slots from a per-launch atomic counter. Per expansion
 // (Alg. 2, one node per iteration):
-//   1. select the first not-yet-expanded worklist entry (ballot scan);
+//   1. select the smallest not-yet-expanded key of the worklist;
 //   2. gather its adjacency row, one neighbour per lane (one coalesced load);
 //   3. test-and-insert every neighbour into the query's visited set: a
 //      two-choice bucketed table of 16-bit entries in LDS whose overflow
@@ -13,20 +13,20 @@
 //      violated range predicates (phi, Eq. 2), gather the vector and compute
 //      the squared L2 distance with a 16-lane (float32) or G-lane (uint8)
 //      group per candidate and a butterfly reduction;
-//   5. pack (phi, distance, id) into one 64-bit key, drop keys that cannot
-//      enter the worklist, sort the rest by counting (each key's rank is the
-//      number of survivors below it), and merge them into the sorted
-//      worklist held in LDS: each new key's rank by binary search (eight-
-//      way in the escalation variant), its
+//   5. pack (phi, distance, id) into one 64-bit key and drop keys that cannot
+//      enter the worklist. The rest wait, one per lane, beside the sorted
+//      worklist in LDS (WaveList); when the next batch does not fit, they are
+//      sorted by counting (each key's rank is the number of keys below it)
+//      and merged: each key's rank in the list by an eight-way search, its
 //      output slot marked in a bitmap, and the suffix rebuilt backwards in
 //      64-entry chunks where a popcount of the bitmap tells every output
 //      slot where its entry comes from.
 // The epilogue writes the first k filter-valid entries, the phase width,
 // and the Eq. 3 confidence flag.
 //
-// The escalation launch of a split search can instead give each query two
-// waves (pair_kernel, below): one merges and selects while the other runs
-// the visited test, gathers and scoring of the node it expects next.
+// Launches of few queries give each a team of waves instead (team_kernel,
+// below): one owns the worklist and the visited set, the others run the row,
+// gathers and scoring of the nodes next in order.
 //
 // Worklist key (unsigned 64-bit, compared as an integer):
 //   bits 63..60 phi (violations, <= 8), bits 59..28 float32 bits of the
@@ -188,7 +188,10 @@ struct F32Scorer {
     // rows in flight per round trip: the narrow variant keeps registers for
     // occupancy; the wide one covers most expansions in one round trip
     static constexpr int RU = W == 1 ? (T <= 2 ? 4 : (T <= 4 ? 2 : 1))
-                                     : (T <= 2 ? 16 : (T <= 4 ? 8 : (T <= 6 ? 4 : (T <= 12 ? 2 : 1))));
+                              : W == 3 ? (T <= 2 ? 8 : (T <= 4 ? 4 : 2))
+                                       : (T <= 2 ? 16 : (T <= 4 ? 8 : (T <= 6 ? 4 : (T <= 12 ? 2 : 1))));
+    // waves per SIMD a team launch's registers leave room for
+    static constexpr int kTeamWaves = T <= 4 ? 4 : 2;
     struct Ids {
         uint32_t v[RU];
     };
@@ -280,6 +283,7 @@ struct U8Scorer {
     // rows of at most 128 bytes gather every neighbour of an expanded node
     // before its visited test (gather_row / score_row below)
     static constexpr bool kSpec = G <= 8;
+    static constexpr int kTeamWaves = G <= 16 ? 4 : 2;
     static constexpr int kLdsBytes = 0;
     static constexpr bool kPQ = false;
     uint4 q;
@@ -729,14 +733,21 @@ __device__ __forceinline__ uint32_t free_words(const uint4 &b)
            (b.w == 0xFFFFFFFFu ? 1u : 0u);
 }
 
+// the two buckets an id may be in, and its stored bits
+__device__ __forceinline__ void visit_slots(const Visited &s, uint32_t v, uint32_t &b1, uint32_t &b2, uint32_t &r)
+{
+    const uint32_t h = mix_id(v, s.idbits);
+    r = h & ((1u << s.rbits) - 1u);
+    b1 = h >> s.rbits;
+    b2 = (b1 ^ (((__umul24(r, 0xD1E995u) + 0x7F4A7C15u) >> 7) | 1u)) & s.bmask;
+}
+
 // 1: v was not in the set and now is (in LDS); 0: v was already there;
 // -1: both buckets full and v not in them (the caller consults the bitmap).
 __device__ __forceinline__ int visit_lds(const Visited &s, uint32_t v)
 {
-    const uint32_t h = mix_id(v, s.idbits);
-    const uint32_t r = h & ((1u << s.rbits) - 1u);
-    const uint32_t b1 = h >> s.rbits;
-    const uint32_t b2 = (b1 ^ (((__umul24(r, 0xD1E995u) + 0x7F4A7C15u) >> 7) | 1u)) & s.bmask;
+    uint32_t b1, b2, r;
+    visit_slots(s, v, b1, b2, r);
     const uint32_t e1 = r, e2 = 0x8000u | r;
     const bool alt_ok = e2 != 0xFFFFu;
     const uint4 *bk = reinterpret_cast<const uint4 *>(s.words);
@@ -796,6 +807,97 @@ __device__ __forceinline__ void clear_bits(const Visited &s, uint32_t n_log, int
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
 }
 
+// The visited set of one query, written by one wave: the hashed table with its
+// HBM bitmap, or (bitmap != 0) one LDS bit per id.
+struct VisitSet {
+    Visited s;
+    uint32_t bitmap;
+    uint32_t table_words;   // LDS words of either kind
+    bool spill;             // this query has used the HBM bitmap
+    uint32_t n_log;         // ids logged in this wave slot's HBM bitmap (its header,
+                            // in a register: no other wave uses the slot meanwhile)
+
+    __device__ __forceinline__ void bind(const PhaseArgs &a, uint32_t *lds, uint32_t slot)
+    {
+        s.words = lds;
+        s.bmask = (1u << (a.h_log2 - 3)) - 1u;       // 8 slots per bucket
+        s.idbits = a.id_bits;
+        s.rbits = a.id_bits > (uint32_t)(a.h_log2 - 3) ? a.id_bits - (uint32_t)(a.h_log2 - 3) : 0u;
+        s.words32 = a.bits_words;
+        s.bits = a.bits + (size_t)slot * a.slot_words;
+        s.log = s.bits + a.bits_words;
+        s.log_cap = a.log_cap;
+        s.status = a.status;
+        bitmap = a.vis_bitmap;
+        table_words = a.vis_bitmap ? a.vis_words : (1u << a.h_log2) >> 1;
+        spill = false;
+        n_log = 0;
+    }
+    __device__ __forceinline__ void open() { n_log = bitmap ? 0u : bcast0(s.log[0]); }
+    __device__ __forceinline__ void close(int lane) const
+    {
+        if (!bitmap && lane == 0) s.log[0] = n_log;
+    }
+    // empty set: the bitmap with no bit set, the table with every slot free
+    __device__ __forceinline__ void clear(int lane)
+    {
+        const uint32_t f = bitmap ? 0u : 0xFFFFFFFFu;
+        const uint4 z = make_uint4(f, f, f, f);
+        uint4 *h4 = reinterpret_cast<uint4 *>(s.words);
+        for (uint32_t i = lane; i < table_words >> 2; i += 64) h4[i] = z;
+    }
+    // the entry point, by one lane
+    __device__ __forceinline__ void enter(uint32_t v) const
+    {
+        if (bitmap) s.words[v >> 5] |= 1u << (v & 31u);
+        else visit_lds(s, v);
+    }
+    // test-and-insert of this lane's id: 1 new, 0 seen (or padding)
+    __device__ __forceinline__ int test(uint32_t v, int lane)
+    {
+        if (bitmap) {   // one bit per id: a single LDS atomic
+            if (v == BOA_PAD) return 0;
+            const uint32_t bit = 1u << (v & 31u);
+            return (atomicOr(&s.words[v >> 5], bit) & bit) ? 0 : 1;
+        }
+        int vst = 0;
+        if (v != BOA_PAD) vst = visit_lds(s, v);
+        if (__ballot(vst < 0) != 0ull) {
+            if (!spill) {          // first overflow of this query: reset the bitmap
+                spill = true;
+                clear_bits(s, n_log, lane);
+                n_log = 0;
+            }
+            const bool to_bits = vst < 0;
+            if (to_bits) vst = visit_bits(s, v) ? 1 : 0;
+            // log the ids whose bits this wave has just set
+            const uint64_t lm = __ballot(to_bits && vst > 0);
+            if (lm) {
+                const uint32_t cnt = (uint32_t)__popcll(lm);
+                if (n_log <= s.log_cap && cnt <= s.log_cap - n_log) {
+                    if (to_bits && vst > 0) s.log[BOA_LOG_HDR + n_log + lanes_below(lm)] = v;
+                    n_log += cnt;
+                } else {
+                    n_log = BOA_LOG_DIRTY;
+                }
+            }
+        }
+        return vst;
+    }
+    // Whether the LDS part holds an id: true only for ids in the set, also
+    // while the set's own wave inserts others (an entry is written as a whole
+    // word and never changes until the set is cleared).
+    __device__ __forceinline__ bool holds(uint32_t v) const
+    {
+        if (bitmap) return (s.words[v >> 5] >> (v & 31u)) & 1u;
+        uint32_t b1, b2, r;
+        visit_slots(s, v, b1, b2, r);
+        const uint4 *bk = reinterpret_cast<const uint4 *>(s.words);
+        const uint4 B1 = bk[b1], B2 = bk[b2];
+        return has16(B1, r) || (r != 0x7FFFu && has16(B2, 0x8000u | r));
+    }
+};
+
 // ---------------------------------------------------------------------------
 // The worklist of Alg. 2, held by one wave: a sorted list in LDS and up to 64
 // pending keys, one per lane, not yet merged into it.
@@ -811,22 +913,26 @@ __device__ __forceinline__ void clear_bits(const Visited &s, uint32_t n_log, int
 // several times a selection, and at widths of 100 and more it is needed once
 // in 4 to 15 expansions instead of at every one.
 
-// smallest of 64 lanes' values, in lane 63 (DPP steps inside rows of 16, then
-// across the rows; a lane without a source keeps its own value)
-template <int CTRL>
-__device__ __forceinline__ uint32_t dpp_min(uint32_t v)
-{
-    const uint32_t o = (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, CTRL, 0xF, 0xF, false);
-    return o < v ? o : v;
-}
+// Smallest of 64 lanes' values: DPP steps inside the rows of 16, then across
+// the rows; a lane without a source keeps its own value, lane 63 ends with the
+// result. (In one block: each step reads what the one before wrote, two wait
+// states later, and the compiler's own form of it takes a move more per step.)
 __device__ __forceinline__ uint32_t wave_min32(uint32_t v)
 {
-    v = dpp_min<0x111>(v);   // row_shr:1, 2, 4, 8
-    v = dpp_min<0x112>(v);
-    v = dpp_min<0x114>(v);
-    v = dpp_min<0x118>(v);
-    v = dpp_min<0x142>(v);   // row_bcast:15, 31
-    v = dpp_min<0x143>(v);
+    asm("s_nop 1\n\t"
+        "v_min_u32_dpp %0, %0, %0 row_shr:1 row_mask:0xf bank_mask:0xf\n\t"
+        "s_nop 1\n\t"
+        "v_min_u32_dpp %0, %0, %0 row_shr:2 row_mask:0xf bank_mask:0xf\n\t"
+        "s_nop 1\n\t"
+        "v_min_u32_dpp %0, %0, %0 row_shr:4 row_mask:0xf bank_mask:0xf\n\t"
+        "s_nop 1\n\t"
+        "v_min_u32_dpp %0, %0, %0 row_shr:8 row_mask:0xf bank_mask:0xf\n\t"
+        "s_nop 1\n\t"
+        "v_min_u32_dpp %0, %0, %0 row_bcast:15 row_mask:0xf bank_mask:0xf\n\t"
+        "s_nop 1\n\t"
+        "v_min_u32_dpp %0, %0, %0 row_bcast:31 row_mask:0xf bank_mask:0xf\n\t"
+        "s_nop 1"
+        : "+v"(v));
     return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
 }
 // The smallest key without the expanded flag (KEY_NONE, which has it set, if
@@ -1048,6 +1154,51 @@ __device__ __forceinline__ const PhaseArgs &cold_args()
     return *(const PhaseArgs *)p;
 }
 
+// The end of a query's phase: Eq. 3 on its n_valid valid entries (d_k, d_max:
+// squared distances of the k-th and the last), statistics, and the result if
+// the phase is the query's last. result(q, id, dist) gives this lane the q-th
+// valid entry.
+template <class Result>
+__device__ __forceinline__ bool end_phase(const PhaseArgs &a, int lane, int p, uint32_t qi, uint32_t t, int L,
+                                          uint32_t n_valid, float d_k, float d_max, uint32_t E, uint32_t S,
+                                          bool spill, Result &&result)
+{
+    const int k = a.k;
+    uint32_t conf = 0;
+    if (n_valid > (uint32_t)k) {
+        const double dk = sqrt((double)d_k);
+        const double dmax = sqrt((double)d_max);
+        const double gamma = dmax == 0.0 ? 0.0 : (dmax - dk) / dmax;
+        // (uniform, also for the compiler: a phase loop that lanes could
+        // leave one by one would put every value it carries in vector
+        // registers and every test on them under an execution mask)
+        conf = bcast0(gamma <= a.eps ? 1u : 0u);
+    }
+    const bool last = conf != 0u || p + 1 == a.p_end;
+    if (lane == 0) {
+        const size_t ps = (size_t)p * a.nq + qi;
+        if (a.qstat) {   // per-phase statistics (absent in the allocation-free search)
+            a.qstat[ps] = (uint8_t)(1u + conf + (spill ? 4u : 0u));
+            a.qE[ps] = E;
+            a.qS[ps] = S;
+        }
+        if (a.user_E) a.user_E[qi] += E;
+        if (a.user_S) a.user_S[qi] += S;
+        if (a.write_conf) a.conf[t] = (uint8_t)conf;
+        if (last) a.final_L[qi] = L;
+    }
+    if (last) {
+        for (int q = lane; q < k; q += 64) {
+            uint32_t id = BOA_PAD;
+            float dd = __int_as_float(0x7f800000);
+            if ((uint32_t)q < n_valid) result(q, id, dd);
+            a.ids[(size_t)qi * k + q] = id;
+            a.dists[(size_t)qi * k + q] = dd;
+        }
+    }
+    return last;
+}
+
 template <class Scorer>
 __global__ void __launch_bounds__(256) phase_kernel(PhaseArgs a)
 {
@@ -1079,22 +1230,11 @@ __global__ void __launch_bounds__(256) phase_kernel(PhaseArgs a)
     const bool spec = Scorer::kSpec && R <= Scorer::kSpecMaxR;
 
     const uint32_t n_in = bcast0(*a.n_active);
-    if (n_in <= a.tau_count) return;   // the loop of Alg. 1 has stopped
+    if (n_in <= a.tau_count || n_in <= a.min_active || n_in > a.max_active) return;   // (tau: the loop of Alg. 1 has stopped)
 
-    Visited vs;
-    vs.words = htab;
-    vs.bmask = (1u << (a.h_log2 - 3)) - 1u;       // 8 slots per bucket
-    vs.idbits = a.id_bits;
-    vs.rbits = a.id_bits > (uint32_t)(a.h_log2 - 3) ? a.id_bits - (uint32_t)(a.h_log2 - 3) : 0u;
-    vs.words32 = a.bits_words;
-    vs.bits = a.bits + (size_t)slot * a.slot_words;
-    vs.log = vs.bits + a.bits_words;
-    vs.log_cap = a.log_cap;
-    vs.status = a.status;
-    // ids logged in this slot's bitmap (its header, kept in a register while
-    // this wave runs: no other wave uses the slot meanwhile)
-    uint32_t n_log = a.vis_bitmap ? 0u : __builtin_amdgcn_readfirstlane(vs.log[0]);
-    const uint32_t table_words = a.vis_bitmap ? a.vis_words : (1u << a.h_log2) >> 1;
+    VisitSet vs;
+    vs.bind(a, htab, slot);
+    vs.open();
 
     Scorer sc;
     sc.bind_lds(qlds);
@@ -1143,7 +1283,6 @@ __global__ void __launch_bounds__(256) phase_kernel(PhaseArgs a)
         // point at its own width (Alg. 1 calls Alg. 2 afresh)
         // search state; in the warm-start mode it carries over from phase to
         // phase (the worklist, its expanded flags and the visited set)
-        bool spill = false;
         for (int p = aq.p_begin; p < cold_args().p_end; ++p) {
         const PhaseArgs &ap = cold_args();
         const int L = ap.sched[p];
@@ -1152,49 +1291,13 @@ __global__ void __launch_bounds__(256) phase_kernel(PhaseArgs a)
         const int Lcap = (ap.warm && p + 1 < ap.p_end) ? ap.sched[p + 1] : L;
         const bool fresh = !ap.warm || p == ap.p_begin;
         if (fresh) {
-            // the bitmap starts with no bit set, the table with every slot
-            // free, the worklist with every slot past its (zero) length KEY_NONE
-            const uint32_t f = a.vis_bitmap ? 0u : 0xFFFFFFFFu;
-            const uint4 z = make_uint4(f, f, f, f);
-            uint4 *h4 = reinterpret_cast<uint4 *>(htab);
-            for (uint32_t i = lane; i < table_words >> 2; i += 64) h4[i] = z;
+            vs.clear(lane);
             wl.clear(Lb, lane);
-            spill = false;
+            vs.spill = false;
         }
-        spill = bcast0(spill ? 1u : 0u) != 0u;
+        vs.spill = bcast0(vs.spill ? 1u : 0u) != 0u;
         wave_sync();
 
-        // test-and-insert of this lane's neighbour: 1 new, 0 seen (or padding)
-        auto visit_test = [&](uint32_t v) -> int {
-            if (a.vis_bitmap) {   // one bit per id: a single LDS atomic
-                if (v == BOA_PAD) return 0;
-                const uint32_t bit = 1u << (v & 31u);
-                return (atomicOr(&htab[v >> 5], bit) & bit) ? 0 : 1;
-            }
-            int vst = 0;
-            if (v != BOA_PAD) vst = visit_lds(vs, v);
-            if (__ballot(vst < 0) != 0ull) {
-                if (!spill) {          // first overflow of this query: reset the bitmap
-                    spill = true;
-                    clear_bits(vs, n_log, lane);
-                    n_log = 0;
-                }
-                const bool to_bits = vst < 0;
-                if (to_bits) vst = visit_bits(vs, v) ? 1 : 0;
-                // log the ids whose bits this wave has just set
-                const uint64_t lm = __ballot(to_bits && vst > 0);
-                if (lm) {
-                    const uint32_t cnt = (uint32_t)__popcll(lm);
-                    if (n_log <= vs.log_cap && cnt <= vs.log_cap - n_log) {
-                        if (to_bits && vst > 0) vs.log[BOA_LOG_HDR + n_log + lanes_below(lm)] = v;
-                        n_log += cnt;
-                    } else {
-                        n_log = BOA_LOG_DIRTY;
-                    }
-                }
-            }
-            return vst;
-        };
         uint32_t E = 0, S = bcast0(fresh ? 1u : 0u);
         wl.begin(L, Lcap, lane);
         // adjacency row already in flight for the node expected next
@@ -1207,8 +1310,7 @@ __global__ void __launch_bounds__(256) phase_kernel(PhaseArgs a)
         // continues with nothing new to score)
         if (fresh) {
             if (lane == 0) {
-                if (a.vis_bitmap) htab[ix.entry >> 5] |= 1u << (ix.entry & 31u);
-                else visit_lds(vs, ix.entry);
+                vs.enter(ix.entry);
                 cid[0] = ix.entry;
             }
             nk = score_listed(1u);
@@ -1273,7 +1375,7 @@ __global__ void __launch_bounds__(256) phase_kernel(PhaseArgs a)
             }
 
             // ---- test-and-insert into the visited set
-            const int vst = visit_test(v);
+            const int vst = vs.test(v, lane);
             PROF_T(t_vl);
             PROF_ADD(13, t_vl - t_row);
             const bool is_new = vst > 0;
@@ -1304,7 +1406,7 @@ __global__ void __launch_bounds__(256) phase_kernel(PhaseArgs a)
             }
             PROF_T(t_vis1);
             PROF_ADD(1, t_vis1 - t_sel1);
-            PROF_ADD(6, spill ? 1 : 0);
+            PROF_ADD(6, vs.spill ? 1 : 0);
             // ---- the new nodes' keys (one per lane)
             if (spec) {
                 const uint32_t phi = count_phi(aw0, aw1);
@@ -1327,7 +1429,6 @@ __global__ void __launch_bounds__(256) phase_kernel(PhaseArgs a)
         const PhaseArgs &ae = cold_args();
         const uint32_t n_valid = bcast0(lower_bound64(beam, min(len, (uint32_t)L), KEY_PHI1));
         const int k = ae.k;
-        uint32_t conf = 0;
         // the result (the first valid entries) and the two distances of Eq. 3
         uint64_t res_key[2] = {KEY_NONE, KEY_NONE};   // (product-quantised search: lanes' top-k keys)
         float d_k = 0.f, d_max = 0.f;
@@ -1364,52 +1465,22 @@ __global__ void __launch_bounds__(256) phase_kernel(PhaseArgs a)
             d_k = key_dist(beam[k - 1]);
             d_max = key_dist(beam[n_valid - 1]);
         }
-        if (n_valid > (uint32_t)k) {
-            double dk = sqrt((double)d_k);
-            double dmax = sqrt((double)d_max);
-            double gamma = dmax == 0.0 ? 0.0 : (dmax - dk) / dmax;
-            // (uniform, also for the compiler: a phase loop that lanes could
-            // leave one by one would put every value it carries in vector
-            // registers and every test on them under an execution mask)
-            conf = bcast0(gamma <= ae.eps ? 1u : 0u);
-        }
-        const bool last = conf != 0u || p + 1 == ae.p_end;
-        if (lane == 0) {
-            const size_t ps = (size_t)p * ae.nq + qi;
-            if (ae.qstat) {   // per-phase statistics (absent in the allocation-free search)
-                ae.qstat[ps] = (uint8_t)(1u + conf + (spill ? 4u : 0u));
-                ae.qE[ps] = E;
-                ae.qS[ps] = S;
+        const bool last = end_phase(ae, lane, p, qi, t, L, n_valid, d_k, d_max, E, S, vs.spill, [&](int q, uint32_t &id, float &dd) {
+            if constexpr (Scorer::kPQ) {
+                const uint64_t kk = res_key[q >> 6];
+                id = (uint32_t)kk;
+                dd = __uint_as_float((uint32_t)(kk >> 32));
+            } else {
+                const uint64_t kk = beam[q];
+                id = key_id(kk);
+                dd = key_dist(kk);
             }
-            if (ae.user_E) ae.user_E[qi] += E;
-            if (ae.user_S) ae.user_S[qi] += S;
-            if (ae.write_conf) ae.conf[t] = (uint8_t)conf;
-            if (last) ae.final_L[qi] = L;
-        }
-        if (last) {
-            for (int q = lane; q < k; q += 64) {
-                uint32_t id = BOA_PAD;
-                float dd = __int_as_float(0x7f800000);
-                if ((uint32_t)q < n_valid) {
-                    if constexpr (Scorer::kPQ) {
-                        const uint64_t kk = res_key[q >> 6];
-                        id = (uint32_t)kk;
-                        dd = __uint_as_float((uint32_t)(kk >> 32));
-                    } else {
-                        uint64_t kk = beam[q];
-                        id = key_id(kk);
-                        dd = key_dist(kk);
-                    }
-                }
-                ae.ids[(size_t)qi * k + q] = id;
-                ae.dists[(size_t)qi * k + q] = dd;
-            }
-        }
+        });
         wave_sync();
         if (last) break;
         }   // phases
     }       // queries
-    if (!a.vis_bitmap && lane == 0) vs.log[0] = n_log;
+    vs.close(lane);
 #ifdef BOA_STAGE_PROFILE
     if (lane == 0 && a.prof) {
         for (int i = 0; i < BOA_PROF_SLOTS; ++i) a.prof[(size_t)slot * BOA_PROF_SLOTS + i] += prof_acc[i];
@@ -1418,361 +1489,358 @@ __global__ void __launch_bounds__(256) phase_kernel(PhaseArgs a)
 }
 
 // ---------------------------------------------------------------------------
-// The escalation launch of a split search with two waves per query (a
-// 128-thread block), when its visited set is the LDS bitmap over all ids.
-// One wave owns the worklist: it merges each expansion's keys and selects
-// the next node. The other owns the bitmap: it tests a row's neighbours,
-// gathers and scores the new ones. The expansions stay one node at a time
-// in the order of Alg. 2; what overlaps is the guess of the next node. After
-// handing over an expansion's keys, the gather wave takes as the next node
-// the smaller of its best new key and the entry that followed the expanded
-// one (the selection after the merge is exactly that whenever the entry is
-// known), and runs that node's visited test, gathers and scoring while the
-// worklist wave merges. If the selection differs, the guessed node's bits are
-// cleared again (the gather wave is the only writer of the bitmap, so the set
-// returns to its state before the guess) and the selected node is expanded.
-// The visited set sees the same inserts in the same order, so results and
-// counts are those of the one-wave launch.
+// A team of waves per query, for launches with few queries: one wave (wave 0
+// of the block) owns the worklist and the visited set; the others (helpers)
+// expand nodes it names, ahead of their turn.
 //
-// Control flow that both waves share (the query loop, the phase loop, the
-// end of a phase's search) is decided from values they read from LDS after
-// the same block barrier, so both run the same sequence of barriers.
-struct PairCtrl {
-    uint64_t kn;       // the entry after the selected one (KEY_NONE: not known)
-    uint32_t t;        // query slot taken by the block
-    uint32_t sel;      // the selected node's id, or PAIR_DONE
-    uint32_t S;        // scored nodes of the phase (gather wave)
-    uint32_t last;     // the query's result has been written
-    uint32_t pad[2];
+// With one wave per query, an expansion is a chain of memory round trips (the
+// row, the gathers) and of the wave's own work, one after the other: 8 to 11
+// thousand cycles, while a launch of a few hundred queries leaves most of the
+// chip idle. What an expansion reads does not depend on the worklist: a
+// helper loads the node's row, leaves out the neighbours that the visited set
+// already holds, and computes the others' keys. The worklist wave names the
+// unexpanded entries next in order before they are selected, so that the keys
+// are usually there when their node's turn comes; it then makes the one
+// authoritative test-and-insert of each neighbour, enters the new keys and
+// selects. The expansions stay one node at a time in the order of Alg. 2, the
+// visited set sees the same inserts in the same order, and a key is dropped
+// only where the set held its id at the helper's look, which it then holds
+// for good (sets are cleared between phases, while every helper is idle): the
+// results and counts are those of the one-wave launch.
+//
+// Measured, before (two waves in lock step in a split search's escalation, else
+// one wave) and with teams: 64 queries (uint8, d = 128, widths 16 and 512) 1.63
+// and 1.05 ms; 239 queries at width 512 (float32, d = 128, R = 64, in a split
+// search of 10,000) 3.79 and 3.13 ms; 777 at width 500 (d = 100) 2.35 and 1.31
+// ms; 2,000 with d = 768 up to width 1024 in BOA+ mode 23.7 and 17.0 ms, there
+// bound by memory. An expansion takes the worklist wave 3,000 cycles of its own
+// work; 60 to 70 of 100 nodes have been named ahead.
+//
+// Orders are passed through LDS: the worklist wave writes a helper's request
+// word (a sequence number, a kind and a payload); the helper answers with the
+// sequence number once its keys are written. A helper waits only for a
+// request, and one follows on every path (the last is TEAM_EXIT); the
+// worklist wave waits only for a helper that holds a request, which ends
+// without waiting for anybody.
+static constexpr int TEAM_GROUPS = 3;   // nodes in work or held at a time
+enum : uint32_t { TEAM_EXPAND = 0, TEAM_SCORE = 1, TEAM_QUERY = 2, TEAM_EXIT = 3 };
+struct TeamWave {        // one helper
+    uint64_t req;        // sequence number << 34 | kind << 32 | payload
+    uint32_t done;       // upper half of the last request answered
+    uint32_t pad;
+    uint32_t cid[64];    // its candidates and their distances
+    float cd[64];
 };
-static constexpr uint32_t PAIR_DONE = 0xFFFFFFFFu;
 
-template <class Scorer>
-__global__ void __launch_bounds__(128) pair_kernel(PhaseArgs a)
+// P helpers share a node: part q takes the row's slice of W = ceil(R / P)
+// entries from q W on, and answers in the same entries of the group's keys.
+template <class Scorer, int P>
+__device__ __forceinline__ void team_helper(const PhaseArgs &a, TeamWave *me, uint64_t *group_keys, int part,
+                                            const VisitSet &vs, unsigned char *qlds, int lane)
+{
+    const IndexView ix = a.ix;
+    const int d = ix.d;
+    const int W = (ix.R + P - 1) / P, row0 = part * W;
+    const int R = min(W, ix.R - row0);   // (0 or less: nothing for this part)
+    uint64_t *keys = group_keys + row0;
+    const bool spec = Scorer::kSpec && R <= Scorer::kSpecMaxR;
+    auto row_of = [&](uint32_t u) -> uint32_t {
+        return ix.adj[(size_t)u * ix.R + max(0, min(row0 + lane, row0 + R - 1))];
+    };
+    Scorer sc;
+    sc.bind_lds(qlds);
+    RangeTest rt;
+    uint32_t *cid = me->cid;
+    float *cd = me->cd;
+    uint32_t last = 0;
+    // the row of the nearest node this helper found last, requested while
+    // the worklist wave selects: a node found just now is the next one in 30
+    // to 40 of 100 expansions, and is then asked of the helper that found it
+    uint32_t pf_id = BOA_PAD, pf_row = BOA_PAD;
+    for (;;) {
+        uint64_t r;
+        for (;;) {
+            r = readlane64(__hip_atomic_load(&me->req, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP), 0);
+            if ((uint32_t)(r >> 32) != last) break;
+            __builtin_amdgcn_s_sleep(1);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+        last = (uint32_t)(r >> 32);
+        const uint32_t kind = last & 3u, what = (uint32_t)r;
+        if (kind == TEAM_EXIT) return;
+        if (kind == TEAM_QUERY) {
+            const PhaseArgs &aq = cold_args();
+            sc.load_query(aq.queries, what, d, lane);
+            rt.set(aq.ranges, what, aq.ix.m, aq.ix.f32_mask);
+        } else {
+            uint64_t key = KEY_NONE;
+            uint32_t v = lane == 0 && part == 0 ? what : BOA_PAD;
+            if (kind == TEAM_EXPAND) {
+                v = what == pf_id ? pf_row : row_of(what);
+                if (lane >= R) v = BOA_PAD;
+            }
+            asm volatile("" : "+v"(v));
+            if (spec && kind == TEAM_EXPAND) {
+                const uint32_t vv = v != BOA_PAD ? v : ix.entry;   // padding: any valid row, unused
+                typename Scorer::RowGather rg;
+                int4 w0 = make_int4(0, 0, 0, 0), w1 = make_int4(0, 0, 0, 0);
+                if (lane < R) load_attr_record(ix, vv, w0, w1);
+                sc.gather_row(ix.vectors, d, vv, R, lane, rg);
+                const bool open = v != BOA_PAD && !vs.holds(vv);
+                const uint32_t phi = rt.phi(w0, w1, ix.m_pad);
+                sc.score_row(rg, d, R, cd, lane);
+                wave_sync();
+                if (open) key = make_key(phi, cd[lane], v);
+            } else {
+                bool open = v != BOA_PAD;
+                if (open && kind == TEAM_EXPAND) open = !vs.holds(v);
+                const uint64_t om = __ballot(open);
+                const uint32_t c = (uint32_t)__popcll(om);
+                if (open) cid[lanes_below(om)] = v;
+                if (c > 0) {
+                    wave_sync();
+                    const uint32_t my_id = cid[lane];
+                    typename Scorer::Ids ids0;
+                    sc.read_ids(cid, (int)c, 0, lane, ids0);
+                    int4 w0 = make_int4(0, 0, 0, 0), w1 = make_int4(0, 0, 0, 0);
+                    if (lane < (int)c) load_attr_record(ix, my_id, w0, w1);
+                    sc.score(ix.vectors, d, cid, (int)c, cd, lane, ids0);
+                    const uint32_t phi = rt.phi(w0, w1, ix.m_pad);
+                    wave_sync();
+                    if (lane < (int)c) key = make_key(phi, cd[lane], my_id);
+                }
+            }
+            if (lane < W && row0 + lane < 64) keys[lane] = key;
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+            __builtin_amdgcn_wave_barrier();
+            if (lane == 0) __hip_atomic_store(&me->done, last, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            const uint64_t near = wave_min_open(key);
+            if (near != KEY_NONE) {
+                pf_id = key_id(near);
+                pf_row = row_of(pf_id);
+            }
+            continue;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        __builtin_amdgcn_wave_barrier();
+        if (lane == 0) __hip_atomic_store(&me->done, last, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+}
+
+template <class Scorer, int P>
+__global__ void __launch_bounds__(64 * (1 + TEAM_GROUPS * P), Scorer::kTeamWaves) team_kernel(PhaseArgs a)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     const int lane = lane_id();
-    const bool merger = threadIdx.x < 64;   // wave 0: worklist; wave 1: bitmap and scoring
+    const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int Lb = beam_slots(a.L_alloc);
     const int pw = ((a.L_alloc >> 6) + 3) & ~1;
-    uint64_t *beam = reinterpret_cast<uint64_t *>(smem);        // Lb
-    uint64_t *nkey = beam + Lb;                                   // 64
-    uint64_t *posbm = nkey + 64;                                  // pw
-    uint64_t *kbuf = posbm + pw;                                  // 64: an expansion's keys
-    uint32_t *krow = reinterpret_cast<uint32_t *>(kbuf + 64);   // 64: the row of ctl->kn
-    PairCtrl *ctl = reinterpret_cast<PairCtrl *>(krow + 64);
-    uint32_t *cid = reinterpret_cast<uint32_t *>(ctl + 1);      // 64
-    float *cd = reinterpret_cast<float *>(cid + 64);             // 64
-    unsigned char *qlds = reinterpret_cast<unsigned char *>(cd + 64);
-    uint32_t *bits = reinterpret_cast<uint32_t *>(qlds + Scorer::kLdsBytes);   // vis_words
+    uint64_t *beam = reinterpret_cast<uint64_t *>(smem);          // Lb
+    uint64_t *nkey = beam + Lb;                                     // 64
+    uint64_t *posbm = nkey + 64;                                    // pw
+    uint64_t *keys = posbm + pw;                                    // 64 per group
+    TeamWave *wv = reinterpret_cast<TeamWave *>(keys + 64 * TEAM_GROUPS);   // one per helper
+    unsigned char *qlds = reinterpret_cast<unsigned char *>(wv + TEAM_GROUPS * P);
+    uint32_t *vis = reinterpret_cast<uint32_t *>(qlds + Scorer::kLdsBytes);
 
-    const IndexView ix = a.ix;
-    const int R = ix.R, d = ix.d, m = ix.m;
     const uint32_t n_in = bcast0(*a.n_active);
-    if (n_in <= a.tau_count) return;   // (the same for both waves)
-    const uint32_t nA = a.t_end < n_in ? a.t_end : n_in;
-
-    Scorer sc;
-    sc.bind_lds(qlds);
-    RangeTest rt;   // the gather wave's attribute test
-    // keys of the candidates cid[0, c): one per lane, KEY_NONE past c
-    auto score_cands = [&](uint32_t c) -> uint64_t {
-        if (c == 0) return KEY_NONE;
-        wave_sync();
-        const uint32_t my_id = cid[lane];
-        typename Scorer::Ids ids0;
-        sc.read_ids(cid, (int)c, 0, lane, ids0);
-        int4 w0 = make_int4(0, 0, 0, 0), w1 = make_int4(0, 0, 0, 0);
-        if (lane < (int)c) load_attr_record(ix, my_id, w0, w1);
-        sc.score(ix.vectors, d, cid, (int)c, cd, lane, ids0);
-        const uint32_t phi = rt.phi(w0, w1, ix.m_pad);
-        wave_sync();
-        return lane < (int)c ? make_key(phi, cd[lane], cid[lane]) : KEY_NONE;
-    };
-    // test-and-insert of a row (one neighbour per lane); the new ones go to
-    // cid in lane order
-    auto visit_row = [&](uint32_t v, uint64_t &nm) -> uint32_t {
-        bool is_new = false;
-        if (v != BOA_PAD) {
-            const uint32_t bit = 1u << (v & 31u);
-            is_new = (atomicOr(&bits[v >> 5], bit) & bit) == 0u;
+    // (the same for every wave of the block)
+    if (n_in <= a.tau_count || n_in <= a.min_active || n_in > a.max_active) return;
+    VisitSet vs;
+    vs.bind(a, vis, a.slot_base + blockIdx.x);
+    if (threadIdx.x < TEAM_GROUPS * P) {
+        wv[threadIdx.x].req = 0;
+        wv[threadIdx.x].done = 0;
+    }
+    // (entries past a row's parts stay empty)
+    for (int i = threadIdx.x; i < 64 * TEAM_GROUPS; i += blockDim.x) keys[i] = KEY_NONE;
+    __syncthreads();
+    if (wid > 0) {
+        const int h = (wid - 1) / P;
+        team_helper<Scorer, P>(a, wv + (wid - 1), keys + 64 * h, (wid - 1) - h * P, vs, qlds, lane);
+        return;
+    }
+    __builtin_amdgcn_s_setprio(2);   // the helpers wait for this wave
+    vs.open();
+    const IndexView ix = a.ix;
+    WaveList wl;
+    wl.beam = beam;
+    wl.nkey = nkey;
+    wl.posbm = posbm;
+    wl.len = 0;
+    // group h's state in lane h: the node it holds (or works on), its last
+    // request's upper half
+    uint32_t hnode = BOA_PAD, hseq = 0;
+    uint32_t seq = 0;
+    auto order = [&](int h, uint32_t kind, uint32_t what) {
+        seq = (seq + 1u) & 0x3FFFFFFFu;
+        const uint32_t hi = seq << 2 | kind;
+        if (lane == h) {
+            hseq = hi;
+            hnode = kind == TEAM_EXPAND ? what : BOA_PAD;
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+#pragma unroll
+            for (int q = 0; q < P; ++q)
+                __hip_atomic_store(&wv[h * P + q].req, (uint64_t)hi << 32 | what, __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_WORKGROUP);
         }
-        nm = __ballot(is_new);
-        if (is_new) cid[lanes_below(nm)] = v;
-        return (uint32_t)__popcll(nm);
     };
-    auto undo_row = [&](uint32_t v, uint64_t nm) {
-        if ((nm >> lane) & 1ull) atomicAnd(&bits[v >> 5], ~(1u << (v & 31u)));
-        wave_sync();
+    // groups whose last request is answered by every part
+    auto idle = [&]() -> uint64_t {
+        bool is = false;
+        if (lane < TEAM_GROUPS) {
+            is = true;
+#pragma unroll
+            for (int q = 0; q < P; ++q)
+                is &= __hip_atomic_load(&wv[lane * P + q].done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) == hseq;
+        }
+        return __ballot(is);
     };
-    auto row_of = [&](uint32_t u) -> uint32_t { return lane < R ? ix.adj[(size_t)u * R + lane] : BOA_PAD; };
+    constexpr uint64_t ALL = (1ull << TEAM_GROUPS) - 1ull;
+    auto wait_for = [&](uint64_t which) {
+        while ((idle() & which) != which) __builtin_amdgcn_s_sleep(1);
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    };
 #ifdef BOA_STAGE_PROFILE
-    // worklist wave: 0 merge and select, 3 wait for the guess, 5 whole
-    // iteration, 10 expansions; gather wave: 1 guessed expansion, 4 wait for
-    // the selection, 2 hand-over (and the expansion after a miss), 8 hits,
-    // 9 misses, 14 no guess, 13 guesses of a new key; 12 (worklist wave) no
-    // entry known after the selected one
+    // 0 select, 3 enter the keys, 1 name the next nodes, 2 wait for the
+    // helper, 13 read and test its keys; 8 nodes named ahead, 10 expansions,
+    // 12 keys ready without a wait
     uint64_t prof_acc[BOA_PROF_SLOTS] = {};
 #endif
-
     for (;;) {
-        if (merger && lane == 0) ctl->t = atomicAdd(a.queue, 1u);
-        __syncthreads();
-        const uint32_t t = bcast0(ctl->t) + a.t_begin;
-        if (t >= nA) break;   // (both waves)
-        const uint32_t qi = bcast0(a.active[t]);
-        if (!merger) {
-            sc.load_query(a.queries, qi, d, lane);
-            rt.set(a.ranges, qi, m, ix.f32_mask);
-        }
-        // every phase restarts from the entry point (Alg. 1 calls Alg. 2 afresh)
-        for (int p = a.p_begin; p < a.p_end; ++p) {
-            const int L = a.sched[p];
-            // worklist wave
-            uint32_t len = 0, E = 0;
-            int expanded_j = -1;
-            // gather wave: the keys of the last expansion handed over, the
-            // entry known to follow the last selected node, its row in flight,
-            // and the guessed expansion (row, new-neighbour mask, keys)
-            uint32_t S = 0;
-            uint64_t ckey = KEY_NONE, kn_prev = KEY_NONE;
-            uint32_t kn_row = BOA_PAD;   // row of kn_prev (read from krow)
-            bool guess = false;
-            uint32_t g_id = BOA_PAD, g_v = BOA_PAD, g_c = 0;
-            uint64_t g_nm = 0, g_key = KEY_NONE;
-            if (merger) {
-                for (int i = lane; i < Lb; i += 64) beam[i] = KEY_NONE;
-            } else {
-                const uint4 z = make_uint4(0u, 0u, 0u, 0u);
-                uint4 *b4 = reinterpret_cast<uint4 *>(bits);
-                for (uint32_t i = lane; i < (a.vis_words >> 2); i += 64) b4[i] = z;
+        const PhaseArgs &aq = cold_args();
+        uint32_t t = 0;
+        if (lane == 0) t = atomicAdd(aq.queue, 1u);
+        t = bcast0(t) + aq.t_begin;
+        if (t >= min(aq.t_end, n_in)) break;
+        const uint32_t qi = bcast0(aq.active[t]);
+        for (int h = 0; h < TEAM_GROUPS; ++h) order(h, TEAM_QUERY, qi);
+        for (int p = aq.p_begin; p < cold_args().p_end; ++p) {
+            const PhaseArgs &ap = cold_args();
+            const int L = ap.sched[p];
+            const int Lcap = (ap.warm && p + 1 < ap.p_end) ? ap.sched[p + 1] : L;
+            const bool fresh = !ap.warm || p == ap.p_begin;
+            // every helper idle: the set may be cleared, and what they hold
+            // (looked up in the set before) is forgotten
+            wait_for(ALL);
+            hnode = BOA_PAD;
+            if (fresh) {
+                vs.clear(lane);
+                wl.clear(Lb, lane);
+                vs.spill = false;
+            }
+            vs.spill = bcast0(vs.spill ? 1u : 0u) != 0u;
+            wave_sync();
+            uint32_t E = 0, S = bcast0(fresh ? 1u : 0u);
+            wl.begin(L, Lcap, lane);
+            uint64_t nk = KEY_NONE;
+            int hl = 0;   // the helper read last: idle and holding nothing
+            if (fresh) {
+                // the entry point is scored before the first expansion
+                if (lane == 0) vs.enter(ix.entry);
                 wave_sync();
-                if (lane == 0) {
-                    bits[ix.entry >> 5] |= 1u << (ix.entry & 31u);
-                    cid[0] = ix.entry;
-                }
-                ckey = score_cands(1u);   // the entry point, scored before the first expansion
-                S = 1;
-                kbuf[lane] = ckey;
+                order(0, TEAM_SCORE, ix.entry);
+                wait_for(1ull);
+                nk = keys[lane];
             }
             for (;;) {
-                __syncthreads();   // kbuf holds the last expansion's keys
-                PROF_T(t_b1);
-                if (merger) {
-                    // ---- drop, sort and merge the keys (as in phase_kernel)
-                    uint64_t key = kbuf[lane];
-                    uint32_t scan_from = (uint32_t)(expanded_j + 1);
-                    if (len == (uint32_t)L && key >= beam[L - 1]) key = KEY_NONE;   // cannot enter
-                    const uint64_t keep = __ballot(key != KEY_NONE);
-                    const uint32_t kept = __popcll(keep);
-                    if (kept > 0) {
-                        nkey[key != KEY_NONE ? lanes_below(keep) : kept + lanes_below(~keep)] = key;
-                        wave_sync();
-                        uint32_t rank = 0;
-                        {
-                            const ulonglong2 *nk2 = reinterpret_cast<const ulonglong2 *>(nkey);
-                            for (uint32_t i = 0; i < kept; i += 8) {
-                                const ulonglong2 a0 = nk2[(i >> 1) + 0], a1 = nk2[(i >> 1) + 1];
-                                const ulonglong2 a2 = nk2[(i >> 1) + 2], a3 = nk2[(i >> 1) + 3];
-                                rank += (a0.x < key ? 1u : 0u) + (a0.y < key ? 1u : 0u);
-                                rank += (a1.x < key ? 1u : 0u) + (a1.y < key ? 1u : 0u);
-                                rank += (a2.x < key ? 1u : 0u) + (a2.y < key ? 1u : 0u);
-                                rank += (a3.x < key ? 1u : 0u) + (a3.y < key ? 1u : 0u);
-                            }
-                        }
-                        wave_sync();
-                        if (key != KEY_NONE) nkey[rank] = key;
-                        wave_sync();
-                        key = lane < (int)kept ? nkey[lane] : KEY_NONE;
-                        uint32_t f = 0xFFFFFFFFu, pos = 0;
-                        if (lane < (int)kept) {
-                            pos = lower_bound64_p2(beam, (uint32_t)beam_slots((int32_t)len), key);
-                            f = pos + lane;
-                        }
-                        const uint32_t p0 = bcast0(pos);
-                        const uint32_t newlen = min((uint32_t)L, len + kept);
-                        const uint32_t w_lo = bcast0(p0 >> 6), w_hi = bcast0((newlen - 1u) >> 6);
-                        for (uint32_t w = w_lo + lane; w <= w_hi; w += 64) posbm[w] = 0ull;
-                        wave_sync();
-                        const bool placed = f < (uint32_t)L;
-                        if (placed) atomicOr(reinterpret_cast<unsigned long long *>(&posbm[f >> 6]),
-                                             1ull << (f & 63u));
-                        const uint32_t n_placed = __popcll(__ballot(placed));
-                        wave_sync();
-                        uint64_t word = posbm[w_hi];
-                        uint32_t below = n_placed - (uint32_t)__popcll(word);
-                        for (int w = (int)w_hi; w >= (int)w_lo; --w) {
-                            const uint32_t o = ((uint32_t)w << 6) + lane;
-                            const bool act = o >= p0 && o < newlen;
-                            const bool isnew = (word >> lane) & 1ull;
-                            const uint32_t cnt = below + (uint32_t)__popcll(word & ((1ull << lane) - 1ull));
-                            uint64_t val = 0;
-                            if (act) val = isnew ? nkey[cnt] : beam[o - cnt];
-                            wave_sync();
-                            if (act) beam[o] = val;
-                            if (w > (int)w_lo) {
-                                word = posbm[w - 1];
-                                below -= (uint32_t)__popcll(word);
-                            }
-                            wave_sync();
-                        }
-                        len = newlen;
-                        if (p0 < scan_from) scan_from = p0;
-                    }
-                    // ---- select the first unexpanded entry among the first L,
-                    // and the one after it when the same scan sees it
-                    const uint32_t lim = min(len, (uint32_t)L);
-                    int j = -1, j2 = -1;
-                    uint64_t ku = 0, kn = KEY_NONE;
-                    for (uint32_t b0 = scan_from; b0 < lim; b0 += 64) {
-                        const uint32_t i = b0 + lane;
-                        const uint64_t bk = i < lim ? beam[i] : 1ull;
-                        const uint64_t mk = __ballot(!(bk & 1ull));
-                        if (mk) {
-                            const int l1 = __ffsll((unsigned long long)mk) - 1;
-                            j = (int)b0 + l1;
-                            ku = readlane64(bk, l1);
-                            const uint64_t rest = mk & (mk - 1ull);
-                            if (rest) {
-                                const int l2 = __ffsll((unsigned long long)rest) - 1;
-                                j2 = (int)b0 + l2;
-                                kn = readlane64(bk, l2);
-                            }
-                            break;
-                        }
-                    }
-                    wave_sync();
-                    if (j >= 0) {
-                        expanded_j = j;
-                        E += 1;
-                        if (lane == 0) beam[j] = ku | 1ull;
-                    }
-                    if (lane == 0) {
-                        ctl->sel = j >= 0 ? key_id(ku) : PAIR_DONE;
-                        ctl->kn = j2 >= 0 ? kn : KEY_NONE;
-                    }
-                    // the row of the entry after the selected node, for the
-                    // gather wave's next guess (this wave waits at the barrier
-                    // for the guessed expansion anyway)
-                    if (j2 >= 0) krow[lane] = lane < R ? ix.adj[(size_t)key_id(kn) * R + lane] : BOA_PAD;
-                    PROF_T(t_m1);
-                    PROF_ADD(0, t_m1 - t_b1);
-                    PROF_ADD(10, j >= 0 ? 1 : 0);
-                    PROF_ADD(12, j >= 0 && j2 < 0 ? 1 : 0);
+                PROF_T(t0);
+                uint64_t ku;
+                const int found = wl.next(nk, ku, lane);
+                if (found != NEXT_FOUND) {
+                    wl.add(nk, true, lane);
+                    if (found == NEXT_NONE && wl.pn == 0) break;
+                    continue;
+                }
+                const uint32_t u = key_id(ku);
+                E += 1;
+                // ---- the helper that holds the node, or one to expand it now
+                uint64_t hm = __ballot(hnode == u);
+                if (hm == 0ull) {
+                    // one that holds nothing, at best the helper read last
+                    // (it may have the node's row); else one that is done with
+                    // a node named ahead, which is then named again later
+                    uint64_t fr = __ballot(hnode == BOA_PAD) & ALL;
+                    if (fr == 0ull)
+                        while ((fr = idle()) == 0ull) __builtin_amdgcn_s_sleep(1);
+                    const int hn = ((fr >> hl) & 1ull) ? hl : __ffsll((unsigned long long)fr) - 1;
+                    order(hn, TEAM_EXPAND, u);
+                    hm = 1ull << hn;
                 } else {
-                    // ---- the guessed next node: visited test, gathers, keys
-                    const uint64_t mk = wave_min64(ckey);
-                    const uint64_t gk = mk < kn_prev ? mk : kn_prev;
-                    guess = gk != KEY_NONE;
-                    if (guess) {
-                        g_id = key_id(gk);
-                        // the entry after the last selected node: its row came
-                        // from the worklist wave; a new key: its row is loaded
-                        // now. (A row of the best new key requested ahead was
-                        // measured slower: the compiler waits for it before the
-                        // gathers of the next expansion, whichever row is used.)
-                        if (bcast0(gk == kn_prev ? 1u : 0u)) {   // (uniform: a scalar branch)
-                            g_v = kn_row;
-                        } else {
-                            g_v = row_of(g_id);
-                            PROF_ADD(13, 1);
+                    PROF_ADD(8, 1);
+                }
+                const int h = __ffsll((unsigned long long)hm) - 1;
+                PROF_T(t1);
+                PROF_ADD(0, t1 - t0);
+                // ---- the previous expansion's keys enter the worklist
+                wl.add(nk, false, lane);
+                PROF_T(t2);
+                PROF_ADD(3, t2 - t1);
+                // ---- the two entries next in order (of the nearest pending
+                // one and the first two of the sorted list) are named to
+                // helpers that hold nothing, or neither of them
+                {
+                    const uint64_t s1 = wl.first_key();
+                    const uint64_t wm = wl.wmask & (wl.wmask - 1ull);
+                    const uint64_t s2 = wm ? readlane64(wl.win, __ffsll((unsigned long long)wm) - 1) : KEY_NONE;
+                    const bool pf = wl.pmin < s1;
+                    const uint64_t c0 = pf ? wl.pmin : s1, c1 = pf ? s1 : min(wl.pmin, s2);
+                    const uint64_t m0 = __ballot(hnode == key_id(c0)), m1 = __ballot(hnode == key_id(c1));
+                    const bool n0 = c0 != KEY_NONE && m0 == 0ull, n1 = c1 != KEY_NONE && m1 == 0ull;
+                    if (n0 || n1) {
+                        uint64_t av = __ballot(hnode == BOA_PAD) & ALL & ~hm;
+                        if (__popcll(av) < (n0 && n1 ? 2 : 1)) av |= idle() & ~(hm | m0 | m1);
+                        if (n0 && av) {
+                            order(__ffsll((unsigned long long)av) - 1, TEAM_EXPAND, key_id(c0));
+                            av &= av - 1ull;
                         }
-                        g_c = visit_row(g_v, g_nm);
-                        g_key = score_cands(g_c);
+                        if (n1 && av) order(__ffsll((unsigned long long)av) - 1, TEAM_EXPAND, key_id(c1));
                     }
-                    PROF_T(t_g1);
-                    PROF_ADD(1, t_g1 - t_b1);
                 }
-                PROF_T(t_pre2);
-                __syncthreads();   // the selection is published
-                PROF_T(t_b2);
-                PROF_ADD(merger ? 3 : 4, t_b2 - t_pre2);
-                const uint32_t sel = bcast0(ctl->sel);
-                if (sel == PAIR_DONE) {   // converged (both waves)
-                    if (!merger && guess) undo_row(g_v, g_nm);
-                    break;
-                }
-                if (!merger) {
-                    const uint64_t kn_new = ctl->kn;
-                    uint32_t c;
-                    PROF_ADD(guess ? (g_id == sel ? 8 : 9) : 14, 1);
-                    if (guess && g_id == sel) {
-                        ckey = g_key;
-                        c = g_c;
-                    } else {
-                        if (guess) undo_row(g_v, g_nm);
-                        uint64_t nm;
-                        const uint32_t v = sel == key_id(kn_prev) && kn_prev != KEY_NONE ? kn_row : row_of(sel);
-                        c = visit_row(v, nm);
-                        ckey = score_cands(c);
-                    }
-                    S += c;
-                    kbuf[lane] = ckey;
-                    // the entry after the selected node and its row, which the
-                    // worklist wave loaded
-                    kn_prev = kn_new;
-                    kn_row = krow[lane];
-                    PROF_T(t_g2);
-                    PROF_ADD(2, t_g2 - t_b2);
-                }
-                if (merger) {
-                    PROF_T(t_m2);
-                    PROF_ADD(5, t_m2 - t_b1);
-                }
+                PROF_T(t3);
+                PROF_ADD(1, t3 - t2);
+                // ---- its keys
+#ifdef BOA_STAGE_PROFILE
+                if (idle() & hm) PROF_ADD(12, 1);
+#endif
+                wait_for(hm);
+                PROF_T(t4);
+                PROF_ADD(2, t4 - t3);
+                const uint64_t key = keys[64 * h + lane];
+                if (lane == h) hnode = BOA_PAD;
+                hl = h;
+                const bool is_new = vs.test(key != KEY_NONE ? key_id(key) : BOA_PAD, lane) > 0;
+                S += (uint32_t)__popcll(__ballot(is_new));
+                nk = wl.filter(is_new ? key : KEY_NONE);
+                PROF_T(t5);
+                PROF_ADD(13, t5 - t4);
+                PROF_ADD(10, 1);
             }
-            // ---- epilogue (worklist wave): Eq. 3 over the first L entries
-            if (!merger && lane == 0) ctl->S = S;
-            __syncthreads();
-            if (merger) {
-                const uint32_t n_valid = lower_bound64(beam, min(len, (uint32_t)L), KEY_PHI1);
-                const int k = a.k;
-                uint32_t conf = 0;
-                if (n_valid > (uint32_t)k) {
-                    const double dk = sqrt((double)key_dist(beam[k - 1]));
-                    const double dmax = sqrt((double)key_dist(beam[n_valid - 1]));
-                    const double gamma = dmax == 0.0 ? 0.0 : (dmax - dk) / dmax;
-                    conf = gamma <= a.eps ? 1u : 0u;
-                }
-                const bool last = conf != 0u || p + 1 == a.p_end;
-                const uint32_t Sp = bcast0(ctl->S);
-                if (lane == 0) {
-                    const size_t ps = (size_t)p * a.nq + qi;
-                    if (a.qstat) {
-                        a.qstat[ps] = (uint8_t)(1u + conf);
-                        a.qE[ps] = E;
-                        a.qS[ps] = Sp;
-                    }
-                    if (a.user_E) a.user_E[qi] += E;
-                    if (a.user_S) a.user_S[qi] += Sp;
-                    if (a.write_conf) a.conf[t] = (uint8_t)conf;
-                    if (last) a.final_L[qi] = L;
-                    ctl->last = last ? 1u : 0u;
-                }
-                if (last) {
-                    for (int q = lane; q < k; q += 64) {
-                        uint32_t id = BOA_PAD;
-                        float dd = __int_as_float(0x7f800000);
-                        if ((uint32_t)q < n_valid) {
-                            id = key_id(beam[q]);
-                            dd = key_dist(beam[q]);
-                        }
-                        a.ids[(size_t)qi * k + q] = id;
-                        a.dists[(size_t)qi * k + q] = dd;
-                    }
-                }
+            // ---- end of the phase
+            const PhaseArgs &ae = cold_args();
+            const uint32_t n_valid = bcast0(lower_bound64(beam, min(wl.len, (uint32_t)L), KEY_PHI1));
+            float d_k = 0.f, d_max = 0.f;
+            if (n_valid > (uint32_t)ae.k) {
+                d_k = key_dist(beam[ae.k - 1]);
+                d_max = key_dist(beam[n_valid - 1]);
             }
-            __syncthreads();
-            if (bcast0(ctl->last)) break;   // (both waves)
+            const bool last = end_phase(ae, lane, p, qi, t, L, n_valid, d_k, d_max, E, S, vs.spill,
+                                        [&](int q, uint32_t &id, float &dd) {
+                                            const uint64_t kk = beam[q];
+                                            id = key_id(kk);
+                                            dd = key_dist(kk);
+                                        });
+            wave_sync();
+            if (last) break;
         }   // phases
+        // (no helper reads the query any more)
+        wait_for(ALL);
     }       // queries
+    for (int h = 0; h < TEAM_GROUPS; ++h) order(h, TEAM_EXIT, 0u);
+    vs.close(lane);
 #ifdef BOA_STAGE_PROFILE
     if (lane == 0 && a.prof) {
-        static constexpr int mine_m[] = {0, 3, 5, 10, 12};
-        static constexpr int mine_g[] = {1, 2, 4, 8, 9, 13, 14};
-        if (merger)
-            for (int i : mine_m) a.prof[(size_t)blockIdx.x * BOA_PROF_SLOTS + i] += prof_acc[i];
-        else
-            for (int i : mine_g) a.prof[(size_t)blockIdx.x * BOA_PROF_SLOTS + i] += prof_acc[i];
+        for (int i = 0; i < BOA_PROF_SLOTS; ++i) a.prof[(size_t)blockIdx.x * BOA_PROF_SLOTS + i] += prof_acc[i];
     }
 #endif
 }
@@ -1921,40 +1989,45 @@ static int occupancy_t(int wpb, size_t lds)
         else BOA_DISPATCH_W(VEC, DIM, 1, CALL);                              \
     } while (0)
 
-template <class Scorer>
-static hipError_t launch_pair_t(const PhaseArgs &a, int blocks, hipStream_t st)
+template <class Scorer, int P>
+static hipError_t launch_team_t(const PhaseArgs &a, int blocks, hipStream_t st)
 {
-    hipLaunchKernelGGL(pair_kernel<Scorer>, dim3(blocks), dim3(128), (size_t)a.lds_per_wave, st, a);
+    hipLaunchKernelGGL((team_kernel<Scorer, P>), dim3(blocks), dim3(64 * (1 + TEAM_GROUPS * P)),
+                       (size_t)a.lds_per_wave, st, a);
     return hipGetLastError();
 }
 
-template <class Scorer>
-static int pair_occupancy_t(size_t lds)
+template <class Scorer, int P>
+static int team_occupancy_t(size_t lds)
 {
     int nb = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, pair_kernel<Scorer>, 128, lds) != hipSuccess) return 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, team_kernel<Scorer, P>, 64 * (1 + TEAM_GROUPS * P), lds) !=
+        hipSuccess)
+        return 0;
     return nb;
 }
 
-// the two-wave escalation launch (wide scorers; lds_per_wave is the block's LDS)
-hipError_t launch_pair(const PhaseArgs &a, int vec_dtype, int blocks, hipStream_t st)
+// the launch with a team of waves per query (lds_per_wave is the block's LDS)
+hipError_t launch_team(const PhaseArgs &a, int vec_dtype, int parts, int blocks, hipStream_t st)
 {
     hipError_t e = hipSuccess;
-    BOA_DISPATCH_W(vec_dtype, a.ix.d, 2, e = launch_pair_t<S_>(a, blocks, st));
+    if (parts == 2) BOA_DISPATCH_W(vec_dtype, a.ix.d, 3, e = (launch_team_t<S_, 2>(a, blocks, st)));
+    else BOA_DISPATCH_W(vec_dtype, a.ix.d, 3, e = (launch_team_t<S_, 1>(a, blocks, st)));
     return e;
 }
 
-int pair_occupancy(int vec_dtype, int d, size_t lds)
+int team_occupancy(int vec_dtype, int d, int parts, size_t lds)
 {
     int r = 0;
-    BOA_DISPATCH_W(vec_dtype, d, 2, r = pair_occupancy_t<S_>(lds));
+    if (parts == 2) BOA_DISPATCH_W(vec_dtype, d, 3, r = (team_occupancy_t<S_, 2>(lds)));
+    else BOA_DISPATCH_W(vec_dtype, d, 3, r = (team_occupancy_t<S_, 1>(lds)));
     return r;
 }
 
-size_t pair_lds_bytes(int32_t L, uint32_t vis_words, int scorer_lds)
+size_t team_lds_bytes(int32_t L, int parts, uint32_t vis_words, int scorer_lds)
 {
     const int32_t Lb = beam_slots(L), pw = ((L >> 6) + 3) & ~1;
-    return (size_t)8 * Lb + 8 * 64 + 8 * (size_t)pw + 8 * 64 + 4 * 64 + sizeof(PairCtrl) + 4 * 64 + 4 * 64 +
+    return (size_t)8 * Lb + 8 * 64 + 8 * (size_t)pw + TEAM_GROUPS * (8 * 64 + parts * sizeof(TeamWave)) +
            (size_t)scorer_lds + 4 * (size_t)vis_words;
 }
 
