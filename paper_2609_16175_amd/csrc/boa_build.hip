@@ -9,7 +9,10 @@
 //   1. medoid: the point nearest (float64) to the float64 centroid, ties to
 //      the lowest id; the centroid is reduced in one fixed order;
 //   2. candidates: the K = min(2R, 128, n - 1) nearest points of every
-//      point by brute force, ordered by (distance, id);
+//      point by brute force, ordered by (distance, id), and for each
+//      attribute level the nearest min(R / 2, 32, n - 1) among the points
+//      within the point's attribute threshold, all from one pass over the
+//      distances;
 //   3. alpha-pruning (DiskANN's dominance rule, alpha = 1.2 on Euclidean
 //      distances): a candidate v of u is dropped when a kept w has
 //      alpha^2 d(w, v) <= d(u, v) on squared distances;
@@ -36,12 +39,9 @@
 namespace boa {
 
 static constexpr uint64_t BKEY_NONE = ~0ull;
-static constexpr int KNN_ROWS_W = 8;      // rows per wave in the kNN scan
-static constexpr int KNN_WAVES = 4;       // waves per block
-static constexpr int KNN_ROWS_B = KNN_ROWS_W * KNN_WAVES;
-static constexpr int KNN_LIST = 128;      // top-K capacity per row
-static constexpr int KNN_BUF = 64;        // new-candidate buffer per row
-static constexpr int KNN_KC = 64;         // dimensions per staged column chunk
+static constexpr int KNN_LIST = 128;      // most candidates per point
+static constexpr int KNN_LEVELS = 4;      // attribute levels
+static constexpr int KNN_LEVEL_LIST = 32; // most candidates per point and level
 
 __device__ __forceinline__ uint64_t bkey(float d, uint32_t id)
 {
@@ -69,6 +69,39 @@ __device__ __forceinline__ float pair_dist_f32(const float *x, const float *y, i
         acc = __builtin_fmaf(t, t, acc);
     }
     return acc;
+}
+
+// Whether scale * (that distance) <= bound. The partial sums never decrease
+// (nor does their product with the scale, both rounded), so the wave stops
+// once no lane's is within its bound; NaN compares false as in the full sum.
+__device__ __forceinline__ bool pair_within_f32(const float *x, const float *y, int d, float scale, float bound)
+{
+    const float4 *a = reinterpret_cast<const float4 *>(x);
+    const float4 *b = reinterpret_cast<const float4 *>(y);
+    const int nch = d >> 2;
+    float acc = 0.f;
+    for (int c0 = 0; c0 < nch; c0 += 8) {
+        float4 p[8], q[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {   // (past the row: its last chunk, not added)
+            p[i] = a[min(c0 + i, nch - 1)];
+            q[i] = b[min(c0 + i, nch - 1)];
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            if (c0 + i >= nch) break;
+            float t = p[i].x - q[i].x;
+            acc = __builtin_fmaf(t, t, acc);
+            t = p[i].y - q[i].y;
+            acc = __builtin_fmaf(t, t, acc);
+            t = p[i].z - q[i].z;
+            acc = __builtin_fmaf(t, t, acc);
+            t = p[i].w - q[i].w;
+            acc = __builtin_fmaf(t, t, acc);
+        }
+        if (__ballot(scale * acc <= bound) == 0ull) return false;
+    }
+    return scale * acc <= bound;
 }
 
 // exact squared distance of two uint8 rows: |x|^2 + |y|^2 - 2 x.y in int32
@@ -100,7 +133,7 @@ __device__ __forceinline__ float dist_ids(const BuildView &v, uint32_t a, uint32
 }
 
 // ---------------------------------------------------------------------------
-// in-wave bitonic sort of 256 u64 keys held in LDS (ascending)
+// in-wave bitonic sort of N u64 keys held in LDS (ascending; N = 128 or 256)
 
 __device__ __forceinline__ void wave_fence()
 {
@@ -109,15 +142,16 @@ __device__ __forceinline__ void wave_fence()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-__device__ void bitonic256(uint64_t *a, int lane)
+template <int N>
+__device__ void bitonic(uint64_t *a, int lane)
 {
-    for (int k = 2; k <= 256; k <<= 1) {
+    for (int k = 2; k <= N; k <<= 1) {
         for (int j = k >> 1; j > 0; j >>= 1) {
-            // 128 compare-exchanges per step, two per lane
+            // N / 2 compare-exchanges per step, N / 128 per lane
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const int t = lane + 64 * h;                       // pair index 0..127
-                const int i = ((t / j) * 2 * j) + (t % j);         // lower element
+            for (int h = 0; h < N / 128; ++h) {
+                const int t = lane + 64 * h;                       // pair index
+                const int i = ((t & ~(j - 1)) << 1) | (t & (j - 1)); // lower element
                 const int p = i + j;
                 const bool up = (i & k) == 0;
                 const uint64_t x = a[i], y = a[p];
@@ -208,221 +242,377 @@ __global__ void __launch_bounds__(256) medoid_partial_kernel(MedoidArgs a)
     }
 }
 
-__global__ void norms_kernel(BuildView v, uint32_t *norms)
+// |x|^2 of every uint8 point, and of the point shifted by -128 (for signed
+// matrix instructions)
+__global__ void norms_kernel(BuildView v, uint32_t *norms, int32_t *norms_shifted)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= v.n) return;
     const uint32_t *x = reinterpret_cast<const uint32_t *>(reinterpret_cast<const uint8_t *>(v.vectors) + (size_t)i * v.d);
     uint32_t s = 0;
-    for (int c = 0; c < (v.d >> 2); ++c) s = __builtin_amdgcn_udot4(x[c], x[c], s, false);
+    int32_t t = 0;
+    for (int c = 0; c < (v.d >> 2); ++c) {
+        s = __builtin_amdgcn_udot4(x[c], x[c], s, false);
+        const int32_t y = (int32_t)(x[c] ^ 0x80808080u);
+        t = __builtin_amdgcn_sdot4(y, y, t, false);
+    }
     norms[i] = s;
+    norms_shifted[i] = t;
 }
 
 // ---------------------------------------------------------------------------
-// 2. exact K nearest candidates of every point
+// 2. exact nearest candidates of every point
 //
-// A block of 4 waves owns 32 rows (8 per wave) and streams every column
-// tile of 64 points through LDS, dimension-major in chunks of 64 dims (lane
-// j reads column j, conflict-free). Each lane accumulates its column's
-// distance to the wave's 8 rows (row values are wave-uniform). Each row
-// keeps its K best (distance, id) keys in LDS plus a buffer of new keys
-// below its current K-th; a full buffer is merged by a bitonic sort.
+// A panel of rows at a time: its distances to all points go to memory, and a
+// wave per row then picks the nearest for every list in one sweep. One sweep per list, with the distances computed
+// again for each and the rows' lists holding the compute units' LDS, took 5
+// times 11.7 ms at n = 30,000, d = 96, five lists; see the kernels for theirs.
 
-struct KnnArgs {
-    BuildView v;
-    int32_t K;
-    uint32_t *cand;    // n x K ids (0xFFFFFFFF padded)
-    float *cand_d;     // n x K squared distances
-    // attribute-threshold pass: only points within a row's threshold count
-    const int32_t *ranks;   // n x m quantile ranks (null: no filter)
-    const int32_t *thr;     // n thresholds in rank units
-    int32_t m;
-};
+static constexpr int DT = 128;   // rows and columns of a distance tile
+static constexpr int DK = 16;    // dimensions staged at once (float32)
 
-// attribute distance of two points: the largest gap between their ranks
-// over the columns
-__device__ __forceinline__ int32_t rank_gap(const int32_t *ranks, int m, int64_t a, int64_t b)
+// Distances of rows [r0, r0 + rows) to every point, float32, dimensions in
+// order (the sums of pair_dist_f32). 128 x 128 tiles, 8 x 8 pairs per thread:
+// 128 vector instructions for four LDS reads per dimension, so that it runs at
+// the vector units' rate (a difference and a fused multiply-add per pair and
+// dimension; matrix instructions would sum in another order).
+__global__ void __launch_bounds__(256) dist_f32_kernel(const float *X, int64_t n, int d, int64_t r0, int64_t rows,
+                                                       int64_t ld, float *D)
 {
-    int32_t g = 0;
-    for (int j = 0; j < m; ++j) {
-        const int32_t t = ranks[a * m + j] - ranks[b * m + j];
-        g = max(g, t < 0 ? -t : t);
+    __shared__ __align__(16) float A[DK][DT + 4], B[DK][DT + 4];
+    const int t = threadIdx.x, tr = t >> 4, tc = t & 15;
+    const int64_t row0 = r0 + (int64_t)blockIdx.y * DT, col0 = (int64_t)blockIdx.x * DT;
+    float acc[8][8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) acc[i][j] = 0.f;
+    for (int k0 = 0; k0 < d; k0 += DK) {
+        // 128 points x 16 dimensions of each side, two float4 per thread; zeros
+        // past the row's dimensions (they add zero) and past the last point
+        float4 x[2], y[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int e = t + 256 * h, p = e >> 2, k = k0 + 4 * (e & 3);
+            const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
+            x[h] = k < d && row0 + p < n ? *reinterpret_cast<const float4 *>(X + (size_t)(row0 + p) * d + k) : z;
+            y[h] = k < d && col0 + p < n ? *reinterpret_cast<const float4 *>(X + (size_t)(col0 + p) * d + k) : z;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int e = t + 256 * h, p = e >> 2, k = 4 * (e & 3);
+            A[k][p] = x[h].x;
+            A[k + 1][p] = x[h].y;
+            A[k + 2][p] = x[h].z;
+            A[k + 3][p] = x[h].w;
+            B[k][p] = y[h].x;
+            B[k + 1][p] = y[h].y;
+            B[k + 2][p] = y[h].z;
+            B[k + 3][p] = y[h].w;
+        }
+        __syncthreads();
+#pragma unroll 4
+        for (int k = 0; k < DK; ++k) {
+            const float4 a0 = *reinterpret_cast<const float4 *>(&A[k][4 * tr]);
+            const float4 a1 = *reinterpret_cast<const float4 *>(&A[k][64 + 4 * tr]);
+            const float4 b0 = *reinterpret_cast<const float4 *>(&B[k][4 * tc]);
+            const float4 b1 = *reinterpret_cast<const float4 *>(&B[k][64 + 4 * tc]);
+            const float a[8] = {a0.x, a0.y, a0.z, a0.w, a1.x, a1.y, a1.z, a1.w};
+            const float b[8] = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w};
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const float e = a[i] - b[j];
+                    acc[i][j] = __builtin_fmaf(e, e, acc[i][j]);
+                }
+        }
     }
-    return g;
+    // (ld is a multiple of the tile: columns past n are written and not read)
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const int64_t r = (int64_t)blockIdx.y * DT + (i < 4 ? 4 * tr + i : 64 + 4 * tr + i - 4);
+        if (r >= rows) continue;
+        float *o = D + (size_t)r * ld + col0;
+        *reinterpret_cast<float4 *>(o + 4 * tc) = make_float4(acc[i][0], acc[i][1], acc[i][2], acc[i][3]);
+        *reinterpret_cast<float4 *>(o + 64 + 4 * tc) = make_float4(acc[i][4], acc[i][5], acc[i][6], acc[i][7]);
+    }
 }
 
-template <bool U8>
-__global__ void __launch_bounds__(256) knn_kernel(KnnArgs a)
+typedef int32_t int4v __attribute__((ext_vector_type(4)));
+typedef int32_t int16v __attribute__((ext_vector_type(16)));
+
+// The same for uint8 points, exact: |x - y|^2 = |x'|^2 + |y'|^2 - 2 x'.y' of
+// the points shifted by -128, whose products are matrix instructions on signed
+// bytes (32 x 32 pairs, 32 dimensions each: 16 consecutive bytes of a row per
+// lane, as they lie in memory). A wave computes 64 x 64 pairs, a block of four
+// 128 x 128; the products are a twentieth of the time, the writes the rest.
+__global__ void __launch_bounds__(256) dist_u8_kernel(const uint8_t *X, const int32_t *norms, int64_t n, int d,
+                                                      int64_t r0, int64_t rows, int64_t ld, float *D)
 {
-    extern __shared__ __align__(16) unsigned char smem[];
-    const int lane = threadIdx.x & 63;
-    const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int d = a.v.d, K = a.K;
-    const int64_t n = a.v.n;
-    // LDS: per wave 8 rows x (list 128 + buffer 64) keys and a 256-key sort
-    // scratch; then the staged column chunk (64 columns x 64 dims) and row
-    // chunk (32 rows x 64 dims), both in 4-dimension units
-    constexpr int PER_WAVE = KNN_ROWS_W * (KNN_LIST + KNN_BUF) + 256;
-    uint64_t *lists = reinterpret_cast<uint64_t *>(smem) + (size_t)wid * PER_WAVE;
-    uint64_t *scratch = lists + KNN_ROWS_W * (KNN_LIST + KNN_BUF);
-    unsigned char *colbase = smem + (size_t)KNN_WAVES * PER_WAVE * 8;
-    constexpr int UNIT = U8 ? 4 : 16;   // bytes per 4-dimension unit
-    unsigned char *rowbase = colbase + (size_t)(KNN_KC / 4) * 64 * UNIT;
-
-    const int64_t blk_row0 = (int64_t)blockIdx.x * KNN_ROWS_B;
-    const int64_t row0 = blk_row0 + wid * KNN_ROWS_W;
-    for (int i = lane; i < KNN_ROWS_W * (KNN_LIST + KNN_BUF); i += 64) lists[i] = BKEY_NONE;
-    uint64_t thr[KNN_ROWS_W];
-    uint32_t bufn[KNN_ROWS_W], listn[KNN_ROWS_W], rnorm[KNN_ROWS_W];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int half = lane >> 5, l32 = lane & 31;
+    const int64_t row0 = r0 + (int64_t)blockIdx.y * DT + 64 * (w >> 1);
+    const int64_t col0 = (int64_t)blockIdx.x * DT + 64 * (w & 1);
+    int16v acc[2][2] = {};
+    for (int k0 = 0; k0 < d; k0 += 32) {
+        const int k = k0 + 16 * half;
+        int4v a[2], b[2];
 #pragma unroll
-    for (int r = 0; r < KNN_ROWS_W; ++r) {
-        thr[r] = BKEY_NONE;
-        bufn[r] = 0;
-        listn[r] = 0;
-        const int64_t row = row0 + r;
-        rnorm[r] = (U8 && row < n) ? a.v.norms[row] : 0u;
+        for (int h = 0; h < 2; ++h) {
+            // (a row past the last point: point 0, its pairs are not read; bytes
+            // past the row's dimensions: zero)
+            const int64_t r = row0 + 32 * h + l32, c = col0 + 32 * h + l32;
+            a[h] = 0;
+            b[h] = 0;
+            if (k < d) {
+                a[h] = *reinterpret_cast<const int4v *>(X + (size_t)(r < n ? r : 0) * d + k) ^ (int32_t)0x80808080;
+                b[h] = *reinterpret_cast<const int4v *>(X + (size_t)(c < n ? c : 0) * d + k) ^ (int32_t)0x80808080;
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+                acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[i], b[j], acc[i][j], 0, 0, 0);
     }
-    wave_fence();
-
-    // merge row r's buffer into its list: both copied into the scratch,
-    // sorted, the K best written back
-    auto merge_row = [&](int r) {
-        uint64_t *L = lists + r * (KNN_LIST + KNN_BUF);
-        uint64_t *B = L + KNN_LIST;
-        for (int i = lane; i < 256; i += 64) {
-            uint64_t x = BKEY_NONE;
-            if (i < KNN_LIST) x = L[i];
-            else if (i < KNN_LIST + KNN_BUF) x = B[i - KNN_LIST];
-            scratch[i] = x;
-        }
-        wave_fence();
-        bitonic256(scratch, lane);
-        for (int i = lane; i < KNN_LIST + KNN_BUF; i += 64) {
-            if (i < KNN_LIST) L[i] = i < K ? scratch[i] : BKEY_NONE;
-            else B[i - KNN_LIST] = BKEY_NONE;
-        }
-        wave_fence();
-        const uint32_t tot = min(listn[r] + bufn[r], (uint32_t)K);
-        listn[r] = tot;
-        bufn[r] = 0;
-        thr[r] = tot == (uint32_t)K ? L[K - 1] : BKEY_NONE;
-    };
-
-    const int nchunk = (d + KNN_KC - 1) / KNN_KC;
-    for (int64_t c0 = 0; c0 < n; c0 += 64) {
-        const int64_t col = c0 + lane;
-        const bool colv = col < n;
-        float accf[KNN_ROWS_W];
-        uint32_t acci[KNN_ROWS_W];
+    // accumulator register g of lane l: row 8 (g / 4) + 4 (l / 32) + g % 4,
+    // column l % 32
 #pragma unroll
-        for (int r = 0; r < KNN_ROWS_W; ++r) {
-            accf[r] = 0.f;
-            acci[r] = 0u;
-        }
-        for (int ch = 0; ch < nchunk; ++ch) {
-            const int k0 = ch * KNN_KC;
-            const int nu = min(KNN_KC, d - k0) >> 2;   // 4-dimension units in this chunk
-            __syncthreads();   // the previous chunk is consumed
-            // unit u of column j at colT[u * 64 + j]; of row r at rowT[r * 16 + u]
-            for (int e = threadIdx.x; e < nu * 64; e += 256) {
-                const int u = e >> 6, j = e & 63;
-                const int64_t cj = c0 + j;
-                if (U8) {
-                    const uint8_t *X = reinterpret_cast<const uint8_t *>(a.v.vectors);
-                    reinterpret_cast<uint32_t *>(colbase)[e] =
-                        cj < n ? reinterpret_cast<const uint32_t *>(X + (size_t)cj * d + k0)[u] : 0u;
-                } else {
-                    const float *X = reinterpret_cast<const float *>(a.v.vectors);
-                    reinterpret_cast<float4 *>(colbase)[e] =
-                        cj < n ? reinterpret_cast<const float4 *>(X + (size_t)cj * d + k0)[u]
-                               : make_float4(0.f, 0.f, 0.f, 0.f);
-                }
+    for (int i = 0; i < 2; ++i) {
+#pragma unroll
+        for (int g = 0; g < 16; ++g) {
+            const int64_t r = row0 + 32 * i + 8 * (g >> 2) + 4 * half + (g & 3);
+            if (r >= r0 + rows) continue;
+            const int32_t nr = norms[r];
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const int64_t c = col0 + 32 * j + l32;
+                const int32_t nc = norms[c < n ? c : 0];
+                D[(size_t)(r - r0) * ld + c] = (float)(nr + nc - 2 * acc[i][j][g]);
             }
-            for (int e = threadIdx.x; e < KNN_ROWS_B * 16; e += 256) {
-                const int r = e >> 4, u = e & 15;
-                const int64_t rr = blk_row0 + r;
-                if (u >= nu) continue;
-                if (U8) {
-                    const uint8_t *X = reinterpret_cast<const uint8_t *>(a.v.vectors);
-                    reinterpret_cast<uint32_t *>(rowbase)[e] =
-                        rr < n ? reinterpret_cast<const uint32_t *>(X + (size_t)rr * d + k0)[u] : 0u;
-                } else {
-                    const float *X = reinterpret_cast<const float *>(a.v.vectors);
-                    reinterpret_cast<float4 *>(rowbase)[e] =
-                        rr < n ? reinterpret_cast<const float4 *>(X + (size_t)rr * d + k0)[u]
-                               : make_float4(0.f, 0.f, 0.f, 0.f);
-                }
-            }
-            __syncthreads();
-            if (U8) {
-                const uint32_t *colT = reinterpret_cast<const uint32_t *>(colbase);
-                const uint32_t *rowT = reinterpret_cast<const uint32_t *>(rowbase) + wid * KNN_ROWS_W * 16;
-                for (int u = 0; u < nu; ++u) {
-                    const uint32_t cv = colT[u * 64 + lane];
+        }
+    }
+}
+
+struct SelectArgs {
+    const float *D;          // rows [r0, r0 + rows) x ld
+    int64_t n, r0, rows, ld;
+    int32_t K, Kl, levels, m;
+    const int32_t *ranks;    // m x n quantile ranks
+    const int32_t *thr;      // levels x n thresholds in rank units, not decreasing over the levels
+    uint32_t *cand;          // n x K ids (0xFFFFFFFF padded)
+    uint32_t *lcand;         // levels x n x Kl ids
+};
+
+// The K (at most N / 2) smallest keys seen, in the first half of N slots of
+// LDS (BKEY_NONE past their number), and behind them the newer ones: sorted and
+// cut when the next ones do not fit.
+template <int N>
+struct TopList {
+    uint64_t *a;
+    int cnt, K;
+    uint64_t limit;   // a key must be below it to enter
+    __device__ __forceinline__ void init(uint64_t *lds, int K_, int lane)
+    {
+        a = lds;
+        cnt = 0;
+        K = K_;
+        limit = BKEY_NONE;
+        for (int i = lane; i < N; i += 64) a[i] = BKEY_NONE;
+    }
+    __device__ __forceinline__ void cut(int lane)
+    {
+        wave_fence();
+        bitonic<N>(a, lane);
+        for (int i = lane; i < N; i += 64)
+            if (i >= K) a[i] = BKEY_NONE;
+        wave_fence();
+        if (cnt >= K) {
+            cnt = K;
+            const uint64_t last = a[K - 1];
+            limit = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(last >> 32)) << 32) |
+                    (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)last);
+        }
+    }
+    __device__ __forceinline__ void push(uint64_t key, int lane)
+    {
+        uint64_t m = __ballot(key < limit);
+        if (m == 0ull) return;
+        if (cnt + (int)__popcll(m) > N) {
+            cut(lane);
+            m = __ballot(key < limit);
+            if (m == 0ull) return;
+        }
+        const int below = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+        if (key < limit) a[cnt + below] = key;
+        cnt += (int)__popcll(m);
+    }
+};
+
+// A wave per row: one sweep over the row's distances fills the list by vector
+// distance and one list per attribute level. At n = 30,000 and m = 3 a sweep
+// is about 120 thousand cycles, a third of them the lists' sorts; 24 waves per
+// CU (6 KB of lists each) run side by side.
+__global__ void __launch_bounds__(256) select_kernel(SelectArgs a)
+{
+    __shared__ uint64_t lists[4][256 + 128 * KNN_LEVELS];
+    const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t i = (int64_t)blockIdx.x * 4 + wid;
+    if (i >= a.rows) return;
+    const int64_t row = a.r0 + i;
+    TopList<256> near;
+    TopList<128> lvl[KNN_LEVELS];
+    near.init(lists[wid], a.K, lane);
+    int32_t t[KNN_LEVELS];
 #pragma unroll
-                    for (int r = 0; r < KNN_ROWS_W; ++r)
-                        acci[r] = __builtin_amdgcn_udot4(cv, rowT[r * 16 + u], acci[r], false);
-                }
-            } else {
-                const float4 *colT = reinterpret_cast<const float4 *>(colbase);
-                const float4 *rowT = reinterpret_cast<const float4 *>(rowbase) + wid * KNN_ROWS_W * 16;
-                for (int u = 0; u < nu; ++u) {
-                    const float4 cv = colT[u * 64 + lane];
+    for (int l = 0; l < KNN_LEVELS; ++l) {
+        lvl[l].init(lists[wid] + 256 + 128 * l, a.Kl, lane);
+        t[l] = l < a.levels ? a.thr[(size_t)l * a.n + row] : -1;
+    }
+    int32_t mine[BOA_MAX_M];
 #pragma unroll
-                    for (int r = 0; r < KNN_ROWS_W; ++r) {
-                        const float4 rv = rowT[r * 16 + u];   // the same address in every lane
-                        float t = cv.x - rv.x;
-                        accf[r] = __builtin_fmaf(t, t, accf[r]);
-                        t = cv.y - rv.y;
-                        accf[r] = __builtin_fmaf(t, t, accf[r]);
-                        t = cv.z - rv.z;
-                        accf[r] = __builtin_fmaf(t, t, accf[r]);
-                        t = cv.w - rv.w;
-                        accf[r] = __builtin_fmaf(t, t, accf[r]);
+    for (int j = 0; j < BOA_MAX_M; ++j) mine[j] = a.levels > 0 && j < a.m ? a.ranks[(size_t)j * a.n + row] : 0;
+    const float *D = a.D + (size_t)i * a.ld;
+    constexpr int U = 4;   // columns per lane in flight
+    for (int64_t c0 = 0; c0 < a.n; c0 += 64 * U) {
+        float dd[U];
+        int32_t gap[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t c = c0 + 64 * u + lane;
+            dd[u] = D[c < a.n ? c : a.n - 1];
+            gap[u] = 0;
+        }
+        if (a.levels > 0) {
+            // attribute distance: the largest gap of ranks over the columns
+#pragma unroll
+            for (int j = 0; j < BOA_MAX_M; ++j) {
+                if (j < a.m) {   // uniform
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        const int64_t c = c0 + 64 * u + lane;
+                        const int32_t g = mine[j] - a.ranks[(size_t)j * a.n + (c < a.n ? c : a.n - 1)];
+                        gap[u] = max(gap[u], g < 0 ? -g : g);
                     }
                 }
             }
         }
-        const uint32_t cnorm = (U8 && colv) ? a.v.norms[col] : 0u;
-        // candidates below each row's K-th key go to its buffer
 #pragma unroll
-        for (int r = 0; r < KNN_ROWS_W; ++r) {
-            const int64_t row = row0 + r;
-            if (row >= n) continue;   // uniform
-            const float dd = U8 ? (float)(int32_t)(rnorm[r] + cnorm - 2u * acci[r]) : accf[r];
-            bool within = colv && col != row;
-            if (a.ranks && within) within = rank_gap(a.ranks, a.m, row, col) <= a.thr[row];
-            const uint64_t key = within ? bkey(dd, (uint32_t)col) : BKEY_NONE;
-            const uint64_t m = __ballot(key < thr[r]);
-            if (m) {
-                if (bufn[r] + (uint32_t)__popcll(m) > (uint32_t)KNN_BUF) merge_row(r);
-                // re-test against the threshold the merge may have tightened
-                const bool pass = key < thr[r];
-                const uint64_t m2 = __ballot(pass);
-                if (m2) {
-                    uint64_t *B = lists + r * (KNN_LIST + KNN_BUF) + KNN_LIST;
-                    const uint32_t below = __builtin_amdgcn_mbcnt_hi((uint32_t)(m2 >> 32),
-                                                                     __builtin_amdgcn_mbcnt_lo((uint32_t)m2, 0u));
-                    if (pass) B[bufn[r] + below] = key;
-                    bufn[r] += (uint32_t)__popcll(m2);
-                    wave_fence();
-                }
+        for (int u = 0; u < U; ++u) {
+            const int64_t c = c0 + 64 * u + lane;
+            const uint64_t key = c < a.n && c != row ? bkey(dd[u], (uint32_t)c) : BKEY_NONE;
+            near.push(key, lane);
+#pragma unroll
+            for (int l = 0; l < KNN_LEVELS; ++l)
+                if (l < a.levels) lvl[l].push(gap[u] <= t[l] ? key : BKEY_NONE, lane);
+        }
+    }
+    near.cut(lane);
+    for (int q = lane; q < a.K; q += 64) {
+        const uint64_t x = near.a[q];
+        a.cand[(size_t)row * a.K + q] = x == BKEY_NONE ? BOA_PAD : (uint32_t)x;
+    }
+#pragma unroll
+    for (int l = 0; l < KNN_LEVELS; ++l) {
+        if (l >= a.levels) break;
+        lvl[l].cut(lane);
+        for (int q = lane; q < a.Kl; q += 64) {
+            const uint64_t x = lvl[l].a[q];
+            a.lcand[((size_t)l * a.n + row) * a.Kl + q] = x == BKEY_NONE ? BOA_PAD : (uint32_t)x;
+        }
+    }
+}
+
+// Quantile rank of every cell within its column: the number of strictly
+// smaller values (equal values share a rank; float32 columns compare as
+// floats). A thread per cell, the column through LDS: n^2 comparisons, 0.4 ms
+// a column at n = 60,000, without a sort.
+__global__ void __launch_bounds__(256) ranks_kernel(const int32_t *attrs, int64_t n, int m, uint32_t f32_mask,
+                                                    int32_t *ranks)
+{
+    __shared__ int32_t tile[1024];
+    const int j = blockIdx.y;
+    const bool f = (f32_mask >> j) & 1u;
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const int32_t x = i < n ? attrs[(size_t)i * m + j] : 0;
+    int32_t below = 0;
+    for (int64_t c0 = 0; c0 < n; c0 += 1024) {
+        const int cn = (int)(n - c0 < 1024 ? n - c0 : 1024);
+        __syncthreads();
+        for (int c = threadIdx.x; c < cn; c += 256) tile[c] = attrs[(size_t)(c0 + c) * m + j];
+        __syncthreads();
+        if (f) {
+            const float xf = __int_as_float(x);
+            for (int c = 0; c < cn; ++c) below += __int_as_float(tile[c]) < xf ? 1 : 0;
+        } else {
+            for (int c = 0; c < cn; ++c) below += tile[c] < x ? 1 : 0;
+        }
+    }
+    if (i < n) ranks[(size_t)j * n + i] = below;
+}
+
+static constexpr int SAMPLE = 4096;
+
+// ranks of the sample points floor(s n / S), S = min(SAMPLE, n): m x SAMPLE
+__global__ void sample_kernel(const int32_t *ranks, int64_t n, int32_t *sample)
+{
+    const int s = blockIdx.x * blockDim.x + threadIdx.x;
+    if (s >= SAMPLE || s >= n) return;
+    const int64_t id = n >= SAMPLE ? ((int64_t)s * n) / SAMPLE : s;
+    sample[(size_t)blockIdx.y * SAMPLE + s] = ranks[(size_t)blockIdx.y * n + id];
+}
+
+struct ThresholdArgs {
+    const int32_t *ranks;    // m x n
+    const int32_t *sample;   // m x SAMPLE
+    int64_t n;
+    int32_t m, levels;
+    int32_t order[KNN_LEVELS];   // per level: the threshold's place in the sorted distances
+    int32_t *thr;            // levels x n
+};
+
+// Per point and level: the order[l]-th smallest of its attribute distances to
+// the sample. A wave per point holds the S distances in registers and finds
+// the smallest value with enough distances at or below it by bisection (up to
+// 21 counts of S comparisons per level, in place of a selection per level on
+// the host: 150 ms of 16 threads at n = 60,000).
+__global__ void __launch_bounds__(256) thresholds_kernel(ThresholdArgs a)
+{
+    const int lane = threadIdx.x & 63;
+    const int64_t u = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (u >= a.n) return;
+    const int S = a.n < SAMPLE ? (int)a.n : SAMPLE;
+    int32_t g[SAMPLE / 64];
+#pragma unroll
+    for (int i = 0; i < SAMPLE / 64; ++i) g[i] = lane + 64 * i < S ? 0 : INT32_MAX;   // (past it: never counted)
+    for (int j = 0; j < a.m; ++j) {
+        const int32_t *rk = a.sample + (size_t)j * SAMPLE;
+        const int32_t x = a.ranks[(size_t)j * a.n + u];
+#pragma unroll
+        for (int i = 0; i < SAMPLE / 64; ++i) {
+            const int s = lane + 64 * i;
+            if (s < S) {
+                const int32_t t = x - rk[s];
+                g[i] = max(g[i], t < 0 ? -t : t);
             }
         }
     }
-    // final merges and output
+    for (int l = 0; l < a.levels; ++l) {
+        int32_t lo = 0, hi = (int32_t)(a.n - 1);   // the answer is in [lo, hi]
+        while (lo < hi) {
+            const int32_t mid = lo + ((hi - lo) >> 1);
+            int32_t c = 0;
 #pragma unroll
-    for (int r = 0; r < KNN_ROWS_W; ++r) {
-        const int64_t row = row0 + r;
-        if (row >= n) continue;
-        if (bufn[r] > 0) merge_row(r);
-        const uint64_t *L = lists + r * (KNN_LIST + KNN_BUF);
-        for (int i = lane; i < K; i += 64) {
-            const uint64_t x = L[i];
-            a.cand[(size_t)row * K + i] = x == BKEY_NONE ? BOA_PAD : (uint32_t)x;
-            a.cand_d[(size_t)row * K + i] =
-                x == BKEY_NONE ? __int_as_float(0x7f800000) : __uint_as_float((uint32_t)(x >> 32));
+            for (int i = 0; i < SAMPLE / 64; ++i) c += g[i] <= mid ? 1 : 0;
+#pragma unroll
+            for (int s = 32; s >= 1; s >>= 1) c += __shfl_xor(c, s);
+            c = __builtin_amdgcn_readfirstlane(c);
+            if (c > a.order[l]) hi = mid;
+            else lo = mid + 1;
         }
+        if (lane == 0) a.thr[(size_t)l * a.n + u] = lo;
     }
 }
 
@@ -445,59 +635,82 @@ struct PruneArgs {
     uint32_t *out;     // n x R (0xFFFFFFFF padded)
 };
 
-// Prune the keys sorted in `keys[0, cnt)` (cnt <= 256) for point u into out
-// (at most `budget` ids), by the alpha-dominance rule. Lanes test each
-// candidate against all kept points at once.
-__device__ void alpha_prune(const BuildView &v, uint32_t u, const uint64_t *keys, int cnt, int budget,
-                            float alpha2, uint32_t *kept, uint32_t *out_row, int R, int lane)
+// Prune the keys sorted in `keys[0, cnt)` (cnt <= 256) into out_row (at most
+// `budget` ids), by the alpha-dominance rule. Every kept point is tested at
+// once against all the candidates still alive, four per lane: as many steps
+// as points are kept (8 to 63), instead of one per candidate (up to 256) with
+// a lane per kept point: 14.5 and 5.6 ms of pruning at n = 30,000, d = 96, R = 64;
+// 28.7 and 12.1 ms at n = 10,000, d = 768, R = 48.
+__device__ void alpha_prune(const BuildView &v, const uint64_t *keys, int cnt, int budget, float alpha2,
+                            uint32_t *out_row, int R, int lane)
 {
+    uint64_t key[4];
+    bool alive[4];
+#pragma unroll
+    for (int h = 0; h < 4; ++h) {
+        const int i = lane + 64 * h;
+        key[h] = i < cnt ? keys[i] : BKEY_NONE;
+        alive[h] = key[h] != BKEY_NONE;
+    }
     int nk = 0;
-    for (int c = 0; c < cnt && nk < budget; ++c) {
-        const uint64_t key = keys[c];
-        if (key == BKEY_NONE) break;
-        const uint32_t cv = (uint32_t)key;
-        const float duv = __uint_as_float((uint32_t)(key >> 32));
-        bool dom = false;
-        for (int j0 = 0; j0 < nk; j0 += 64) {
-            const int j = j0 + lane;
-            bool hit = false;
-            if (j < nk) hit = alpha2 * dist_ids(v, kept[j], cv) <= duv;
-            if (__ballot(hit)) {
-                dom = true;
-                break;
+    uint32_t mine = BOA_PAD;   // lane i: the i-th kept id (budget < R <= 64)
+    while (nk < budget) {
+        // the nearest candidate alive
+        uint32_t w = BOA_PAD;
+#pragma unroll
+        for (int h = 0; h < 4; ++h) {
+            const uint64_t m = __ballot(alive[h]);
+            if (w == BOA_PAD && m) {
+                const int l = __ffsll((unsigned long long)m) - 1;
+                w = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)key[h], l);
+                if (lane == l) alive[h] = false;
             }
         }
-        if (!dom) {
-            if (lane == 0) kept[nk] = cv;
-            ++nk;
-            wave_fence();
+        if (w == BOA_PAD) break;
+        if (lane == nk) mine = w;
+        ++nk;
+        if (nk == budget) break;
+#pragma unroll
+        for (int h = 0; h < 4; ++h) {
+            if (alive[h]) {
+                const uint32_t c = (uint32_t)key[h];
+                const float duv = __uint_as_float((uint32_t)(key[h] >> 32));
+                bool dom;
+                if (v.u8) {
+                    dom = alpha2 * dist_ids(v, w, c) <= duv;
+                } else {
+                    const float *X = reinterpret_cast<const float *>(v.vectors);
+                    dom = pair_within_f32(X + (size_t)w * v.d, X + (size_t)c * v.d, v.d, alpha2, duv);
+                }
+                if (dom) alive[h] = false;
+            }
         }
     }
-    for (int i = lane; i < R; i += 64) out_row[i] = i < nk ? kept[i] : BOA_PAD;
-    (void)u;
+    if (lane < R) out_row[lane] = mine;
 }
 
 __global__ void __launch_bounds__(256) prune_fwd_kernel(PruneArgs a)
 {
     __shared__ uint64_t keys_s[4][256];
-    __shared__ uint32_t kept_s[4][128];
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     const int64_t u = (int64_t)blockIdx.x * 4 + wid;
     if (u >= a.v.n) return;
     uint64_t *keys = keys_s[wid];
     // the candidates in (distance, id) order, with this pass's own distance
-    for (int i = lane; i < 256; i += 64) {
+    const uint32_t *cand = a.cand + ((size_t)blockIdx.y * a.v.n + u) * a.K;
+    const int N = a.K <= 128 ? 128 : 256;
+    for (int i = lane; i < N; i += 64) {
         uint64_t k = BKEY_NONE;
         if (i < a.K) {
-            const uint32_t c = a.cand[(size_t)u * a.K + i];
+            const uint32_t c = cand[i];
             if (c != BOA_PAD) k = bkey(dist_ids(a.v, (uint32_t)u, c), c);
         }
         keys[i] = k;
     }
     wave_fence();
-    bitonic256(keys, lane);
-    alpha_prune(a.v, (uint32_t)u, keys, min(a.K, 256), a.budget, a.alpha2, kept_s[wid], a.out + (size_t)u * a.R,
-                a.R, lane);
+    if (a.K <= 128) bitonic<128>(keys, lane);
+    else bitonic<256>(keys, lane);
+    alpha_prune(a.v, keys, min(a.K, 256), a.budget, a.alpha2, a.out + ((size_t)blockIdx.y * a.v.n + u) * a.R, a.R, lane);
 }
 
 // Re-prune each point's forward row together with its reverse neighbours
@@ -506,7 +719,6 @@ __global__ void __launch_bounds__(256) prune_union_kernel(PruneArgs a)
 {
     __shared__ uint64_t keys_s[4][256];
     __shared__ uint64_t buf_s[4][256];
-    __shared__ uint32_t kept_s[4][128];
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     const int64_t u = (int64_t)blockIdx.x * 4 + wid;
     if (u >= a.v.n) return;
@@ -522,7 +734,7 @@ __global__ void __launch_bounds__(256) prune_union_kernel(PruneArgs a)
         keys[i] = k;
     }
     wave_fence();
-    bitonic256(keys, lane);
+    bitonic<256>(keys, lane);
     // reverse neighbours not already forward ones, merged 128 at a time
     // into the 256 best (a row holds at most R <= 64 forward ids)
     const uint32_t r0 = a.rev_off[u], r1 = a.rev_off[u + 1];
@@ -547,12 +759,12 @@ __global__ void __launch_bounds__(256) prune_union_kernel(PruneArgs a)
         // the 256 best of keys[0,256) and the new 128: the first 128 of the
         // sorted keys stay; sort (keys[128..256) + new 128) and keep the best
         // 128 of those as the upper half
-        bitonic256(buf, lane);
+        bitonic<256>(buf, lane);
         for (int i = lane; i < 128; i += 64) keys[128 + i] = buf[i];
         wave_fence();
-        bitonic256(keys, lane);
+        bitonic<256>(keys, lane);
     }
-    alpha_prune(a.v, (uint32_t)u, keys, 256, a.budget, a.alpha2, kept_s[wid], a.out + (size_t)u * a.R, a.R, lane);
+    alpha_prune(a.v, keys, 256, a.budget, a.alpha2, a.out + (size_t)u * a.R, a.R, lane);
 }
 
 __global__ void count_in_kernel(const uint32_t *adj, int64_t n, int R, uint32_t *indeg)
@@ -572,6 +784,50 @@ __global__ void scatter_rev_kernel(const uint32_t *adj, int64_t n, int R, const 
     if (v == BOA_PAD) return;
     const uint32_t pos = atomicAdd(&cursor[v], 1u);
     rev[off[v] + pos] = (uint32_t)(i / R);
+}
+
+// 5. rows: the levels' edges appended to a point's row (one wave per point),
+// narrowest level first, without ids the row has, up to one free slot
+__global__ void __launch_bounds__(256) append_levels_kernel(uint32_t *adj, const uint32_t *level_rows, int64_t n, int R,
+                                                            int levels, int b_lvl, unsigned long long *added)
+{
+    __shared__ int sum[2][4];
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    const int64_t u = (int64_t)blockIdx.x * 4 + wid;
+    const bool in = u < n;
+    uint32_t v = in && lane < R ? adj[(size_t)u * R + lane] : BOA_PAD;
+    int cnt = __popcll(__ballot(v != BOA_PAD));   // (the ids fill a row's front)
+    const int cnt0 = cnt;
+    for (int l = 0; in && l < levels; ++l) {
+        const uint32_t e = lane < b_lvl ? level_rows[((size_t)l * n + u) * R + lane] : BOA_PAD;
+        for (int i = 0; i < b_lvl && cnt < R - 1; ++i) {
+            const uint32_t x = (uint32_t)__builtin_amdgcn_readlane((int)e, i);
+            if (x == BOA_PAD) break;
+            if (__ballot(v == x) != 0ull) continue;
+            if (lane == cnt) v = x;
+            ++cnt;
+        }
+    }
+    if (in && lane < R) adj[(size_t)u * R + lane] = v;
+    if (lane == 0) {
+        sum[0][wid] = cnt - cnt0;
+        sum[1][wid] = cnt;
+    }
+    __syncthreads();
+    if (threadIdx.x < 2)
+        atomicAdd(&added[threadIdx.x], (unsigned long long)(sum[threadIdx.x][0] + sum[threadIdx.x][1] +
+                                                            sum[threadIdx.x][2] + sum[threadIdx.x][3]));
+}
+
+// one step of a breadth-first search, one wave per frontier node
+__global__ void __launch_bounds__(256) bfs_kernel(const uint32_t *adj, int R, uint32_t *seen, const uint32_t *in,
+                                                  uint32_t n_in, uint32_t *out, uint32_t *n_out)
+{
+    const int lane = threadIdx.x & 63;
+    const uint32_t f = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (f >= n_in) return;
+    const uint32_t y = lane < R ? adj[(size_t)in[f] * R + lane] : BOA_PAD;
+    if (y != BOA_PAD && seen[y] == 0u && atomicExch(&seen[y], 1u) == 0u) out[atomicAdd(n_out, 1u)] = y;
 }
 
 // ---------------------------------------------------------------------------
@@ -640,89 +896,101 @@ hipError_t compute_medoid(const void *d_vectors, int64_t n, int32_t d, int vec_d
     return hipSuccess;
 }
 
-size_t knn_lds_bytes(int vec_dtype)
-{
-    const size_t lists = (size_t)KNN_WAVES * (KNN_ROWS_W * (KNN_LIST + KNN_BUF) + 256) * 8;
-    const size_t unit = vec_dtype == BOA_VEC_U8 ? 4 : 16;
-    return lists + (size_t)(KNN_KC / 4) * 64 * unit + (size_t)KNN_ROWS_B * (KNN_KC / 4) * unit;
-}
-
 namespace {
 
-// Quantile rank of every attribute cell within its column: the number of
-// strictly smaller values (equal values share a rank); float32 columns
-// compare as floats.
-std::vector<int32_t> column_ranks(const int32_t *attrs, int64_t n, int m, uint32_t f32_mask)
+hipError_t ranks_and_thresholds(const int32_t *h_attrs, int64_t n, int m, uint32_t f32_mask, const double *q, int levels,
+                                int32_t *ranks, int32_t *thr)
 {
-    std::vector<int32_t> rk((size_t)n * m);
-    std::vector<int64_t> ord((size_t)n);
-    for (int j = 0; j < m; ++j) {
-        const bool f = (f32_mask >> j) & 1u;
-        auto val = [&](int64_t i) -> double {
-            const int32_t c = attrs[(size_t)i * m + j];
-            if (!f) return (double)c;
-            float x;
-            std::memcpy(&x, &c, 4);
-            return (double)x;
-        };
-        for (int64_t i = 0; i < n; ++i) ord[i] = i;
-        std::sort(ord.begin(), ord.end(), [&](int64_t a, int64_t b) { return val(a) < val(b); });
-        int64_t r = 0;
-        for (int64_t t = 0; t < n; ++t) {
-            if (t > 0 && val(ord[t]) != val(ord[t - 1])) r = t;
-            rk[(size_t)ord[t] * m + j] = (int32_t)r;
-        }
-    }
-    return rk;
+    DevBuf attrs;
+    BTRY(attrs.alloc((size_t)n * m * 4));
+    BTRY(hipMemcpy(attrs.p, h_attrs, (size_t)n * m * 4, hipMemcpyHostToDevice));
+    hipLaunchKernelGGL(ranks_kernel, dim3((unsigned)((n + 255) / 256), (unsigned)m), dim3(256), 0, 0,
+                       attrs.as<int32_t>(), n, m, f32_mask, ranks);
+    BTRY(hipGetLastError());
+    DevBuf sample;
+    BTRY(sample.alloc((size_t)m * SAMPLE * 4));
+    hipLaunchKernelGGL(sample_kernel, dim3(SAMPLE / 256, (unsigned)m), dim3(256), 0, 0, ranks, n, sample.as<int32_t>());
+    BTRY(hipGetLastError());
+    ThresholdArgs ta{};
+    ta.ranks = ranks;
+    ta.sample = sample.as<int32_t>();
+    ta.n = n;
+    ta.m = m;
+    ta.levels = levels;
+    ta.thr = thr;
+    const int64_t S = std::min<int64_t>(SAMPLE, n);
+    for (int l = 0; l < levels; ++l)
+        ta.order[l] = (int32_t)std::max<int64_t>(0, (int64_t)std::ceil(q[l] * (double)S) - 1);
+    hipLaunchKernelGGL(thresholds_kernel, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, 0, ta);
+    BTRY(hipGetLastError());
+    return hipSuccess;   // (freeing the copy of the attributes waits for the kernels)
 }
 
-// Per point and level: the q-quantile of its attribute distance to an
-// evenly spaced sample of S points (ids floor(i n / S)).
-std::vector<int32_t> level_thresholds(const std::vector<int32_t> &rk, int64_t n, int m, const double *q, int levels)
+// Panels of rows: as many as the selection has waves resident (24 per CU of
+// 256), within 8 GB of distances. (Panels of 192 MB, which stay in the last
+// cache, leave the selection with under a tenth of its waves.)
+hipError_t find_candidates(const BuildView &v, const int32_t *norms_shifted, int K, int Kl, int levels, int m,
+                           const int32_t *ranks, const int32_t *thr, uint32_t *cand, uint32_t *lcand)
 {
-    const int64_t S = std::min<int64_t>(4096, n);
-    std::vector<int64_t> smp((size_t)S);
-    for (int64_t i = 0; i < S; ++i) smp[i] = (i * n) / S;
-    std::vector<int32_t> thr((size_t)levels * n);
-    auto work = [&](int64_t u0, int64_t u1) {
-        std::vector<int32_t> g((size_t)S);
-        for (int64_t u = u0; u < u1; ++u) {
-            for (int64_t i = 0; i < S; ++i) {
-                int32_t x = 0;
-                for (int j = 0; j < m; ++j) {
-                    const int32_t t = rk[(size_t)u * m + j] - rk[(size_t)smp[i] * m + j];
-                    x = std::max(x, t < 0 ? -t : t);
-                }
-                g[i] = x;
-            }
-            for (int l = 0; l < levels; ++l) {
-                const int64_t idx = std::max<int64_t>(0, (int64_t)std::ceil(q[l] * (double)S) - 1);
-                std::nth_element(g.begin(), g.begin() + idx, g.end());
-                thr[(size_t)l * n + u] = g[idx];
-            }
-        }
-    };
-    const int nt = (int)std::max<unsigned>(1u, std::min<unsigned>(16u, std::thread::hardware_concurrency()));
-    std::vector<std::thread> th;
-    for (int t = 0; t < nt; ++t) th.emplace_back(work, n * t / nt, n * (t + 1) / nt);
-    for (auto &x : th) x.join();
-    return thr;
+    const int64_t n = v.n, ld = (n + DT - 1) / DT * DT;
+    int64_t panel = std::min<int64_t>(24 * 256, ((int64_t)8 << 30) / (ld * 4) / DT * DT);
+    panel = std::min<int64_t>(std::max<int64_t>(panel, DT), ld);
+    DevBuf dist;
+    BTRY(dist.alloc((size_t)panel * ld * 4));
+    for (int64_t r0 = 0; r0 < n; r0 += panel) {
+        const int64_t rows = std::min<int64_t>(panel, n - r0);
+        const dim3 tiles((unsigned)(ld / DT), (unsigned)((rows + DT - 1) / DT));
+        if (v.u8)
+            hipLaunchKernelGGL(dist_u8_kernel, tiles, dim3(256), 0, 0, reinterpret_cast<const uint8_t *>(v.vectors),
+                               norms_shifted, n, v.d, r0, rows, ld, dist.as<float>());
+        else
+            hipLaunchKernelGGL(dist_f32_kernel, tiles, dim3(256), 0, 0, reinterpret_cast<const float *>(v.vectors), n,
+                               v.d, r0, rows, ld, dist.as<float>());
+        BTRY(hipGetLastError());
+        SelectArgs sa{};
+        sa.D = dist.as<float>();
+        sa.n = n;
+        sa.r0 = r0;
+        sa.rows = rows;
+        sa.ld = ld;
+        sa.K = K;
+        sa.Kl = Kl;
+        sa.levels = levels;
+        sa.m = m;
+        sa.ranks = ranks;
+        sa.thr = thr;
+        sa.cand = cand;
+        sa.lcand = lcand;
+        hipLaunchKernelGGL(select_kernel, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, 0, sa);
+        BTRY(hipGetLastError());
+    }
+    return hipSuccess;
 }
 
-hipError_t knn_launch(const KnnArgs &ka, int vec_dtype, int64_t n)
+// points a breadth-first search from `entry` reaches
+hipError_t count_reached(const uint32_t *adj, int64_t n, int R, uint32_t entry, int64_t *reached)
 {
-    const size_t lds = knn_lds_bytes(vec_dtype);
-    const unsigned blocks = (unsigned)((n + KNN_ROWS_B - 1) / KNN_ROWS_B);
-    if (vec_dtype == BOA_VEC_U8) {
-        BTRY(hipFuncSetAttribute(reinterpret_cast<const void *>(knn_kernel<true>),
-                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-        hipLaunchKernelGGL(knn_kernel<true>, dim3(blocks), dim3(256), lds, 0, ka);
-    } else {
-        BTRY(hipFuncSetAttribute(reinterpret_cast<const void *>(knn_kernel<false>),
-                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-        hipLaunchKernelGGL(knn_kernel<false>, dim3(blocks), dim3(256), lds, 0, ka);
+    DevBuf seen, list, count;
+    BTRY(seen.alloc((size_t)n * 4));
+    BTRY(list.alloc((size_t)n * 2 * 4));
+    BTRY(count.alloc(4));
+    BTRY(hipMemset(seen.p, 0, (size_t)n * 4));
+    const uint32_t one = 1;
+    BTRY(hipMemcpy(seen.as<uint32_t>() + entry, &one, 4, hipMemcpyHostToDevice));
+    BTRY(hipMemcpy(list.p, &entry, 4, hipMemcpyHostToDevice));
+    uint32_t *in = list.as<uint32_t>(), *out = in + n;
+    uint32_t n_in = 1;
+    *reached = 0;
+    while (n_in > 0) {   // (each point is listed once: at most n steps)
+        *reached += n_in;
+        BTRY(hipMemset(count.p, 0, 4));
+        hipLaunchKernelGGL(bfs_kernel, dim3((n_in + 3) / 4), dim3(256), 0, 0, adj, R, seen.as<uint32_t>(), in, n_in, out,
+                           count.as<uint32_t>());
+        BTRY(hipGetLastError());
+        BTRY(hipMemcpy(&n_in, count.p, 4, hipMemcpyDeviceToHost));
+        std::swap(in, out);
     }
-    return hipGetLastError();
+    return hipSuccess;
 }
 
 }  // namespace
@@ -740,11 +1008,13 @@ hipError_t build_graph(const void *d_vectors, int64_t n, int32_t d, int vec_dtyp
     const int b_lvl = std::max(1, R / 8);
     const int budget = std::max(1, R - 1 - levels * b_lvl);
     const int K = (int)std::min<int64_t>(std::min(2 * R, KNN_LIST), n - 1);
-    DevBuf norms;
+    DevBuf norms, norms2;
     BuildView v{d_vectors, nullptr, n, d, u8 ? 1 : 0};
     if (u8) {
         BTRY(norms.alloc((size_t)n * 4));
-        hipLaunchKernelGGL(norms_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, 0, v, norms.as<uint32_t>());
+        BTRY(norms2.alloc((size_t)n * 4));
+        hipLaunchKernelGGL(norms_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, 0, v, norms.as<uint32_t>(),
+                           norms2.as<int32_t>());
         BTRY(hipGetLastError());
         v.norms = norms.as<uint32_t>();
     }
@@ -752,16 +1022,23 @@ hipError_t build_graph(const void *d_vectors, int64_t n, int32_t d, int vec_dtyp
         BTRY(hipMemset(d_adj, 0xFF, (size_t)n * R * 4));
         return hipSuccess;
     }
-    // 2. candidates by vector distance
-    DevBuf cand, cand_d;
+    // 2. candidates by vector distance, for all attribute levels too (JAG
+    // threshold pruning, Sec. II "Graph construction": per level, the nearest
+    // vectors among the points within the point's attribute threshold, where
+    // the capped attribute distance is zero)
+    const int Kl = (int)std::min<int64_t>(std::min(4 * b_lvl, KNN_LEVEL_LIST), n - 1);
+    DevBuf cand, lcand, ranks, thr;
     BTRY(cand.alloc((size_t)n * K * 4));
-    BTRY(cand_d.alloc((size_t)n * K * 4));
-    {
-        KnnArgs ka{v, K, cand.as<uint32_t>(), cand_d.as<float>(), nullptr, nullptr, 0};
-        BTRY(knn_launch(ka, vec_dtype, n));
+    if (levels > 0) {
+        BTRY(ranks.alloc((size_t)n * m * 4));
+        BTRY(thr.alloc((size_t)n * levels * 4));
+        BTRY(lcand.alloc((size_t)n * Kl * levels * 4));
+        BTRY(ranks_and_thresholds(h_attrs, n, m, f32_mask, kLevelQ, levels, ranks.as<int32_t>(), thr.as<int32_t>()));
     }
+    BTRY(find_candidates(v, norms2.as<int32_t>(), K, Kl, levels, m, ranks.as<int32_t>(), thr.as<int32_t>(),
+                         cand.as<uint32_t>(), lcand.as<uint32_t>()));
     // 3. forward prune
-    DevBuf fwd;
+    DevBuf fwd, lrow;
     BTRY(fwd.alloc((size_t)n * R * 4));
     {
         PruneArgs pa{};
@@ -773,6 +1050,19 @@ hipError_t build_graph(const void *d_vectors, int64_t n, int32_t d, int vec_dtyp
         pa.alpha2 = alpha2;
         pa.out = fwd.as<uint32_t>();
         hipLaunchKernelGGL(prune_fwd_kernel, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, 0, pa);
+        BTRY(hipGetLastError());
+    }
+    if (levels > 0) {   // the levels' b_lvl edges per point
+        BTRY(lrow.alloc((size_t)n * R * levels * 4));
+        PruneArgs pa{};
+        pa.v = v;
+        pa.cand = lcand.as<uint32_t>();
+        pa.K = Kl;
+        pa.R = R;
+        pa.budget = b_lvl;
+        pa.alpha2 = alpha2;
+        pa.out = lrow.as<uint32_t>();
+        hipLaunchKernelGGL(prune_fwd_kernel, dim3((unsigned)((n + 3) / 4), (unsigned)levels), dim3(256), 0, 0, pa);
         BTRY(hipGetLastError());
     }
     // 4. reverse edges (CSR), then the union re-pruned
@@ -807,60 +1097,30 @@ hipError_t build_graph(const void *d_vectors, int64_t n, int32_t d, int vec_dtyp
         hipLaunchKernelGGL(prune_union_kernel, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, 0, pa);
         BTRY(hipGetLastError());
     }
+    // 5. the levels' edges appended to the rows
+    DevBuf added;
+    BTRY(added.alloc(16));
+    BTRY(hipMemset(added.p, 0, 16));
+    hipLaunchKernelGGL(append_levels_kernel, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, 0, d_adj, lrow.as<uint32_t>(), n,
+                       R, levels, b_lvl, added.as<unsigned long long>());
+    BTRY(hipGetLastError());
+    unsigned long long h_added[2] = {0, 0};
+    BTRY(hipMemcpy(h_added, added.p, 16, hipMemcpyDeviceToHost));
+    int64_t reached = 0;
+    BTRY(count_reached(d_adj, n, R, entry, &reached));
+    if (stats) {
+        stats->K = K;
+        stats->repaired = 0;
+        stats->repair_fallback = 0;
+        stats->attr_edges = (int64_t)h_added[0];
+        stats->edges = (int64_t)h_added[1];
+    }
+    if (reached == n) return hipSuccess;
     std::vector<uint32_t> adj((size_t)n * R), hc((size_t)n * K);
     BTRY(hipMemcpy(adj.data(), d_adj, adj.size() * 4, hipMemcpyDeviceToHost));
     BTRY(hipMemcpy(hc.data(), cand.p, hc.size() * 4, hipMemcpyDeviceToHost));
-    // 5. attribute-aware edges (JAG threshold pruning, Sec. II "Graph
-    // construction"): per level, the alpha-pruned nearest vectors among the
-    // points within the point's attribute threshold (where the capped
-    // attribute distance is zero), b_lvl edges each, appended to the row
-    int64_t attr_edges = 0;
-    if (levels > 0) {
-        const std::vector<int32_t> rk = column_ranks(h_attrs, n, m, f32_mask);
-        const std::vector<int32_t> thr = level_thresholds(rk, n, m, kLevelQ, levels);
-        const int Kl = (int)std::min<int64_t>(std::min(4 * b_lvl, KNN_LIST), n - 1);
-        DevBuf d_rk, d_thr, lc, lcd, lrow;
-        BTRY(d_rk.alloc(rk.size() * 4));
-        BTRY(d_thr.alloc((size_t)n * 4));
-        BTRY(lc.alloc((size_t)n * Kl * 4));
-        BTRY(lcd.alloc((size_t)n * Kl * 4));
-        BTRY(lrow.alloc((size_t)n * R * 4));
-        BTRY(hipMemcpy(d_rk.p, rk.data(), rk.size() * 4, hipMemcpyHostToDevice));
-        std::vector<uint32_t> hl((size_t)n * R);
-        for (int l = 0; l < levels; ++l) {
-            BTRY(hipMemcpy(d_thr.p, thr.data() + (size_t)l * n, (size_t)n * 4, hipMemcpyHostToDevice));
-            KnnArgs ka{v, Kl, lc.as<uint32_t>(), lcd.as<float>(), d_rk.as<int32_t>(), d_thr.as<int32_t>(), m};
-            BTRY(knn_launch(ka, vec_dtype, n));
-            PruneArgs pa{};
-            pa.v = v;
-            pa.cand = lc.as<uint32_t>();
-            pa.K = Kl;
-            pa.R = R;
-            pa.budget = b_lvl;
-            pa.alpha2 = alpha2;
-            pa.out = lrow.as<uint32_t>();
-            hipLaunchKernelGGL(prune_fwd_kernel, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, 0, pa);
-            BTRY(hipGetLastError());
-            BTRY(hipMemcpy(hl.data(), lrow.p, hl.size() * 4, hipMemcpyDeviceToHost));
-            for (int64_t u = 0; u < n; ++u) {
-                uint32_t *row = &adj[(size_t)u * R];
-                int cnt = 0;
-                while (cnt < R && row[cnt] != BOA_PAD) ++cnt;
-                for (int i = 0; i < b_lvl && cnt < R - 1; ++i) {
-                    const uint32_t x = hl[(size_t)u * R + i];
-                    if (x == BOA_PAD) break;
-                    bool dup = false;
-                    for (int t = 0; t < cnt; ++t) dup |= row[t] == x;
-                    if (!dup) {
-                        row[cnt++] = x;
-                        ++attr_edges;
-                    }
-                }
-            }
-        }
-    }
-    // 6. connectivity repair from s (host): breadth-first search, then each
-    // unreached point (ascending id) gets an in-edge from its nearest
+    // 6. connectivity repair from s (host, where the device's search found
+    // points out of reach): breadth-first search, then each unreached point (ascending id) gets an in-edge from its nearest
     // reached kNN candidate with a free slot; the search then continues
     // from it
     std::vector<uint8_t> seen((size_t)n, 0);
@@ -912,13 +1172,9 @@ hipError_t build_graph(const void *d_vectors, int64_t n, int32_t d, int vec_dtyp
     }
     BTRY(hipMemcpy(d_adj, adj.data(), adj.size() * 4, hipMemcpyHostToDevice));
     if (stats) {
-        stats->K = K;
         stats->repaired = repaired;
         stats->repair_fallback = fallback;
-        stats->attr_edges = attr_edges;
-        int64_t edges = 0;
-        for (uint32_t x : adj) edges += x != BOA_PAD;
-        stats->edges = edges;
+        stats->edges += repaired;
     }
     return hipSuccess;
 }
