@@ -485,6 +485,14 @@ uint32_t min_table_slots(const boa_index *ix)
     return std::max<uint32_t>(64u, B > 15 ? (8u << (B - 15)) : 64u);
 }
 
+// LDS of the scorer: its query copy, or a product-quantised search's table,
+// whose place then also holds the re-rank keys (Lb of them)
+int32_t scorer_lds(const boa_index *ix, int32_t Lb, bool wide, int pq_m)
+{
+    const int32_t b = scorer_lds_bytes(ix->vec_dtype, ix->view.d, wide, pq_m);
+    return pq_m ? std::max(b, 8 * Lb) : b;
+}
+
 PhasePlan plan_phase(const boa_index *ix, int32_t L, int32_t forced_h, int64_t max_active, bool wide = false,
                      int pq_m = 0)
 {
@@ -500,9 +508,7 @@ PhasePlan plan_phase(const boa_index *ix, int32_t L, int32_t forced_h, int64_t m
     h = std::max<uint32_t>(h, min_table_slots(ix));
     pl.h_slots = (int32_t)h;
     const int32_t Lb = beam_slots(L), pw = ((L >> 6) + 3) & ~1;
-    // (a product-quantised search also keeps its re-rank keys, Lb of them)
-    pl.lds_per_wave = 8 * Lb + 8 * 64 + 8 * pw + 4 * 64 + 4 * 64 +
-                      scorer_lds_bytes(ix->vec_dtype, ix->view.d, wide, pq_m) + (pq_m ? 8 * Lb : 0) + 2 * (int32_t)h;
+    pl.lds_per_wave = 8 * Lb + 8 * 64 + 8 * pw + 4 * 64 + 4 * 64 + scorer_lds(ix, Lb, wide, pq_m) + 2 * (int32_t)h;
     pl.lds_per_wave = (pl.lds_per_wave + 15) & ~15;
     // waves per block: the choice with the most resident waves per CU
     int best_w = 0, best_wpb = 1, best_occ = 1;
@@ -605,8 +611,7 @@ PhasePlan plan_bitmap(const boa_index *ix, int32_t L, int64_t S, int pq_m = 0)
     pl.h_slots = 0;
     const int64_t words = ((ix->view.n + 31) / 32 + 3) & ~(int64_t)3;
     const int32_t Lb = beam_slots(L), pw = ((L >> 6) + 3) & ~1;
-    const int64_t lds = 8 * Lb + 8 * 64 + 8 * pw + 4 * 64 + 4 * 64 + scorer_lds_bytes(ix->vec_dtype, ix->view.d, true, pq_m) +
-                        (pq_m ? 8 * Lb : 0) + 4 * words;
+    const int64_t lds = 8 * Lb + 8 * 64 + 8 * pw + 4 * 64 + 4 * 64 + scorer_lds(ix, Lb, true, pq_m) + 4 * words;
     pl.lds_per_wave = (int32_t)((lds + 15) & ~(int64_t)15);
     pl.wpb = 1;
     if ((size_t)pl.lds_per_wave > ix->lds_per_block_hw) return pl;   // capacity 0: not possible
@@ -647,10 +652,10 @@ struct TeamPlan {
 
 // Visited set of a team launch: the exact bitmap, or else the largest table,
 // with which all S queries are resident at once; else what holds most.
-TeamPlan plan_team(const boa_index *ix, int32_t L, int64_t S, int32_t forced_h)
+TeamPlan plan_team(const boa_index *ix, int32_t L, int64_t S, int32_t forced_h, int pq_m)
 {
     TeamPlan best;
-    const int sl = scorer_lds_bytes(ix->vec_dtype, ix->view.d, true, 0);
+    const int sl = scorer_lds(ix, beam_slots(L), true, pq_m);
     auto consider = [&](uint32_t words, int32_t h, int parts) -> bool {
         const size_t lds = team_lds_bytes(L, parts, words, sl);
         if (lds > ix->lds_per_block_hw) return false;
@@ -659,7 +664,7 @@ TeamPlan plan_team(const boa_index *ix, int32_t L, int64_t S, int32_t forced_h)
         pl.h_slots = h;
         pl.vis_words = words;
         pl.parts = parts;
-        pl.capacity = (int64_t)team_occupancy(ix->vec_dtype, ix->view.d, parts, lds) * ix->num_cu;
+        pl.capacity = (int64_t)team_occupancy(ix->vec_dtype, ix->view.d, parts, lds, pq_m) * ix->num_cu;
         pl.blocks = (int32_t)std::min<int64_t>(pl.capacity, std::max<int64_t>(S, 1));
         if (pl.capacity > best.capacity) best = pl;
         return pl.capacity > 0 && pl.capacity >= S;
@@ -672,7 +677,7 @@ TeamPlan plan_team(const boa_index *ix, int32_t L, int64_t S, int32_t forced_h)
     // queries at width 512, R = 64, d = 128 float32: 2.95 instead of 3.56 ms;
     // R = 16, d = 32: 0.51 instead of 0.49 ms.
     const size_t row = (size_t)ix->view.d * (ix->vec_dtype == BOA_VEC_U8 ? 1 : 4);
-    for (int parts = ix->view.R > 32 || row > 256 ? 2 : 1; parts >= 1; --parts) {
+    for (int parts = pq_m == 0 && (ix->view.R > 32 || row > 256) ? 2 : 1; parts >= 1; --parts) {
         if (forced_h > 0) {
             if (consider((uint32_t)forced_h / 2u, forced_h, parts)) break;
             continue;
@@ -756,7 +761,7 @@ int validate(const boa_index *ix, const void *queries, const int32_t *ranges, in
     rq.pq_m = p->pq ? ix->pq_m : 0;
     if (p->escalation_waves != 0 && p->escalation_waves != 1)
         return fail(BOA_EINVAL, "escalation_waves must be 0 or 1");
-    rq.team = p->escalation_waves == 0 && rq.pq_m == 0;
+    rq.team = p->escalation_waves == 0;
     rq.sub = rq.plus ? std::min<int64_t>(p->sub_batches, std::max<int64_t>(nq, 1)) : 1;
     rq.n_counters = rq.n_phases * (rq.sub + 1) + 8;
     rq.tau_count = (uint32_t)std::floor(p->tau * (double)nq);
@@ -786,7 +791,7 @@ int plan_search(const boa_index *ix, const Request &rq, int64_t nq, int32_t forc
         slots = std::max<uint64_t>(slots, (uint64_t)pl.blocks * pl.wpb);
         plans[ph] = pl;
         if (rq.team) {
-            teams[ph] = plan_team(ix, widest ? Lw : rq.sched[ph], nq, forced_h);
+            teams[ph] = plan_team(ix, widest ? Lw : rq.sched[ph], nq, forced_h, rq.pq_m);
             slots = std::max<uint64_t>(slots, (uint64_t)teams[ph].blocks);
         }
     }
@@ -1005,7 +1010,7 @@ int run_search(boa_index *ix, const void *queries, const int32_t *ranges, int64_
                 if (int rc2 = stage_profile_begin(&prof, pn, st)) return rc2;
                 e.prof = prof;
 #endif
-                const TeamPlan te = rq.team ? plan_team(ix, Lw, S, p->lds_hash_slots) : TeamPlan();
+                const TeamPlan te = rq.team ? plan_team(ix, Lw, S, p->lds_hash_slots, rq.pq_m) : TeamPlan();
                 if (int rc = launch(e, pe.blocks, st, true, 1, te, S, true, ws.slots)) return rc;
                 if (te.capacity > 0 && (int64_t)S <= te.capacity) {
                     pe.h_slots = te.h_slots;
@@ -1393,12 +1398,24 @@ extern "C" int boa_set_pq(boa_index *ix, const float *codebook, const uint8_t *c
     uint8_t *cc = nullptr;
     int rc;
     if ((rc = dalloc(&cb, (size_t)M * 16 * (d / M)))) return rc;
-    if ((rc = dalloc(&cc, (size_t)n * (M / 2)))) {
+    // rows of whole 16-byte chunks on the device (zero nibbles past the code)
+    const int32_t half = M / 2, row = pq_row_bytes(M);
+    std::vector<uint8_t> padded;
+    if (row != half) {
+        try {
+            padded.assign((size_t)n * row, 0);
+        } catch (...) {
+            dfree(cb);
+            return fail(BOA_ENOMEM, "host allocation failed");
+        }
+        for (int64_t i = 0; i < n; ++i) std::memcpy(&padded[(size_t)i * row], codes + (size_t)i * half, (size_t)half);
+    }
+    if ((rc = dalloc(&cc, (size_t)n * row))) {
         dfree(cb);
         return rc;
     }
     if (hipMemcpy(cb, codebook, (size_t)M * 16 * (d / M) * 4, hipMemcpyHostToDevice) != hipSuccess ||
-        hipMemcpy(cc, codes, (size_t)n * (M / 2), hipMemcpyHostToDevice) != hipSuccess) {
+        hipMemcpy(cc, row != half ? padded.data() : codes, (size_t)n * row, hipMemcpyHostToDevice) != hipSuccess) {
         dfree(cb);
         dfree(cc);
         return fail(BOA_EHIP, "upload of the product-quantisation data failed");

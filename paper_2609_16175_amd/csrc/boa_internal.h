@@ -27,6 +27,10 @@ __host__ __device__ inline int32_t beam_slots(int32_t L)
     return p;
 }
 
+// Bytes of a point's product-quantisation code in device memory: M / 2, padded
+// to whole 16-byte chunks.
+__host__ __device__ inline int32_t pq_row_bytes(int32_t M) { return (M / 2 + 15) & ~15; }
+
 // A float32 attribute cell as an order-preserving int32: for floats a, b
 // that are not NaN, a <= b exactly when f32_ord(a) <= f32_ord(b) (both zeros
 // map to 0, so -0 and +0 compare equal as floats do). NaN maps to INT32_MIN,
@@ -86,7 +90,7 @@ struct PhaseArgs {
     int32_t pq;               // traverse with product-quantised distances, re-rank exactly
     int32_t pq_m;             // subspaces (16 centroids each)
     const float *pq_cb;       // pq_m x 16 x d/pq_m
-    const uint8_t *pq_codes;  // n x pq_m/2, subspace 2b in the low nibble of byte b
+    const uint8_t *pq_codes;  // n x pq_row_bytes, subspace 2b in the low nibble of byte b
     int32_t vec_u8;           // the vectors are uint8 (the exact re-rank's arithmetic)
     int32_t L_alloc;          // widest of them: sizes the per-wave LDS
     int32_t h_log2;           // log2 of the LDS visited-table slots (16-bit entries)
@@ -156,12 +160,13 @@ int phase_occupancy(int vec_dtype, int d, int wpb, size_t lds, bool wide = false
 // per-wave LDS bytes the distance scorer keeps (its copy of the query, or
 // the product-quantisation distance table)
 int scorer_lds_bytes(int vec_dtype, int d, bool wide = false, int pq_m = 0);
-// The launch with a team of waves per query (exact distances): its LDS per
+// The launch with a team of waves per query: its LDS per
 // block, resident blocks per CU, and the launch (lds_per_wave carries the
 // block's LDS bytes; a block uses one wave slot).
-// parts: waves that share one node's row (1 or 2).
+// parts: waves that share one node's row (1 or 2; 1 with product
+// quantisation).
 size_t team_lds_bytes(int32_t L, int parts, uint32_t vis_words, int scorer_lds);
-int team_occupancy(int vec_dtype, int d, int parts, size_t lds);
+int team_occupancy(int vec_dtype, int d, int parts, size_t lds, int pq_m);
 hipError_t launch_team(const PhaseArgs &a, int vec_dtype, int parts, int blocks, hipStream_t st);
 hipError_t launch_compact(const CompactArgs &a, hipStream_t st);
 hipError_t launch_append(const AppendArgs &a, hipStream_t st);

@@ -417,11 +417,18 @@ struct U8Scorer {
 // in LDS; a 16-lane group scores one candidate, lane p adding the entries of
 // subspaces p, p+16, ... in increasing order (nibble (p + 16t) of the packed
 // code), then the same pairwise tree as the exact float32 distance.
+//
+// A code is read as 16-byte chunks (rows are padded to whole ones), chunk c by
+// lane c of the group, in one load per candidate and 32 candidates per round
+// trip; the nibbles then reach their lanes by row broadcasts, two per 16
+// subspaces. (A byte load per 16 subspaces and lane, eight candidates per
+// round trip, took 11,800 cycles of an expansion at M = 192.)
 template <int T>
 struct PQScorer {
     static constexpr bool kWide = false;
     static constexpr bool kSpec = false;
     static constexpr int kSpecMaxR = 0;
+    static constexpr int kTeamWaves = 4;
     struct RowGather {};
     __device__ __forceinline__ void gather_row(const void *, int, uint32_t, int, int, RowGather &) const {}
     __device__ __forceinline__ void score_row(const RowGather &, int, int, float *, int) const {}
@@ -430,27 +437,28 @@ struct PQScorer {
     float *lut = nullptr;
     const uint8_t *codes = nullptr;
     const float *cb = nullptr;
-    int M = 0, half = 0, ds = 0, u8 = 0;
+    int M = 0, row = 0, ds = 0, u8 = 0;
 
     __device__ __forceinline__ void bind_lds(void *buf) { lut = reinterpret_cast<float *>(buf); }
     __device__ __forceinline__ void bind_pq(const uint8_t *c, int m, const float *codebook, int d, int vec_u8)
     {
         codes = c;
         M = m;
-        half = m >> 1;
+        row = pq_row_bytes(m);
         cb = codebook;
         ds = d / m;
         u8 = vec_u8;
     }
 
-    // table entry (m, c): fma chain over the subspace's dimensions from +0
-    // (the caller's wave_sync orders these writes before the reads)
-    __device__ __forceinline__ void load_query(const void *Q, uint32_t qi, int d, int lane)
+    // table entry (m, c): fma chain over the subspace's dimensions from +0;
+    // zero past the M-th subspace, which adds nothing (the caller orders
+    // these writes before the reads). Entries first, first + step, ...
+    __device__ __forceinline__ void load_table(const void *Q, uint32_t qi, int d, int first, int step)
     {
-        for (int e = lane; e < M * 16; e += 64) {
+        for (int e = first; e < 16 * T * 16; e += step) {
             const int m = e >> 4, c = e & 15;
             float acc = 0.0f;
-            for (int j = 0; j < ds; ++j) {
+            for (int j = 0; m < M && j < ds; ++j) {
                 const size_t qo = (size_t)qi * d + m * ds + j;
                 const float qv = u8 ? (float)reinterpret_cast<const uint8_t *>(Q)[qo]
                                     : reinterpret_cast<const float *>(Q)[qo];
@@ -460,8 +468,12 @@ struct PQScorer {
             lut[e] = acc;
         }
     }
+    __device__ __forceinline__ void load_query(const void *Q, uint32_t qi, int d, int lane)
+    {
+        load_table(Q, qi, d, lane, 64);
+    }
 
-    static constexpr int RU = T <= 4 ? 4 : 2;   // rounds of 4 candidates per round trip
+    static constexpr int RU = 8;   // rounds of 4 candidates per round trip
     struct Ids {
         uint32_t v[RU];
     };
@@ -476,34 +488,40 @@ struct PQScorer {
         }
     }
 
+    // the t-th term of the lane's sum: dword 2 t + (p >> 3) of the code holds
+    // its nibble, in chunk t / 2
+    template <int TT>
+    __device__ __forceinline__ void add_terms(const uint4 &x, const float *mine, int shift, float &acc) const
+    {
+        if constexpr (TT < T) {
+            const uint32_t lo = (TT & 1) ? x.z : x.x, hi = (TT & 1) ? x.w : x.y;
+            int w = __builtin_amdgcn_update_dpp(0, (int)lo, 0x150 + TT / 2, 0xF, 0xF, false);   // row_newbcast
+            w = __builtin_amdgcn_update_dpp(w, (int)hi, 0x150 + TT / 2, 0xF, 0xC, false);       // (lanes 8-15)
+            acc = acc + mine[TT * 256 + (((uint32_t)w >> shift) & 15u)];
+            add_terms<TT + 1>(x, mine, shift, acc);
+        }
+    }
+
     __device__ __forceinline__ void score(const void *, int, const uint32_t *cid, int c, float *cd, int lane,
                                           const Ids &first)
     {
         const int g = lane >> 4, p = lane & 15;
+        const float *mine = lut + p * 16;
+        const int shift = 4 * (p & 7);
+        const int chunk = 16 * min(p, (row >> 4) - 1);
         for (int r0 = 0; r0 < c; r0 += 4 * RU) {
             Ids ids = first;
             if (r0 > 0) read_ids(cid, c, r0, lane, ids);
-            uint32_t b[RU][T];
+            uint4 x[RU];
 #pragma unroll
-            for (int u = 0; u < RU; ++u) {
-                if (r0 + 4 * u < c) {   // uniform
-                    const uint8_t *row = codes + (size_t)ids.v[u] * half;
-#pragma unroll
-                    for (int t = 0; t < T; ++t) {
-                        const int m = p + 16 * t;
-                        b[u][t] = row[(m < M ? m : M - 1) >> 1];   // a valid byte; masked below
-                    }
-                }
-            }
+            for (int u = 0; u < RU; ++u)
+                if (r0 + 4 * u < c)   // uniform
+                    x[u] = *reinterpret_cast<const uint4 *>(codes + (size_t)ids.v[u] * row + chunk);
 #pragma unroll
             for (int u = 0; u < RU; ++u) {
                 if (r0 + 4 * u >= c) break;   // uniform
                 float acc = 0.0f;
-#pragma unroll
-                for (int t = 0; t < T; ++t) {
-                    const int m = p + 16 * t;
-                    if (m < M) acc = acc + lut[m * 16 + ((b[u][t] >> (4 * (m & 1))) & 15u)];
-                }
+                add_terms<0>(x[u], mine, shift, acc);
                 acc = acc + from_lane_minus_f<8>(acc);
                 acc = acc + from_lane_minus_f<4>(acc);
                 acc = acc + from_lane_minus_f<2>(acc);
@@ -515,57 +533,82 @@ struct PQScorer {
     }
 };
 
-// Exact squared distance of one point to the query, computed by one lane in
-// the fixed order of the float32 path (16 partials over 4-dimension chunks,
-// then pairwise), or exactly in int32 for uint8 vectors: the re-rank of a
-// product-quantised search.
-__device__ __forceinline__ float exact_dist_lane(const void *V, const void *Q, uint32_t qi, uint32_t id, int d,
-                                                 bool u8)
+// The re-rank of a product-quantised search: keys (exact distance bits, id) of
+// the worklist's first n entries, by 16-lane groups in the fixed order of the
+// float32 path (lane p: chunks p, p+16, ..., then pairwise), or exactly in
+// int32 for uint8 vectors; 16 entries at a time, each row read in whole lines.
+__device__ __forceinline__ void exact_keys(const PhaseArgs &a, uint32_t qi, const uint64_t *beam, uint32_t n,
+                                           uint64_t *out, int lane)
 {
-    if (u8) {
-        const uint4 *x = reinterpret_cast<const uint4 *>(reinterpret_cast<const uint8_t *>(V) + (size_t)id * d);
-        const uint4 *q = reinterpret_cast<const uint4 *>(reinterpret_cast<const uint8_t *>(Q) + (size_t)qi * d);
-        int32_t s = 0;
-        for (int c = 0; c < (d >> 4); ++c) {
-            const uint4 a = x[c], b = q[c];
-            const uint32_t wa[4] = {a.x, a.y, a.z, a.w}, wb[4] = {b.x, b.y, b.z, b.w};
+    const int d = a.ix.d, g = lane >> 4, p = lane & 15;
+    constexpr int RU = 4;
+    for (uint32_t e0 = 0; e0 < n; e0 += 4 * RU) {
+        uint32_t id[RU];
 #pragma unroll
-            for (int w = 0; w < 4; ++w)
+        for (int u = 0; u < RU; ++u) id[u] = key_id(beam[min(e0 + 4u * u + (uint32_t)g, n - 1u)]);
+        float dist[RU];
+        if (a.vec_u8) {
+            const uint8_t *V = reinterpret_cast<const uint8_t *>(a.ix.vectors);
+            const uint4 *q4 = reinterpret_cast<const uint4 *>(reinterpret_cast<const uint8_t *>(a.queries) + (size_t)qi * d);
+            const int nch = d >> 4;
+            uint32_t acc[RU] = {};
+            for (int c0 = 0; c0 < nch; c0 += 16) {
+                const int c = min(c0 + p, nch - 1);
+                const uint4 qv = q4[c];
+                const uint32_t qq = U8Scorer<1>::dot16(qv, qv);
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int32_t t = (int32_t)((wa[w] >> (8 * i)) & 0xFF) - (int32_t)((wb[w] >> (8 * i)) & 0xFF);
-                    s += t * t;
+                for (int u = 0; u < RU; ++u) {
+                    const uint4 x = reinterpret_cast<const uint4 *>(V + (size_t)id[u] * d)[c];
+                    const uint32_t t = U8Scorer<1>::dot16(x, x) + qq - 2u * U8Scorer<1>::dot16(x, qv);
+                    acc[u] += c0 + p < nch ? t : 0u;
                 }
-        }
-        return (float)s;
-    }
-    const float4 *x = reinterpret_cast<const float4 *>(reinterpret_cast<const float *>(V) + (size_t)id * d);
-    const float4 *q = reinterpret_cast<const float4 *>(reinterpret_cast<const float *>(Q) + (size_t)qi * d);
-    const int nch = d >> 2;
-    float acc[16];
+            }
 #pragma unroll
-    for (int pp = 0; pp < 16; ++pp) acc[pp] = 0.0f;
-    for (int c0 = 0; c0 < nch; c0 += 16) {
+            for (int u = 0; u < RU; ++u) {
+                acc[u] += from_lane_minus<8>(acc[u]);
+                acc[u] += from_lane_minus<4>(acc[u]);
+                acc[u] += from_lane_minus<2>(acc[u]);
+                acc[u] += from_lane_minus<1>(acc[u]);
+                dist[u] = (float)(int32_t)acc[u];
+            }
+        } else {
+            const float *V = reinterpret_cast<const float *>(a.ix.vectors);
+            const float4 *q4 = reinterpret_cast<const float4 *>(reinterpret_cast<const float *>(a.queries) + (size_t)qi * d);
+            const int nch = d >> 2;
+            float acc[RU] = {};
+#pragma unroll 2
+            for (int c0 = 0; c0 < nch; c0 += 16) {
+                const int c = min(c0 + p, nch - 1);
+                const float4 qv = q4[c];
 #pragma unroll
-        for (int pp = 0; pp < 16; ++pp) {
-            if (c0 + pp < nch) {
-                const float4 a = x[c0 + pp], b = q[c0 + pp];
-                float t = a.x - b.x;
-                acc[pp] = __builtin_fmaf(t, t, acc[pp]);
-                t = a.y - b.y;
-                acc[pp] = __builtin_fmaf(t, t, acc[pp]);
-                t = a.z - b.z;
-                acc[pp] = __builtin_fmaf(t, t, acc[pp]);
-                t = a.w - b.w;
-                acc[pp] = __builtin_fmaf(t, t, acc[pp]);
+                for (int u = 0; u < RU; ++u) {
+                    float4 x = reinterpret_cast<const float4 *>(V + (size_t)id[u] * d)[c];
+                    if (c0 + p >= nch) x = qv;   // past the row end: adds zero
+                    float t = x.x - qv.x;
+                    acc[u] = __builtin_fmaf(t, t, acc[u]);
+                    t = x.y - qv.y;
+                    acc[u] = __builtin_fmaf(t, t, acc[u]);
+                    t = x.z - qv.z;
+                    acc[u] = __builtin_fmaf(t, t, acc[u]);
+                    t = x.w - qv.w;
+                    acc[u] = __builtin_fmaf(t, t, acc[u]);
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < RU; ++u) {
+                acc[u] = acc[u] + from_lane_minus_f<8>(acc[u]);
+                acc[u] = acc[u] + from_lane_minus_f<4>(acc[u]);
+                acc[u] = acc[u] + from_lane_minus_f<2>(acc[u]);
+                acc[u] = acc[u] + from_lane_minus_f<1>(acc[u]);
+                dist[u] = acc[u];
             }
         }
+#pragma unroll
+        for (int u = 0; u < RU; ++u) {
+            const uint32_t e = e0 + 4u * u + (uint32_t)g;
+            if (p == 15 && e < n) out[e] = ((uint64_t)__float_as_uint(dist[u]) << 32) | id[u];
+        }
     }
-#pragma unroll
-    for (int st = 8; st >= 1; st >>= 1)
-#pragma unroll
-        for (int pp = 0; pp < st; ++pp) acc[pp] = acc[pp] + acc[pp + st];
-    return acc[0];
 }
 
 __device__ __forceinline__ uint64_t wave_min64(uint64_t v)
@@ -1199,6 +1242,67 @@ __device__ __forceinline__ bool end_phase(const PhaseArgs &a, int lane, int p, u
     return last;
 }
 
+// What the end of a phase reads of its worklist: the number of valid entries,
+// the squared distances of the k-th and of the last, and the entries (lane q
+// mod 64 holds the q-th of a re-ranked list).
+template <class Scorer>
+struct PhaseResult {
+    uint32_t n_valid;
+    float d_k, d_max;
+    uint64_t key[2];
+    const uint64_t *beam;
+
+    // rrk: LDS for the exact keys of a product-quantised search (its distance
+    // table's place: the table is loaded again if another phase follows)
+    __device__ __forceinline__ void read(const PhaseArgs &a, const WaveList &wl, uint32_t qi, uint64_t *rrk, int lane)
+    {
+        beam = wl.beam;
+        n_valid = bcast0(lower_bound64(beam, min(wl.len, wl.L), KEY_PHI1));
+        const int k = a.k;
+        d_k = d_max = 0.f;
+        key[0] = key[1] = KEY_NONE;
+        if constexpr (Scorer::kPQ) {
+            // re-rank the valid entries by exact distance (Sec. III-B step 8):
+            // keys (exact distance bits, id); the k smallest in order by k
+            // rounds of a wave minimum, the largest by one wave maximum
+            exact_keys(a, qi, beam, n_valid, rrk, lane);
+            wave_sync();
+            uint64_t prev = 0, mx = 0;
+            for (uint32_t i = lane; i < n_valid; i += 64) mx = max(mx, rrk[i]);
+            mx = ~wave_min64(~mx);
+            const int kk = min(k, (int)n_valid);
+            for (int q = 0; q < kk; ++q) {
+                uint64_t mn = KEY_NONE;
+                for (uint32_t i = lane; i < n_valid; i += 64) {
+                    const uint64_t x = rrk[i];
+                    if ((q == 0 || x > prev) && x < mn) mn = x;
+                }
+                mn = wave_min64(mn);
+                if (q == lane) key[0] = mn;
+                if (q == lane + 64) key[1] = mn;
+                prev = mn;
+            }
+            if (kk > 0) d_k = __uint_as_float((uint32_t)(prev >> 32));
+            d_max = __uint_as_float((uint32_t)(mx >> 32));
+        } else if (n_valid > (uint32_t)k) {
+            d_k = key_dist(beam[k - 1]);
+            d_max = key_dist(beam[n_valid - 1]);
+        }
+    }
+    __device__ __forceinline__ void entry(int q, uint32_t &id, float &dd) const
+    {
+        if constexpr (Scorer::kPQ) {
+            const uint64_t kk = q < 64 ? key[0] : key[1];
+            id = (uint32_t)kk;
+            dd = __uint_as_float((uint32_t)(kk >> 32));
+        } else {
+            const uint64_t kk = beam[q];
+            id = key_id(kk);
+            dd = key_dist(kk);
+        }
+    }
+};
+
 template <class Scorer>
 __global__ void __launch_bounds__(256) phase_kernel(PhaseArgs a)
 {
@@ -1219,9 +1323,11 @@ __global__ void __launch_bounds__(256) phase_kernel(PhaseArgs a)
     uint32_t *cid = reinterpret_cast<uint32_t *>(posbm + pw);   // 64
     float *cd = reinterpret_cast<float *>(cid + 64);             // 64
     unsigned char *qlds = reinterpret_cast<unsigned char *>(cd + 64);   // the scorer's query copy or table
-    // the exact re-rank keys of a product-quantised search (Lb entries)
-    uint64_t *rrk = reinterpret_cast<uint64_t *>(qlds + Scorer::kLdsBytes);
-    uint32_t *htab = reinterpret_cast<uint32_t *>(rrk + (Scorer::kPQ ? Lb : 0));   // H/2 words (H 16-bit slots)
+    // the exact re-rank keys of a product-quantised search (Lb entries), over
+    // its table, which the re-rank does not need
+    uint64_t *rrk = reinterpret_cast<uint64_t *>(qlds);
+    uint32_t *htab = reinterpret_cast<uint32_t *>(
+        qlds + (Scorer::kPQ ? max(Scorer::kLdsBytes, 8 * Lb) : Scorer::kLdsBytes));   // H/2 words (H 16-bit slots)
 
     const IndexView ix = a.ix;
     int R = ix.R;   // (made opaque once per expansion, see there)
@@ -1420,64 +1526,19 @@ __global__ void __launch_bounds__(256) phase_kernel(PhaseArgs a)
             PROF_T(t_sc1);
             PROF_ADD(2, t_sc1 - t_vis1);
         }
-        const uint32_t len = wl.len;
 
         // ---- epilogue: confidence (Eq. 3) over the phase's worklist (its
         // first L entries); the result is written by the last phase the
         // query runs in this launch
         wave_sync();
         const PhaseArgs &ae = cold_args();
-        const uint32_t n_valid = bcast0(lower_bound64(beam, min(len, (uint32_t)L), KEY_PHI1));
-        const int k = ae.k;
-        // the result (the first valid entries) and the two distances of Eq. 3
-        uint64_t res_key[2] = {KEY_NONE, KEY_NONE};   // (product-quantised search: lanes' top-k keys)
-        float d_k = 0.f, d_max = 0.f;
-        if constexpr (Scorer::kPQ) {
-            // re-rank the valid entries by exact distance (Sec. III-B step 8):
-            // keys (exact distance bits, id); the k smallest in order by k
-            // rounds of a wave minimum, the largest by one wave maximum
-            for (uint32_t b0 = 0; b0 < n_valid; b0 += 64) {
-                const uint32_t e = b0 + lane;
-                if (e < n_valid) {
-                    const uint32_t id = key_id(beam[e]);
-                    const float dx = exact_dist_lane(ae.ix.vectors, ae.queries, qi, id, d, ae.vec_u8 != 0);
-                    rrk[e] = ((uint64_t)__float_as_uint(dx) << 32) | id;
-                }
-            }
-            wave_sync();
-            uint64_t prev = 0, mx = 0;
-            for (uint32_t i = lane; i < n_valid; i += 64) mx = max(mx, rrk[i]);
-            mx = ~wave_min64(~mx);
-            const int kk = min(k, (int)n_valid);
-            for (int q = 0; q < kk; ++q) {
-                uint64_t mn = KEY_NONE;
-                for (uint32_t i = lane; i < n_valid; i += 64) {
-                    const uint64_t x = rrk[i];
-                    if ((q == 0 || x > prev) && x < mn) mn = x;
-                }
-                mn = wave_min64(mn);
-                if ((q & 63) == lane) res_key[q >> 6] = mn;
-                prev = mn;
-            }
-            if (kk > 0) d_k = __uint_as_float((uint32_t)(prev >> 32));
-            d_max = __uint_as_float((uint32_t)(mx >> 32));
-        } else if (n_valid > (uint32_t)k) {
-            d_k = key_dist(beam[k - 1]);
-            d_max = key_dist(beam[n_valid - 1]);
-        }
-        const bool last = end_phase(ae, lane, p, qi, t, L, n_valid, d_k, d_max, E, S, vs.spill, [&](int q, uint32_t &id, float &dd) {
-            if constexpr (Scorer::kPQ) {
-                const uint64_t kk = res_key[q >> 6];
-                id = (uint32_t)kk;
-                dd = __uint_as_float((uint32_t)(kk >> 32));
-            } else {
-                const uint64_t kk = beam[q];
-                id = key_id(kk);
-                dd = key_dist(kk);
-            }
-        });
+        PhaseResult<Scorer> res;
+        res.read(ae, wl, qi, rrk, lane);
+        const bool last = end_phase(ae, lane, p, qi, t, L, res.n_valid, res.d_k, res.d_max, E, S, vs.spill,
+                                    [&](int q, uint32_t &id, float &dd) { res.entry(q, id, dd); });
         wave_sync();
         if (last) break;
+        if constexpr (Scorer::kPQ) sc.load_query(ae.queries, qi, d, lane);
         }   // phases
     }       // queries
     vs.close(lane);
@@ -1535,8 +1596,8 @@ struct TeamWave {        // one helper
 // P helpers share a node: part q takes the row's slice of W = ceil(R / P)
 // entries from q W on, and answers in the same entries of the group's keys.
 template <class Scorer, int P>
-__device__ __forceinline__ void team_helper(const PhaseArgs &a, TeamWave *me, uint64_t *group_keys, int part,
-                                            const VisitSet &vs, unsigned char *qlds, int lane)
+__device__ __forceinline__ void team_helper(const PhaseArgs &a, TeamWave *me, int helper, uint64_t *group_keys,
+                                            int part, const VisitSet &vs, unsigned char *qlds, int lane)
 {
     const IndexView ix = a.ix;
     const int d = ix.d;
@@ -1549,6 +1610,7 @@ __device__ __forceinline__ void team_helper(const PhaseArgs &a, TeamWave *me, ui
     };
     Scorer sc;
     sc.bind_lds(qlds);
+    if constexpr (Scorer::kPQ) sc.bind_pq(a.pq_codes, a.pq_m, a.pq_cb, d, a.vec_u8);
     RangeTest rt;
     uint32_t *cid = me->cid;
     float *cd = me->cd;
@@ -1570,7 +1632,11 @@ __device__ __forceinline__ void team_helper(const PhaseArgs &a, TeamWave *me, ui
         if (kind == TEAM_EXIT) return;
         if (kind == TEAM_QUERY) {
             const PhaseArgs &aq = cold_args();
-            sc.load_query(aq.queries, what, d, lane);
+            // (the helpers share a table; each has its own copy of a query)
+            if constexpr (Scorer::kPQ)
+                sc.load_table(aq.queries, what, d, lane + 64 * helper, 64 * TEAM_GROUPS * P);
+            else
+                sc.load_query(aq.queries, what, d, lane);
             rt.set(aq.ranges, what, aq.ix.m, aq.ix.f32_mask);
         } else {
             uint64_t key = KEY_NONE;
@@ -1641,7 +1707,8 @@ __global__ void __launch_bounds__(64 * (1 + TEAM_GROUPS * P), Scorer::kTeamWaves
     uint64_t *keys = posbm + pw;                                    // 64 per group
     TeamWave *wv = reinterpret_cast<TeamWave *>(keys + 64 * TEAM_GROUPS);   // one per helper
     unsigned char *qlds = reinterpret_cast<unsigned char *>(wv + TEAM_GROUPS * P);
-    uint32_t *vis = reinterpret_cast<uint32_t *>(qlds + Scorer::kLdsBytes);
+    uint32_t *vis = reinterpret_cast<uint32_t *>(
+        qlds + (Scorer::kPQ ? max(Scorer::kLdsBytes, 8 * Lb) : Scorer::kLdsBytes));
 
     const uint32_t n_in = bcast0(*a.n_active);
     // (the same for every wave of the block)
@@ -1657,7 +1724,7 @@ __global__ void __launch_bounds__(64 * (1 + TEAM_GROUPS * P), Scorer::kTeamWaves
     __syncthreads();
     if (wid > 0) {
         const int h = (wid - 1) / P;
-        team_helper<Scorer, P>(a, wv + (wid - 1), keys + 64 * h, (wid - 1) - h * P, vs, qlds, lane);
+        team_helper<Scorer, P>(a, wv + (wid - 1), wid - 1, keys + 64 * h, (wid - 1) - h * P, vs, qlds, lane);
         return;
     }
     __builtin_amdgcn_s_setprio(2);   // the helpers wait for this wave
@@ -1818,18 +1885,15 @@ __global__ void __launch_bounds__(64 * (1 + TEAM_GROUPS * P), Scorer::kTeamWaves
             }
             // ---- end of the phase
             const PhaseArgs &ae = cold_args();
-            const uint32_t n_valid = bcast0(lower_bound64(beam, min(wl.len, (uint32_t)L), KEY_PHI1));
-            float d_k = 0.f, d_max = 0.f;
-            if (n_valid > (uint32_t)ae.k) {
-                d_k = key_dist(beam[ae.k - 1]);
-                d_max = key_dist(beam[n_valid - 1]);
+            if constexpr (Scorer::kPQ) wait_for(ALL);   // (the table's place is about to be used)
+            PhaseResult<Scorer> res;
+            res.read(ae, wl, qi, reinterpret_cast<uint64_t *>(qlds), lane);
+            const bool last = end_phase(ae, lane, p, qi, t, L, res.n_valid, res.d_k, res.d_max, E, S, vs.spill,
+                                        [&](int q, uint32_t &id, float &dd) { res.entry(q, id, dd); });
+            if constexpr (Scorer::kPQ) {
+                if (!last)
+                    for (int h = 0; h < TEAM_GROUPS; ++h) order(h, TEAM_QUERY, qi);
             }
-            const bool last = end_phase(ae, lane, p, qi, t, L, n_valid, d_k, d_max, E, S, vs.spill,
-                                        [&](int q, uint32_t &id, float &dd) {
-                                            const uint64_t kk = beam[q];
-                                            id = key_id(kk);
-                                            dd = key_dist(kk);
-                                        });
             wave_sync();
             if (last) break;
         }   // phases
@@ -2011,15 +2075,17 @@ static int team_occupancy_t(size_t lds)
 hipError_t launch_team(const PhaseArgs &a, int vec_dtype, int parts, int blocks, hipStream_t st)
 {
     hipError_t e = hipSuccess;
-    if (parts == 2) BOA_DISPATCH_W(vec_dtype, a.ix.d, 3, e = (launch_team_t<S_, 2>(a, blocks, st)));
+    if (a.pq) BOA_DISPATCH_PQ(a.pq_m, e = (launch_team_t<S_, 1>(a, blocks, st)));
+    else if (parts == 2) BOA_DISPATCH_W(vec_dtype, a.ix.d, 3, e = (launch_team_t<S_, 2>(a, blocks, st)));
     else BOA_DISPATCH_W(vec_dtype, a.ix.d, 3, e = (launch_team_t<S_, 1>(a, blocks, st)));
     return e;
 }
 
-int team_occupancy(int vec_dtype, int d, int parts, size_t lds)
+int team_occupancy(int vec_dtype, int d, int parts, size_t lds, int pq_m)
 {
     int r = 0;
-    if (parts == 2) BOA_DISPATCH_W(vec_dtype, d, 3, r = (team_occupancy_t<S_, 2>(lds)));
+    if (pq_m > 0) BOA_DISPATCH_PQ(pq_m, r = (team_occupancy_t<S_, 1>(lds)));
+    else if (parts == 2) BOA_DISPATCH_W(vec_dtype, d, 3, r = (team_occupancy_t<S_, 2>(lds)));
     else BOA_DISPATCH_W(vec_dtype, d, 3, r = (team_occupancy_t<S_, 1>(lds)));
     return r;
 }

@@ -38,3 +38,26 @@ def test_team_equals_one_wave_and_oracle(dtype, d, R, m):
                     got = gpu_search(ix, q, r, escalation_waves=waves, lds_hash_slots=slots, **par)
                     assert_parity(got, ref, f"{name} nq={nq} escalation_waves={waves} slots={slots}")
     ix.close()
+
+
+@pytest.mark.parametrize("dtype,d,R,M", [("f32", 36, 40, 18), ("f32", 96, 64, 32), ("u8", 272, 16, 34),
+                                         ("f32", 768, 48, 192), ("f32", 512, 33, 256)])
+def test_pq_team_equals_one_wave_and_oracle(dtype, d, R, M):
+    """Product-quantised search: codes that end inside, at and past a 16-byte
+    chunk, widths whose re-rank keys need more room than the distance table."""
+    import paper_2609_16175_amd as boa
+    from workloads import pq
+    x, attrs, types, adj, entry = random_arrays(n=2000, d=d, m=2, R=R, dtype=dtype, seed=9)
+    cb = pq.train(x, M, seed=2, sample=1000, iters=3)
+    codes = pq.encode(x, cb)
+    ref_ix = oracle.Index(x, attrs, types, adj, entry, cb, codes)
+    ix = boa.Index(x, attrs, types, adj, entry)
+    ix.set_pq(cb, codes)
+    for nq in (3, 1500):
+        q, r = random_queries(ref_ix, nq, 60, nq)
+        for mode, ref in (({"fused": True}, oracle.boa(ref_ix, q, r, 5, [8, 40, 600], 0.02, threads=8)),
+                          ({"fused": True, "warm": True}, oracle.boa_warm(ref_ix, q, r, 5, [8, 40, 600], 0.02))):
+            for waves in (0, 1):
+                got = gpu_search(ix, q, r, k=5, eps=0.02, schedule=[8, 40, 600], pq=True, escalation_waves=waves, **mode)
+                assert_parity(got, ref, f"pq M={M} {mode} nq={nq} escalation_waves={waves}")
+    ix.close()
