@@ -153,7 +153,9 @@ typedef struct {
                                waves get the largest visited table that still lets all
                                survivors run at once (identical results; needs
                                tau == 0). 0: one launch per phase with device-side
-                               compaction between them. */
+                               compaction between them. Where all queries are resident
+                               at once as teams (escalation_waves), 0 (with tau * nq
+                               below 1) and 2 run every phase in one launch as 1 does. */
     int32_t warm_start;     /* 1: warm-start escalation (Sec. III-A "Redundancy
                                Avoidance"): during a phase of width L the sorted list
                                keeps up to the next phase's width, only its first L
@@ -230,7 +232,8 @@ typedef struct {
     int32_t L;              /* phase beamwidth */
     int32_t active;         /* queries searched in the phase */
     int32_t confident;      /* of which resolved by the confidence test */
-    int32_t launches;       /* kernel launches of the phase (BOA+: sub-batches) */
+    int32_t launches;       /* kernel launches of the phase (BOA+: sub-batches); where 0 and 2
+                               run in one launch: 1 for every phase that had queries */
     int64_t expansions;     /* nodes expanded, summed over the phase's queries */
     int64_t scored;         /* nodes scored (distance + predicates) */
     double gathered_bytes;  /* algorithmic bytes the phase had to read */

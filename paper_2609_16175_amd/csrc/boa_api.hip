@@ -140,6 +140,17 @@ struct boa_index {
     double cum_kernel_ms = 0.0;
     int64_t cum_phase_launches[BOA_MAX_PHASES] = {};
     double cum_phase_kernel_ms[BOA_MAX_PHASES] = {};
+    hipEvent_t ev_last = nullptr;    // end of the last search (one of the above)
+    uint32_t *h_back = nullptr;      // pinned: the words a search reads back
+
+    // Resident blocks per CU by launch shape, as the runtime reported them: a
+    // search asks 15 to 60 times while it plans, 1 us each. Direct-mapped by
+    // the shape (an index serves one search at a time).
+    struct Occupancy {
+        uint64_t shape;
+        int32_t blocks;
+    };
+    mutable Occupancy occ[256] = {};
 };
 
 extern "C" {
@@ -194,6 +205,7 @@ void boa_free_index(boa_index *ix)
     if (ix->ev_pool) (void)hipEventDestroy(ix->ev_pool);
     if (ix->ev_join) (void)hipEventDestroy(ix->ev_join);
     if (ix->aux) (void)hipStreamDestroy(ix->aux);
+    if (ix->h_back) (void)hipHostFree(ix->h_back);
     (void)hipSetDevice(cur);
     delete ix;
 }
@@ -344,6 +356,11 @@ int boa_build_index_ex(const void *vectors, int64_t n, int32_t d, int32_t vec_dt
         boa_free_index(ix);
         return fail(BOA_EHIP, "hipEventCreate failed");
     }
+    if (hipHostMalloc(reinterpret_cast<void **>(&ix->h_back), 64, hipHostMallocDefault) != hipSuccess) {
+        ix->h_back = nullptr;
+        boa_free_index(ix);
+        return fail(BOA_ENOMEM, "hipHostMalloc of 64 bytes failed");
+    }
     *out = ix;
     return BOA_OK;
 }
@@ -471,6 +488,29 @@ int make_schedule(const boa_params *p, int32_t *s, int32_t *n)
     return BOA_OK;
 }
 
+template <class Query>
+int cached_occupancy(const boa_index *ix, uint64_t shape, Query &&query)
+{
+    boa_index::Occupancy &o = ix->occ[(shape * 0x9E3779B97F4A7C15ull) >> 56];
+    if (o.shape == shape) return o.blocks;
+    const int b = query();
+    if (b > 0) o = {shape, b};   // (0: does not fit, or an error that may pass)
+    return b;
+}
+
+// (a shape is never 0: lds is not)
+int phase_blocks(const boa_index *ix, int wpb, size_t lds, bool wide, int pq_m)
+{
+    const uint64_t shape = (uint64_t)lds | (uint64_t)wpb << 32 | (uint64_t)(wide ? 1 : 0) << 40 | (uint64_t)pq_m << 44;
+    return cached_occupancy(ix, shape, [&] { return phase_occupancy(ix->vec_dtype, ix->view.d, wpb, lds, wide, pq_m); });
+}
+
+int team_blocks(const boa_index *ix, int parts, size_t lds, int pq_m)
+{
+    const uint64_t shape = (uint64_t)lds | (uint64_t)parts << 32 | 2ull << 40 | (uint64_t)pq_m << 44;
+    return cached_occupancy(ix, shape, [&] { return team_occupancy(ix->vec_dtype, ix->view.d, parts, lds, pq_m); });
+}
+
 uint32_t id_bits(const boa_index *ix)
 {
     uint32_t b = 1;
@@ -514,7 +554,7 @@ PhasePlan plan_phase(const boa_index *ix, int32_t L, int32_t forced_h, int64_t m
     int best_w = 0, best_wpb = 1, best_occ = 1;
     for (int wpb = 4; wpb >= 1; wpb >>= 1) {
         if ((size_t)wpb * pl.lds_per_wave > ix->lds_per_block_max) continue;
-        int occ = phase_occupancy(ix->vec_dtype, ix->view.d, wpb, (size_t)wpb * pl.lds_per_wave, wide, pq_m);
+        int occ = phase_blocks(ix, wpb, (size_t)wpb * pl.lds_per_wave, wide, pq_m);
         if (occ * wpb > best_w) {
             best_w = occ * wpb;
             best_wpb = wpb;
@@ -615,7 +655,7 @@ PhasePlan plan_bitmap(const boa_index *ix, int32_t L, int64_t S, int pq_m = 0)
     pl.lds_per_wave = (int32_t)((lds + 15) & ~(int64_t)15);
     pl.wpb = 1;
     if ((size_t)pl.lds_per_wave > ix->lds_per_block_hw) return pl;   // capacity 0: not possible
-    const int occ = phase_occupancy(ix->vec_dtype, ix->view.d, 1, (size_t)pl.lds_per_wave, true, pq_m);
+    const int occ = phase_blocks(ix, 1, (size_t)pl.lds_per_wave, true, pq_m);
     const int64_t blocks = (int64_t)std::max(occ, 0) * ix->num_cu;
     pl.capacity = blocks;
     pl.blocks = (int32_t)std::min<int64_t>(blocks, std::max<int64_t>(S, 1));
@@ -664,7 +704,7 @@ TeamPlan plan_team(const boa_index *ix, int32_t L, int64_t S, int32_t forced_h, 
         pl.h_slots = h;
         pl.vis_words = words;
         pl.parts = parts;
-        pl.capacity = (int64_t)team_occupancy(ix->vec_dtype, ix->view.d, parts, lds, pq_m) * ix->num_cu;
+        pl.capacity = (int64_t)team_blocks(ix, parts, lds, pq_m) * ix->num_cu;
         pl.blocks = (int32_t)std::min<int64_t>(pl.capacity, std::max<int64_t>(S, 1));
         if (pl.capacity > best.capacity) best = pl;
         return pl.capacity > 0 && pl.capacity >= S;
@@ -716,6 +756,7 @@ struct Request {
     int32_t n_phases;
     bool plus, split, fused, warm;
     bool team;                // teams of waves per query where they apply
+    bool one_launch;          // every phase in one launch (fused, or decided by plan_search)
     int32_t pq_m;             // > 0: product-quantised traversal with that many subspaces
     int32_t sub;              // BOA+ sub-batches (1 otherwise)
     int32_t n_counters;
@@ -762,6 +803,7 @@ int validate(const boa_index *ix, const void *queries, const int32_t *ranges, in
     if (p->escalation_waves != 0 && p->escalation_waves != 1)
         return fail(BOA_EINVAL, "escalation_waves must be 0 or 1");
     rq.team = p->escalation_waves == 0;
+    rq.one_launch = rq.fused;
     rq.sub = rq.plus ? std::min<int64_t>(p->sub_batches, std::max<int64_t>(nq, 1)) : 1;
     rq.n_counters = rq.n_phases * (rq.sub + 1) + 8;
     rq.tau_count = (uint32_t)std::floor(p->tau * (double)nq);
@@ -770,11 +812,32 @@ int validate(const boa_index *ix, const void *queries, const int32_t *ranges, in
 
 // Launch plans of every phase, and the number of wave slots (spill bitmaps)
 // the search may use at once.
-int plan_search(const boa_index *ix, const Request &rq, int64_t nq, int32_t forced_h, PhasePlan *plans,
+int plan_search(const boa_index *ix, Request &rq, int64_t nq, int32_t forced_h, PhasePlan *plans,
                 TeamPlan *teams, uint64_t *slots_out)
 {
     uint64_t slots = 0;
     const int32_t Lw = rq.sched[rq.n_phases - 1];
+    // Where every query is resident at once as a team at the widest width, a
+    // phased or split search runs in one launch too (each phase restarts its
+    // query, so results are the same): nothing is gained by collecting the
+    // survivors, and each further phase costs a compaction and a launch, 18 us
+    // even without a survivor, or the survivor count's way to the host and back,
+    // 45 us.
+    if (!rq.fused && !rq.plus && rq.team && forced_h <= 0 && rq.tau_count == 0 && rq.n_phases > 1) {
+        const TeamPlan tp = plan_team(ix, Lw, nq, 0, rq.pq_m);
+        if (tp.capacity >= nq) {
+            rq.one_launch = true;
+            for (int32_t ph = 0; ph < rq.n_phases; ++ph) {
+                plans[ph] = PhasePlan{};
+                plans[ph].L = rq.sched[ph];
+                plans[ph].wpb = 1;
+                plans[ph].blocks = 1;
+            }
+            teams[0] = tp;
+            *slots_out = tp.h_slots ? (uint64_t)tp.blocks : 1;
+            return BOA_OK;
+        }
+    }
     for (int32_t ph = 0; ph < rq.n_phases; ++ph) {
         // a fused launch, and a BOA+ escalation launch, size LDS for the widest phase
         const bool widest = rq.fused || (rq.plus && ph > 0);
@@ -902,7 +965,8 @@ int run_search(boa_index *ix, const void *queries, const int32_t *ranges, int64_
             e.lds_per_wave = tp.lds;
             e.waves_per_block = 1;
             if (bound > tp.capacity) e.max_active = a.min_active = (uint32_t)tp.capacity;
-            const int64_t tb = std::min<int64_t>(std::min<int64_t>(tp.blocks, bound), (int64_t)max_slots);
+            int64_t tb = std::min<int64_t>(tp.blocks, bound);
+            if (tp.h_slots) tb = std::min<int64_t>(tb, (int64_t)max_slots);   // (a spill bitmap each)
 #ifdef BOA_STAGE_PROFILE
             unsigned long long *tprof = nullptr;
             const size_t tpn = (size_t)tb * BOA_PROF_SLOTS;
@@ -923,7 +987,14 @@ int run_search(boa_index *ix, const void *queries, const int32_t *ranges, int64_
         return BOA_OK;
     };
 
-    if (rq.fused) {
+    // the launch shape that teams take, in the search's statistics
+    auto as_team = [&](PhasePlan &pl, const TeamPlan &tp, int64_t bound) {
+        if (tp.capacity < bound) return;
+        pl.wpb = 1 + 3 * tp.parts;
+        pl.blocks = (int32_t)std::min<int64_t>(tp.blocks, bound);
+        pl.h_slots = tp.h_slots;
+    };
+    if (rq.one_launch) {
         PhasePlan &pl = plans[0];
         PhaseArgs a = base;
         a.active = ws.active[0];
@@ -935,7 +1006,7 @@ int run_search(boa_index *ix, const void *queries, const int32_t *ranges, int64_
         a.p_end = n_phases;
         a.warm = rq.warm ? 1 : 0;
         a.L_alloc = Lw;
-        a.h_log2 = ilog2((uint32_t)pl.h_slots);
+        a.h_log2 = pl.h_slots ? ilog2((uint32_t)pl.h_slots) : 3;   // (a merged search's launch takes the team's)
         a.lds_per_wave = pl.lds_per_wave;
         a.waves_per_block = pl.wpb;
         a.slot_base = 0;
@@ -952,6 +1023,9 @@ int run_search(boa_index *ix, const void *queries, const int32_t *ranges, int64_
         if (int rc2 = stage_profile_end(prof, pn, Lw, pl.blocks * pl.wpb, st)) return rc2;
 #endif
         pl.launches = 1;
+        if (!rq.fused)   // (served: the phases that had queries)
+            for (int32_t ph = 1; ph < n_phases; ++ph) plans[ph].launches = -1;
+        as_team(pl, teams[0], nq);
     } else if (rq.split) {
         // the first phase over every query at its own width ...
         PhasePlan &p0 = plans[0];
@@ -981,9 +1055,9 @@ int run_search(boa_index *ix, const void *queries, const int32_t *ranges, int64_
             ca.n_out = ws.n_active + 1;
             ca.tau_count = rq.tau_count;
             HIP_TRY(launch_compact(ca, st));
-            uint32_t S = 0;
-            HIP_TRY(hipMemcpyAsync(&S, ws.n_active + 1, sizeof(S), hipMemcpyDeviceToHost, st));
+            HIP_TRY(hipMemcpyAsync(ix->h_back, ws.n_active + 1, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
             HIP_TRY(hipStreamSynchronize(st));
+            const uint32_t S = ix->h_back[0];
             if (S > 0) {
                 PhasePlan pe = plan_escalation(ix, Lw, S, p->lds_hash_slots, rq.pq_m);
                 if ((size_t)pe.lds_per_wave > (pe.vis_bitmap ? ix->lds_per_block_hw : ix->lds_per_block_max))
@@ -1012,11 +1086,7 @@ int run_search(boa_index *ix, const void *queries, const int32_t *ranges, int64_
 #endif
                 const TeamPlan te = rq.team ? plan_team(ix, Lw, S, p->lds_hash_slots, rq.pq_m) : TeamPlan();
                 if (int rc = launch(e, pe.blocks, st, true, 1, te, S, true, ws.slots)) return rc;
-                if (te.capacity > 0 && (int64_t)S <= te.capacity) {
-                    pe.h_slots = te.h_slots;
-                    pe.wpb = 1;
-                    pe.blocks = te.blocks;
-                }
+                as_team(pe, te, S);
 #ifdef BOA_STAGE_PROFILE
                 std::fprintf(stderr, "[stage-profile] split escalation: %u survivors, table %d slots, %d waves\n",
                              S, pe.h_slots, pe.blocks * pe.wpb);
@@ -1161,10 +1231,14 @@ int run_search(boa_index *ix, const void *queries, const int32_t *ranges, int64_
         }
     }
 
-    if (ws.timing) HIP_TRY(hipEventRecord(ix->ev_all1, st));
-    uint32_t status = 0;
-    HIP_TRY(hipMemcpyAsync(&status, ws.status, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
+    if (ws.timing) {
+        // (the last launch's own event, where it is the last on the stream)
+        if (rq.plus) HIP_TRY(hipEventRecord(ix->ev_all1, st));
+        ix->ev_last = rq.plus ? ix->ev_all1 : ix->ev_end[ev - 1];
+    }
+    HIP_TRY(hipMemcpyAsync(ix->h_back, ws.status, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));
+    const uint32_t status = ix->h_back[0];
     if (ws.timing) {
         ix->plans.assign(plans, plans + n_phases);
         ix->last_nq = nq;
@@ -1324,7 +1398,6 @@ extern "C" int boa_get_stats(const boa_index *ix, boa_stats *out)
     for (int32_t ph = 0; ph < np; ++ph) {
         boa_phase_stats &ps = out->phase[ph];
         ps.L = ix->plans[ph].L;
-        ps.launches = ix->plans[ph].launches;
         for (int64_t i = 0; i < nq; ++i) {
             uint8_t s = st[(size_t)ph * nq + i];
             if (!s) continue;
@@ -1337,6 +1410,7 @@ extern "C" int boa_get_stats(const boa_index *ix, boa_stats *out)
         // a product-quantised search reads a point's code instead of its
         // vector (the exact re-rank's reads are not counted here)
         const double per_scored = ix->last_pq_m ? 4.0 * v.m + ix->last_pq_m / 2 : 4.0 * v.m + v.d * e;
+        ps.launches = ix->plans[ph].launches >= 0 ? ix->plans[ph].launches : (ps.active > 0 ? 1 : 0);
         ps.gathered_bytes = 4.0 * v.R * (double)ps.expansions + per_scored * (double)ps.scored +
                             (v.d * e + 8.0 * v.m + 8.0 * ix->last_k + 4.0) * (double)ps.active;
     }
@@ -1346,7 +1420,7 @@ extern "C" int boa_get_stats(const boa_index *ix, boa_stats *out)
         out->phase[lp.first].kernel_ms += ms;
     }
     float tot = 0.f;
-    HIP_TRY(hipEventElapsedTime(&tot, ix->ev_all0, ix->ev_all1));
+    HIP_TRY(hipEventElapsedTime(&tot, ix->ev_all0, ix->ev_last));
     out->total_ms = tot;
     out->cum_searches = ix->cum_searches;
     out->cum_launches = ix->cum_launches;
