@@ -192,6 +192,8 @@ struct F32Scorer {
                                        : (T <= 2 ? 16 : (T <= 4 ? 8 : (T <= 6 ? 4 : (T <= 12 ? 2 : 1))));
     // waves per SIMD a team launch's registers leave room for
     static constexpr int kTeamWaves = T <= 4 ? 4 : 2;
+    // ... and a launch with one wave per query
+    static constexpr int kWaves = W == 1 ? (T <= 8 ? 3 : 2) : 1;
     struct Ids {
         uint32_t v[RU];
     };
@@ -284,6 +286,7 @@ struct U8Scorer {
     // before its visited test (gather_row / score_row below)
     static constexpr bool kSpec = G <= 8;
     static constexpr int kTeamWaves = G <= 16 ? 4 : 2;
+    static constexpr int kWaves = W == 1 || G <= 8 ? 3 : 1;
     static constexpr int kLdsBytes = 0;
     static constexpr bool kPQ = false;
     uint4 q;
@@ -429,6 +432,7 @@ struct PQScorer {
     static constexpr bool kSpec = false;
     static constexpr int kSpecMaxR = 0;
     static constexpr int kTeamWaves = 4;
+    static constexpr int kWaves = 2;
     struct RowGather {};
     __device__ __forceinline__ void gather_row(const void *, int, uint32_t, int, int, RowGather &) const {}
     __device__ __forceinline__ void score_row(const RowGather &, int, int, float *, int) const {}
@@ -646,18 +650,20 @@ __device__ __forceinline__ void load_attr_record(const IndexView &ix, uint32_t i
     }
 }
 
+// The bounds stay in lane j of two registers, column j's, and are read back as
+// scalars where a cell is tested (held in all lanes they take 16 registers, and
+// as scalars across the search they spill).
 struct RangeTest {
-    int32_t flo[BOA_MAX_M];
-    uint32_t fspan[BOA_MAX_M];
+    int32_t l;
+    uint32_t s;
     uint32_t phi0;
 
-    // query qi's m ranges (row-major nq x m x 2 cells): lane j takes column
-    // j's, in one load, and the lanes' bounds are then read by every lane
+    // query qi's m ranges (row-major nq x m x 2 cells)
     __device__ __forceinline__ void set(const int32_t *ranges, uint32_t qi, int m, uint32_t f32_mask)
     {
         const int lane = lane_id();
-        int32_t l = 0;
-        uint32_t s = 0xFFFFFFFFu;   // (padding cells pass)
+        l = 0;
+        s = 0xFFFFFFFFu;   // (padding cells pass)
         bool none = false;
         if (lane < m) {
             const int32_t *r = ranges + ((size_t)qi * m + lane) * 2;
@@ -674,16 +680,6 @@ struct RangeTest {
             }
         }
         phi0 = (uint32_t)__popcll(__ballot(none));
-#pragma unroll
-        for (int j = 0; j < BOA_MAX_M; ++j) {
-            int32_t lj = __builtin_amdgcn_readlane(l, j);
-            uint32_t sj = (uint32_t)__builtin_amdgcn_readlane((int)s, j);
-            // (held in vector registers: kept uniform they would be spilled
-            // scalars, reloaded at every use)
-            asm volatile("" : "+v"(lj), "+v"(sj));
-            flo[j] = lj;
-            fspan[j] = sj;
-        }
     }
 
     // phi of a record: its m_pad cells (one uniform dispatch, no per-cell tests)
@@ -694,7 +690,11 @@ struct RangeTest {
             constexpr int NC = decltype(nc_tag)::value;
             uint32_t p = phi0;
 #pragma unroll
-            for (int j = 0; j < NC; ++j) p += (uint32_t)(av[j] - flo[j]) > fspan[j] ? 1u : 0u;
+            for (int j = 0; j < NC; ++j) {
+                const int32_t lj = __builtin_amdgcn_readlane(l, j);
+                const uint32_t sj = (uint32_t)__builtin_amdgcn_readlane((int)s, j);
+                p += (uint32_t)(av[j] - lj) > sj ? 1u : 0u;
+            }
             return p;
         };
         switch (m_pad) {
@@ -1304,7 +1304,7 @@ struct PhaseResult {
 };
 
 template <class Scorer>
-__global__ void __launch_bounds__(256) phase_kernel(PhaseArgs a)
+__global__ void __launch_bounds__(256, Scorer::kWaves) phase_kernel(PhaseArgs a)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     const int lane = lane_id();
