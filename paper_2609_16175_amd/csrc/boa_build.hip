@@ -120,10 +120,13 @@ struct BuildView {
     int64_t n;
     int32_t d;
     int32_t u8;
+    const float *D;          // all n x ld distances, or null
+    int64_t ld;
 };
 
 __device__ __forceinline__ float dist_ids(const BuildView &v, uint32_t a, uint32_t b)
 {
+    if (v.D) return v.D[(size_t)a * v.ld + b];
     if (v.u8) {
         const uint8_t *X = reinterpret_cast<const uint8_t *>(v.vectors);
         return pair_dist_u8(X + (size_t)a * v.d, X + (size_t)b * v.d, v.d, v.norms[a], v.norms[b]);
@@ -263,25 +266,31 @@ __global__ void norms_kernel(BuildView v, uint32_t *norms, int32_t *norms_shifte
 // ---------------------------------------------------------------------------
 // 2. exact nearest candidates of every point
 //
-// A panel of rows at a time: its distances to all points go to memory, and a
-// wave per row then picks the nearest for every list in one sweep. One sweep per list, with the distances computed
+// A tile of rows and columns at a time: its distances go to memory, and a wave
+// per row then picks the nearest for every list in one sweep. One sweep per list, with the distances computed
 // again for each and the rows' lists holding the compute units' LDS, took 5
 // times 11.7 ms at n = 30,000, d = 96, five lists; see the kernels for theirs.
 
 static constexpr int DT = 128;   // rows and columns of a distance tile
 static constexpr int DK = 16;    // dimensions staged at once (float32)
 
-// Distances of rows [r0, r0 + rows) to every point, float32, dimensions in
-// order (the sums of pair_dist_f32). 128 x 128 tiles, 8 x 8 pairs per thread:
+// Distances of rows [r0, r0 + rows) to the points from cb on (as many as the
+// grid's columns), float32, dimensions in order (the sums of pair_dist_f32). 128 x 128 tiles, 8 x 8 pairs per thread:
 // 128 vector instructions for four LDS reads per dimension, so that it runs at
 // the vector units' rate (a difference and a fused multiply-add per pair and
 // dimension; matrix instructions would sum in another order).
+//
+// SYM: all pairs at once (r0 = cb = 0, rows = n); only the tiles on and above the
+// diagonal are computed, and written at their mirrored place too (the two
+// differences have the same square).
+template <bool SYM>
 __global__ void __launch_bounds__(256) dist_f32_kernel(const float *X, int64_t n, int d, int64_t r0, int64_t rows,
-                                                       int64_t ld, float *D)
+                                                       int64_t cb, int64_t ld, float *D)
 {
+    if (SYM && blockIdx.x < blockIdx.y) return;
     __shared__ __align__(16) float A[DK][DT + 4], B[DK][DT + 4];
     const int t = threadIdx.x, tr = t >> 4, tc = t & 15;
-    const int64_t row0 = r0 + (int64_t)blockIdx.y * DT, col0 = (int64_t)blockIdx.x * DT;
+    const int64_t row0 = r0 + (int64_t)blockIdx.y * DT, col0 = cb + (int64_t)blockIdx.x * DT;
     float acc[8][8];
 #pragma unroll
     for (int i = 0; i < 8; ++i)
@@ -334,9 +343,19 @@ __global__ void __launch_bounds__(256) dist_f32_kernel(const float *X, int64_t n
     for (int i = 0; i < 8; ++i) {
         const int64_t r = (int64_t)blockIdx.y * DT + (i < 4 ? 4 * tr + i : 64 + 4 * tr + i - 4);
         if (r >= rows) continue;
-        float *o = D + (size_t)r * ld + col0;
+        float *o = D + (size_t)r * ld + (col0 - cb);
         *reinterpret_cast<float4 *>(o + 4 * tc) = make_float4(acc[i][0], acc[i][1], acc[i][2], acc[i][3]);
         *reinterpret_cast<float4 *>(o + 64 + 4 * tc) = make_float4(acc[i][4], acc[i][5], acc[i][6], acc[i][7]);
+    }
+    if (SYM && blockIdx.x > blockIdx.y) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const int64_t c = col0 + (j < 4 ? 4 * tc + j : 64 + 4 * tc + j - 4);
+            if (c >= n) continue;
+            float *o = D + (size_t)c * ld + row0;
+            *reinterpret_cast<float4 *>(o + 4 * tr) = make_float4(acc[0][j], acc[1][j], acc[2][j], acc[3][j]);
+            *reinterpret_cast<float4 *>(o + 64 + 4 * tr) = make_float4(acc[4][j], acc[5][j], acc[6][j], acc[7][j]);
+        }
     }
 }
 
@@ -349,12 +368,12 @@ typedef int32_t int16v __attribute__((ext_vector_type(16)));
 // lane, as they lie in memory). A wave computes 64 x 64 pairs, a block of four
 // 128 x 128; the products are a twentieth of the time, the writes the rest.
 __global__ void __launch_bounds__(256) dist_u8_kernel(const uint8_t *X, const int32_t *norms, int64_t n, int d,
-                                                      int64_t r0, int64_t rows, int64_t ld, float *D)
+                                                      int64_t r0, int64_t rows, int64_t cb, int64_t ld, float *D)
 {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int half = lane >> 5, l32 = lane & 31;
     const int64_t row0 = r0 + (int64_t)blockIdx.y * DT + 64 * (w >> 1);
-    const int64_t col0 = (int64_t)blockIdx.x * DT + 64 * (w & 1);
+    const int64_t col0 = cb + (int64_t)blockIdx.x * DT + 64 * (w & 1);
     int16v acc[2][2] = {};
     for (int k0 = 0; k0 < d; k0 += 32) {
         const int k = k0 + 16 * half;
@@ -390,21 +409,28 @@ __global__ void __launch_bounds__(256) dist_u8_kernel(const uint8_t *X, const in
             for (int j = 0; j < 2; ++j) {
                 const int64_t c = col0 + 32 * j + l32;
                 const int32_t nc = norms[c < n ? c : 0];
-                D[(size_t)(r - r0) * ld + c] = (float)(nr + nc - 2 * acc[i][j][g]);
+                D[(size_t)(r - r0) * ld + (c - cb)] = (float)(nr + nc - 2 * acc[i][j][g]);
             }
         }
     }
 }
 
 struct SelectArgs {
-    const float *D;          // rows [r0, r0 + rows) x ld
-    int64_t n, r0, rows, ld;
+    const float *D;          // rows [r0, r0 + rows) x ld: distances to points [c0, c1)
+    int64_t n, r0, rows, ld, c0, c1;
+    uint64_t *state;         // per row of the panel: its lists between two column chunks
     int32_t K, Kl, levels, m;
     const int32_t *ranks;    // m x n quantile ranks
     const int32_t *thr;      // levels x n thresholds in rank units, not decreasing over the levels
     uint32_t *cand;          // n x K ids (0xFFFFFFFF padded)
     uint32_t *lcand;         // levels x n x Kl ids
 };
+
+__device__ __forceinline__ uint64_t uniform64(uint64_t x)
+{
+    return ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(x >> 32)) << 32) |
+           (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)x);
+}
 
 // The K (at most N / 2) smallest keys seen, in the first half of N slots of
 // LDS (BKEY_NONE past their number), and behind them the newer ones: sorted and
@@ -422,6 +448,23 @@ struct TopList {
         limit = BKEY_NONE;
         for (int i = lane; i < N; i += 64) a[i] = BKEY_NONE;
     }
+    // the list's slots, and behind them its limit and count
+    __device__ __forceinline__ void save(uint64_t *to, int lane) const
+    {
+        wave_fence();
+        for (int i = lane; i < N; i += 64) to[i] = a[i];
+        if (lane == 0) {
+            to[N] = limit;
+            to[N + 1] = (uint64_t)cnt;
+        }
+    }
+    __device__ __forceinline__ void load(const uint64_t *from, int lane)
+    {
+        for (int i = lane; i < N; i += 64) a[i] = from[i];
+        limit = uniform64(from[N]);
+        cnt = (int)uniform64(from[N + 1]);
+        wave_fence();
+    }
     __device__ __forceinline__ void cut(int lane)
     {
         wave_fence();
@@ -431,11 +474,12 @@ struct TopList {
         wave_fence();
         if (cnt >= K) {
             cnt = K;
-            const uint64_t last = a[K - 1];
-            limit = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(last >> 32)) << 32) |
-                    (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)last);
+            limit = uniform64(a[K - 1]);
         }
     }
+    // whether a distance (its bits) may be below the limit: nothing to push
+    // where no lane's is
+    __device__ __forceinline__ bool may(uint32_t bits) const { return bits <= (uint32_t)(limit >> 32); }
     __device__ __forceinline__ void push(uint64_t key, int lane)
     {
         uint64_t m = __ballot(key < limit);
@@ -471,18 +515,26 @@ __global__ void __launch_bounds__(256) select_kernel(SelectArgs a)
         lvl[l].init(lists[wid] + 256 + 128 * l, a.Kl, lane);
         t[l] = l < a.levels ? a.thr[(size_t)l * a.n + row] : -1;
     }
+    constexpr int STATE = 256 + 2 + KNN_LEVELS * (128 + 2);
+    uint64_t *st = a.state + (size_t)i * STATE;
+    if (a.c0 > 0) {
+        near.load(st, lane);
+#pragma unroll
+        for (int l = 0; l < KNN_LEVELS; ++l)
+            if (l < a.levels) lvl[l].load(st + 258 + 130 * l, lane);
+    }
     int32_t mine[BOA_MAX_M];
 #pragma unroll
     for (int j = 0; j < BOA_MAX_M; ++j) mine[j] = a.levels > 0 && j < a.m ? a.ranks[(size_t)j * a.n + row] : 0;
     const float *D = a.D + (size_t)i * a.ld;
     constexpr int U = 4;   // columns per lane in flight
-    for (int64_t c0 = 0; c0 < a.n; c0 += 64 * U) {
+    for (int64_t c0 = a.c0; c0 < a.c1; c0 += 64 * U) {
         float dd[U];
         int32_t gap[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int64_t c = c0 + 64 * u + lane;
-            dd[u] = D[c < a.n ? c : a.n - 1];
+            dd[u] = D[(c < a.c1 ? c : a.c1 - 1) - a.c0];
             gap[u] = 0;
         }
         if (a.levels > 0) {
@@ -493,7 +545,7 @@ __global__ void __launch_bounds__(256) select_kernel(SelectArgs a)
 #pragma unroll
                     for (int u = 0; u < U; ++u) {
                         const int64_t c = c0 + 64 * u + lane;
-                        const int32_t g = mine[j] - a.ranks[(size_t)j * a.n + (c < a.n ? c : a.n - 1)];
+                        const int32_t g = mine[j] - a.ranks[(size_t)j * a.n + (c < a.c1 ? c : a.c1 - 1)];
                         gap[u] = max(gap[u], g < 0 ? -g : g);
                     }
                 }
@@ -502,12 +554,23 @@ __global__ void __launch_bounds__(256) select_kernel(SelectArgs a)
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int64_t c = c0 + 64 * u + lane;
-            const uint64_t key = c < a.n && c != row ? bkey(dd[u], (uint32_t)c) : BKEY_NONE;
-            near.push(key, lane);
+            const uint32_t bits = __float_as_uint(dd[u]);
+            const uint64_t key = c < a.c1 && c != row ? bkey(dd[u], (uint32_t)c) : BKEY_NONE;
+            if (__ballot(near.may(bits)) != 0ull) near.push(key, lane);
 #pragma unroll
-            for (int l = 0; l < KNN_LEVELS; ++l)
-                if (l < a.levels) lvl[l].push(gap[u] <= t[l] ? key : BKEY_NONE, lane);
+            for (int l = 0; l < KNN_LEVELS; ++l) {
+                if (l >= a.levels) break;   // uniform
+                const bool in = gap[u] <= t[l];
+                if (__ballot(in && lvl[l].may(bits)) != 0ull) lvl[l].push(in ? key : BKEY_NONE, lane);
+            }
         }
+    }
+    if (a.c1 < a.n) {   // more columns to come
+        near.save(st, lane);
+#pragma unroll
+        for (int l = 0; l < KNN_LEVELS; ++l)
+            if (l < a.levels) lvl[l].save(st + 258 + 130 * l, lane);
+        return;
     }
     near.cut(lane);
     for (int q = lane; q < a.K; q += 64) {
@@ -639,8 +702,7 @@ struct PruneArgs {
 // `budget` ids), by the alpha-dominance rule. Every kept point is tested at
 // once against all the candidates still alive, four per lane: as many steps
 // as points are kept (8 to 63), instead of one per candidate (up to 256) with
-// a lane per kept point: 14.5 and 5.6 ms of pruning at n = 30,000, d = 96, R = 64;
-// 28.7 and 12.1 ms at n = 10,000, d = 768, R = 48.
+// a lane per kept point: 14.5 and 5.6 ms of pruning at n = 30,000, d = 96, R = 64.
 __device__ void alpha_prune(const BuildView &v, const uint64_t *keys, int cnt, int budget, float alpha2,
                             uint32_t *out_row, int R, int lane)
 {
@@ -676,7 +738,7 @@ __device__ void alpha_prune(const BuildView &v, const uint64_t *keys, int cnt, i
                 const uint32_t c = (uint32_t)key[h];
                 const float duv = __uint_as_float((uint32_t)(key[h] >> 32));
                 bool dom;
-                if (v.u8) {
+                if (v.u8 || v.D) {
                     dom = alpha2 * dist_ids(v, w, c) <= duv;
                 } else {
                     const float *X = reinterpret_cast<const float *>(v.vectors);
@@ -799,7 +861,7 @@ __global__ void __launch_bounds__(256) append_levels_kernel(uint32_t *adj, const
     int cnt = __popcll(__ballot(v != BOA_PAD));   // (the ids fill a row's front)
     const int cnt0 = cnt;
     for (int l = 0; in && l < levels; ++l) {
-        const uint32_t e = lane < b_lvl ? level_rows[((size_t)l * n + u) * R + lane] : BOA_PAD;
+        const uint32_t e = lane < b_lvl ? level_rows[((size_t)l * n + u) * b_lvl + lane] : BOA_PAD;
         for (int i = 0; i < b_lvl && cnt < R - 1; ++i) {
             const uint32_t x = (uint32_t)__builtin_amdgcn_readlane((int)e, i);
             if (x == BOA_PAD) break;
@@ -841,7 +903,12 @@ struct DevBuf {
     {
         if (p) (void)hipFree(p);
     }
-    hipError_t alloc(size_t bytes) { return hipMalloc(&p, bytes ? bytes : 1); }
+    hipError_t alloc(size_t bytes)
+    {
+        const hipError_t e = hipMalloc(&p, bytes ? bytes : 1);
+        if (e != hipSuccess) p = nullptr;
+        return e;
+    }
     template <class T>
     T *as() const { return reinterpret_cast<T *>(p); }
 };
@@ -859,7 +926,7 @@ struct DevBuf {
 
 hipError_t compute_medoid(const void *d_vectors, int64_t n, int32_t d, int vec_dtype, uint32_t *entry)
 {
-    BuildView v{d_vectors, nullptr, n, d, vec_dtype == BOA_VEC_U8 ? 1 : 0};
+    BuildView v{d_vectors, nullptr, n, d, vec_dtype == BOA_VEC_U8 ? 1 : 0, nullptr, 0};
     const int nb = (int)std::min<int64_t>(512, n);
     const int64_t per = (n + nb - 1) / nb;
     DevBuf part, cen, bd, bi;
@@ -926,43 +993,71 @@ hipError_t ranks_and_thresholds(const int32_t *h_attrs, int64_t n, int m, uint32
     return hipSuccess;   // (freeing the copy of the attributes waits for the kernels)
 }
 
-// Panels of rows: as many as the selection has waves resident (24 per CU of
-// 256), within 8 GB of distances. (Panels of 192 MB, which stay in the last
-// cache, leave the selection with under a tenth of its waves.)
-hipError_t find_candidates(const BuildView &v, const int32_t *norms_shifted, int K, int Kl, int levels, int m,
-                           const int32_t *ranks, const int32_t *thr, uint32_t *cand, uint32_t *lcand)
+// Where all distances fit 512 MB (11,500 points), they are computed in one
+// piece (half of a float32 index's mirrored) and stay for the pruning (v.D),
+// whose tests are then one read each: 12.1 -> 0.3 ms at n = 10,000, d = 768.
+// Otherwise in tiles of 6,144 rows (24 of the selection's waves per CU) by 6,144
+// columns, 151 MB, which stay in the last cache, the rows' lists kept between
+// them (38 MB): 23.6 ms at n = 60,000 uint8 (4,096 rows 27.0, with twice the
+// columns 24.8; 2,048 rows 34.2). More would be faster by itself (all distances
+// kept: 19 ms), but memory is cleared by the driver before it is handed out
+// again: 25 to 28 ms a gigabyte in programs that build repeatedly.
+constexpr int64_t WHOLE_BYTES = (int64_t)512 << 20;
+constexpr int64_t PANEL_ROWS = 6144, PANEL_COLS = 48 * DT;
+
+hipError_t find_candidates(BuildView &v, const int32_t *norms_shifted, int K, int Kl, int levels, int m,
+                           const int32_t *ranks, const int32_t *thr, uint32_t *cand, uint32_t *lcand, DevBuf &dist)
 {
-    const int64_t n = v.n, ld = (n + DT - 1) / DT * DT;
-    int64_t panel = std::min<int64_t>(24 * 256, ((int64_t)8 << 30) / (ld * 4) / DT * DT);
-    panel = std::min<int64_t>(std::max<int64_t>(panel, DT), ld);
-    DevBuf dist;
-    BTRY(dist.alloc((size_t)panel * ld * 4));
+    const int64_t n = v.n, all = (n + DT - 1) / DT * DT;
+    bool whole = n * all * 4 <= WHOLE_BYTES;
+    if (whole && dist.alloc((size_t)(n * all * 4)) != hipSuccess) {
+        (void)hipGetLastError();
+        whole = false;
+    }
+    const int64_t panel = whole ? n : std::min<int64_t>(PANEL_ROWS, all);
+    const int64_t ld = whole ? all : std::min<int64_t>(PANEL_COLS, all);
+    DevBuf state;
+    if (!whole) BTRY(dist.alloc((size_t)(panel * ld * 4)));
+    if (ld < n) BTRY(state.alloc((size_t)panel * (256 + 2 + KNN_LEVELS * (128 + 2)) * 8));
     for (int64_t r0 = 0; r0 < n; r0 += panel) {
         const int64_t rows = std::min<int64_t>(panel, n - r0);
-        const dim3 tiles((unsigned)(ld / DT), (unsigned)((rows + DT - 1) / DT));
-        if (v.u8)
-            hipLaunchKernelGGL(dist_u8_kernel, tiles, dim3(256), 0, 0, reinterpret_cast<const uint8_t *>(v.vectors),
-                               norms_shifted, n, v.d, r0, rows, ld, dist.as<float>());
-        else
-            hipLaunchKernelGGL(dist_f32_kernel, tiles, dim3(256), 0, 0, reinterpret_cast<const float *>(v.vectors), n,
-                               v.d, r0, rows, ld, dist.as<float>());
-        BTRY(hipGetLastError());
-        SelectArgs sa{};
-        sa.D = dist.as<float>();
-        sa.n = n;
-        sa.r0 = r0;
-        sa.rows = rows;
-        sa.ld = ld;
-        sa.K = K;
-        sa.Kl = Kl;
-        sa.levels = levels;
-        sa.m = m;
-        sa.ranks = ranks;
-        sa.thr = thr;
-        sa.cand = cand;
-        sa.lcand = lcand;
-        hipLaunchKernelGGL(select_kernel, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, 0, sa);
-        BTRY(hipGetLastError());
+        for (int64_t c0 = 0; c0 < n; c0 += ld) {
+            const int64_t c1 = std::min<int64_t>(c0 + ld, n);
+            const dim3 tiles((unsigned)((c1 - c0 + DT - 1) / DT), (unsigned)((rows + DT - 1) / DT));
+            if (v.u8)
+                hipLaunchKernelGGL(dist_u8_kernel, tiles, dim3(256), 0, 0, reinterpret_cast<const uint8_t *>(v.vectors),
+                                   norms_shifted, n, v.d, r0, rows, c0, ld, dist.as<float>());
+            else if (whole)
+                hipLaunchKernelGGL(dist_f32_kernel<true>, tiles, dim3(256), 0, 0,
+                                   reinterpret_cast<const float *>(v.vectors), n, v.d, r0, rows, c0, ld, dist.as<float>());
+            else
+                hipLaunchKernelGGL(dist_f32_kernel<false>, tiles, dim3(256), 0, 0,
+                                   reinterpret_cast<const float *>(v.vectors), n, v.d, r0, rows, c0, ld, dist.as<float>());
+            BTRY(hipGetLastError());
+            SelectArgs sa{};
+            sa.D = dist.as<float>();
+            sa.n = n;
+            sa.r0 = r0;
+            sa.rows = rows;
+            sa.ld = ld;
+            sa.c0 = c0;
+            sa.c1 = c1;
+            sa.state = state.as<uint64_t>();
+            sa.K = K;
+            sa.Kl = Kl;
+            sa.levels = levels;
+            sa.m = m;
+            sa.ranks = ranks;
+            sa.thr = thr;
+            sa.cand = cand;
+            sa.lcand = lcand;
+            hipLaunchKernelGGL(select_kernel, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, 0, sa);
+            BTRY(hipGetLastError());
+        }
+    }
+    if (whole) {
+        v.D = dist.as<float>();
+        v.ld = ld;
     }
     return hipSuccess;
 }
@@ -1009,7 +1104,7 @@ hipError_t build_graph(const void *d_vectors, int64_t n, int32_t d, int vec_dtyp
     const int budget = std::max(1, R - 1 - levels * b_lvl);
     const int K = (int)std::min<int64_t>(std::min(2 * R, KNN_LIST), n - 1);
     DevBuf norms, norms2;
-    BuildView v{d_vectors, nullptr, n, d, u8 ? 1 : 0};
+    BuildView v{d_vectors, nullptr, n, d, u8 ? 1 : 0, nullptr, 0};
     if (u8) {
         BTRY(norms.alloc((size_t)n * 4));
         BTRY(norms2.alloc((size_t)n * 4));
@@ -1027,7 +1122,7 @@ hipError_t build_graph(const void *d_vectors, int64_t n, int32_t d, int vec_dtyp
     // vectors among the points within the point's attribute threshold, where
     // the capped attribute distance is zero)
     const int Kl = (int)std::min<int64_t>(std::min(4 * b_lvl, KNN_LEVEL_LIST), n - 1);
-    DevBuf cand, lcand, ranks, thr;
+    DevBuf cand, lcand, ranks, thr, dist;
     BTRY(cand.alloc((size_t)n * K * 4));
     if (levels > 0) {
         BTRY(ranks.alloc((size_t)n * m * 4));
@@ -1036,7 +1131,7 @@ hipError_t build_graph(const void *d_vectors, int64_t n, int32_t d, int vec_dtyp
         BTRY(ranks_and_thresholds(h_attrs, n, m, f32_mask, kLevelQ, levels, ranks.as<int32_t>(), thr.as<int32_t>()));
     }
     BTRY(find_candidates(v, norms2.as<int32_t>(), K, Kl, levels, m, ranks.as<int32_t>(), thr.as<int32_t>(),
-                         cand.as<uint32_t>(), lcand.as<uint32_t>()));
+                         cand.as<uint32_t>(), lcand.as<uint32_t>(), dist));
     // 3. forward prune
     DevBuf fwd, lrow;
     BTRY(fwd.alloc((size_t)n * R * 4));
@@ -1053,12 +1148,12 @@ hipError_t build_graph(const void *d_vectors, int64_t n, int32_t d, int vec_dtyp
         BTRY(hipGetLastError());
     }
     if (levels > 0) {   // the levels' b_lvl edges per point
-        BTRY(lrow.alloc((size_t)n * R * levels * 4));
+        BTRY(lrow.alloc((size_t)n * b_lvl * levels * 4));
         PruneArgs pa{};
         pa.v = v;
         pa.cand = lcand.as<uint32_t>();
         pa.K = Kl;
-        pa.R = R;
+        pa.R = b_lvl;
         pa.budget = b_lvl;
         pa.alpha2 = alpha2;
         pa.out = lrow.as<uint32_t>();
