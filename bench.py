@@ -253,7 +253,7 @@ def main():
     ap.add_argument("--cpu-seconds", type=float, default=15.0, help="budget of the oracle timing")
     ap.add_argument("--lds-slots", type=int, default=0, help="force the LDS visited-table size")
     ap.add_argument("--escalation-waves", type=int, default=0, choices=(0, 1),
-                    help="split mode's escalation launch: 0 two waves per query where it applies, 1 one")
+                    help="0 teams of waves per query where they apply, 1 one wave per query")
     ap.add_argument("--modes", default="phased,fused,split,boa_plus,warm",
                     help="adaptive modes to time (warm: warm-start escalation, fused); the fastest of the "
                          "escalation kind chosen on the held-out batch is the headline")
