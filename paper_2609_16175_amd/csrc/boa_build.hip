@@ -1062,9 +1062,19 @@ hipError_t find_candidates(BuildView &v, const int32_t *norms_shifted, int K, in
     return hipSuccess;
 }
 
-// points a breadth-first search from `entry` reaches
+// Points a breadth-first search from `entry` reaches; -1 where the device's
+// search is not worth its steps, each a round trip to the host of 16 us. The
+// host's own search costs 4 to 16 ns an entry of the adjacency with its copies, so
+// the steps may take up to 2 ns an entry: rows of 16 and more of clustered and
+// random points (n = 1,000 to 60,000) need 4 to 19 steps, points along a line
+// thousands (a build of n = 10,000, R = 4: 91 ms with them, 1.9 without). Rows of
+// less than 8 entries leave points out of reach nearly always, which the host has
+// to repair (scattered points, n = 1,000, R = 4: 1.1 ms with the steps, 0.5 without).
 hipError_t count_reached(const uint32_t *adj, int64_t n, int R, uint32_t entry, int64_t *reached)
 {
+    *reached = -1;
+    const int64_t max_steps = R < 8 ? 0 : n * R / 8192;
+    if (max_steps == 0) return hipSuccess;
     DevBuf seen, list, count;
     BTRY(seen.alloc((size_t)n * 4));
     BTRY(list.alloc((size_t)n * 2 * 4));
@@ -1075,9 +1085,10 @@ hipError_t count_reached(const uint32_t *adj, int64_t n, int R, uint32_t entry, 
     BTRY(hipMemcpy(list.p, &entry, 4, hipMemcpyHostToDevice));
     uint32_t *in = list.as<uint32_t>(), *out = in + n;
     uint32_t n_in = 1;
-    *reached = 0;
-    while (n_in > 0) {   // (each point is listed once: at most n steps)
-        *reached += n_in;
+    int64_t listed = 0;
+    for (int64_t step = 0; n_in > 0; ++step) {
+        if (step == max_steps) return hipSuccess;
+        listed += n_in;
         BTRY(hipMemset(count.p, 0, 4));
         hipLaunchKernelGGL(bfs_kernel, dim3((n_in + 3) / 4), dim3(256), 0, 0, adj, R, seen.as<uint32_t>(), in, n_in, out,
                            count.as<uint32_t>());
@@ -1085,6 +1096,7 @@ hipError_t count_reached(const uint32_t *adj, int64_t n, int R, uint32_t entry, 
         BTRY(hipMemcpy(&n_in, count.p, 4, hipMemcpyDeviceToHost));
         std::swap(in, out);
     }
+    *reached = listed;
     return hipSuccess;
 }
 
@@ -1214,10 +1226,10 @@ hipError_t build_graph(const void *d_vectors, int64_t n, int32_t d, int vec_dtyp
     std::vector<uint32_t> adj((size_t)n * R), hc((size_t)n * K);
     BTRY(hipMemcpy(adj.data(), d_adj, adj.size() * 4, hipMemcpyDeviceToHost));
     BTRY(hipMemcpy(hc.data(), cand.p, hc.size() * 4, hipMemcpyDeviceToHost));
-    // 6. connectivity repair from s (host, where the device's search found
-    // points out of reach): breadth-first search, then each unreached point (ascending id) gets an in-edge from its nearest
-    // reached kNN candidate with a free slot; the search then continues
-    // from it
+    // 6. connectivity repair from s (host, unless the device's search found
+    // every point within reach): breadth-first search, then each unreached
+    // point (ascending id) gets an in-edge from its nearest reached kNN
+    // candidate with a free slot; the search then continues from it
     std::vector<uint8_t> seen((size_t)n, 0);
     std::vector<uint32_t> queue;
     queue.reserve((size_t)n);
