@@ -89,7 +89,8 @@ enum { BOA_ATTR_I32 = 0, BOA_ATTR_F32 = 1 };
  *               a 64-wide wavefront.
  *   entry       the entry point s of every search (Alg. 2), 0 <= entry < n;
  *               -1: the medoid, the point nearest (float64) to the float64
- *               centroid of the vectors, ties to the lowest id.
+ *               centroid of the vectors, ties to the lowest id (point 0 where
+ *               the vectors hold a NaN, which no distance compares with).
  *   n           1 <= n < BOA_MAX_N.
  *   out         receives the index; free it with boa_free_index.
  * Errors: BOA_EINVAL (bad sizes, null pointers, out-of-range ids in the

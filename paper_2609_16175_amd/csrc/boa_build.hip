@@ -959,7 +959,8 @@ hipError_t compute_medoid(const void *d_vectors, int64_t n, int32_t d, int vec_d
             best = hd[b];
             id = hi[b];
         }
-    *entry = id;
+    // (no point compares where the vectors hold a NaN: the lowest id)
+    *entry = id == 0xFFFFFFFFu ? 0u : id;
     return hipSuccess;
 }
 

@@ -209,6 +209,35 @@ def test_single_point_and_tiny_n():
         ix.close()
 
 
+@pytest.mark.parametrize("attr_levels", [0, 4])
+def test_vectors_with_a_nan_enter_at_point_0(attr_levels):
+    """No point is nearest to a centroid that is not a number: the entry point
+    is then point 0 (an id past the last point would be read out of range),
+    for a graph the library builds and for one that it is given."""
+    from workloads import graph
+    boa = _boa()
+    n, R = 300, 12
+    rng = np.random.default_rng(2)
+    x = rng.normal(size=(n, 16)).astype(np.float32)
+    x[7, 3] = np.nan
+    attrs = rng.integers(0, 50, size=(n, 2)).astype(np.int32)
+    types = np.zeros(2, dtype=np.int32)
+    ix = boa.Index(x, attrs, types, None, -1, R=R, attr_levels=attr_levels)
+    adj, entry, _ = ix.graph()
+    ix.close()
+    assert entry == 0
+    assert graph._reachable(n, adj, 0).all()
+    ix = boa.Index(x, attrs, types, adj, -1)
+    assert ix.graph()[1] == 0
+    q = torch.from_numpy(x[20:24].copy()).to("cuda:0")
+    r = torch.zeros((4, 2, 2), dtype=torch.int32, device="cuda:0")
+    r[:, :, 1] = 50
+    out = ix.search(q, r, k=1, fixed_L=64)
+    torch.cuda.synchronize()
+    assert out.ids.cpu().numpy()[:, 0].tolist() == [20, 21, 22, 23]
+    ix.close()
+
+
 @pytest.mark.parametrize("R", [4, 16])
 def test_points_along_a_line_build_about_as_fast_as_scattered_ones(R):
     """A graph thousands of steps deep: the search for points out of reach
