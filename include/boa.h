@@ -233,18 +233,24 @@ typedef struct {
     int32_t L;              /* phase beamwidth */
     int32_t active;         /* queries searched in the phase */
     int32_t confident;      /* of which resolved by the confidence test */
-    int32_t launches;       /* kernel launches of the phase (BOA+: sub-batches); where 0 and 2
-                               run in one launch: 1 for every phase that had queries */
+    int32_t launches;       /* search kernels launched for the phase (BOA+: one per sub-batch;
+                               a later phase whose number of queries is known on the device
+                               only takes two, one for few queries and one for many, of which
+                               one returns at once); where modes 0 and 2 run in one launch:
+                               1 for every phase that had queries */
     int64_t expansions;     /* nodes expanded, summed over the phase's queries */
     int64_t scored;         /* nodes scored (distance + predicates) */
     double gathered_bytes;  /* algorithmic bytes the phase had to read */
-    float kernel_ms;        /* device time of the phase's search launches */
+    float kernel_ms;        /* device time of the launches that start at the phase: a launch
+                               that covers several phases (fused, split, BOA+, and modes 0
+                               and 2 where they run in one launch) counts under the first */
 } boa_phase_stats;
 
 typedef struct {
     int32_t n_phases;
-    int32_t waves_per_block, blocks; /* launch shape of the first phase */
-    int32_t lds_hash_slots;          /* of the first phase */
+    int32_t waves_per_block, blocks; /* shape of the first search launch (a team of waves per
+                                        query: its waves, and a block per query) */
+    int32_t lds_hash_slots;          /* its LDS visited table (0: a bitmap over all ids) */
     int64_t spilled_queries;         /* query-phases whose visited set left LDS */
     float total_ms;                  /* device time of the whole search */
     /* accumulated since boa_reset_counters: searches, search-kernel launches,
@@ -252,8 +258,8 @@ typedef struct {
     int64_t cum_searches, cum_launches;
     double cum_kernel_ms;
     boa_phase_stats phase[BOA_MAX_PHASES];
-    /* accumulated like cum_*, split by the phase a launch starts at (a fused
-       launch counts under phase 0, a split search's second launch under 1) */
+    /* accumulated like cum_*, split by the phase a launch starts at (a launch
+       of all phases counts under 0, a split search's second launch under 1) */
     int64_t cum_phase_launches[BOA_MAX_PHASES];
     double cum_phase_kernel_ms[BOA_MAX_PHASES];
 } boa_stats;

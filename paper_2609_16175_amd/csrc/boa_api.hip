@@ -76,9 +76,12 @@ struct PhasePlan {
     int32_t L;
     int32_t h_slots, wpb, blocks, lds_per_wave;
     int32_t vis_bitmap;  // visited set as an LDS bitmap over all ids (0: hashed table)
-    int32_t launches;
     int64_t capacity;   // waves resident at once on the whole GPU
     bool wide;          // scorer variant with twice the rows in flight
+    // what ran, for the statistics: search kernels launched (-1: part of an
+    // earlier phase's launch), and the first one's shape (h_slots 0: LDS bitmap)
+    int32_t launches;
+    int32_t ran_wpb, ran_blocks, ran_slots;
 };
 
 }  // namespace
@@ -132,7 +135,10 @@ struct boa_index {
     int32_t last_k = 0;
     int32_t last_pq_m = 0;
     std::vector<PhasePlan> plans;
-    std::vector<std::pair<int, int>> launch_phase;  // (phase, event index)
+    struct Launch {
+        int phase, ev, kernels;      // the phase it starts at, its events, its kernels
+    };
+    std::vector<Launch> launched;
     hipEvent_t ev_all0 = nullptr, ev_all1 = nullptr;
     hipEvent_t ev_pool = nullptr, ev_join = nullptr;   // BOA+ cross-stream ordering
     bool have_stats = false;
@@ -567,7 +573,6 @@ PhasePlan plan_phase(const boa_index *ix, int32_t L, int32_t forced_h, int64_t m
     int64_t need = (max_active + best_wpb - 1) / best_wpb;
     if (need < 1) need = 1;
     pl.blocks = (int32_t)std::min<int64_t>(blocks, need);
-    pl.launches = 0;
     return pl;
 }
 
@@ -910,7 +915,7 @@ int run_search(boa_index *ix, const void *queries, const int32_t *ranges, int64_
     ia.reset_slots = ws.reset_logs ? ws.slots : 0;
 
     if (ws.timing) {
-        ix->launch_phase.clear();
+        ix->launched.clear();
         HIP_TRY(hipEventRecord(ix->ev_all0, st));
     }
     ix->have_stats = false;
@@ -950,9 +955,20 @@ int run_search(boa_index *ix, const void *queries, const int32_t *ranges, int64_
     // One search launch over at most `bound` queries (exact: their number),
     // bracketed by HIP events when timing: by a team of waves per query where
     // so few are served, by one wave per query otherwise. Where only the
-    // device knows the number, a launch of each kind.
+    // device knows the number, a launch of each kind. Recorded under the phase
+    // it starts at.
     auto launch = [&](PhaseArgs a, int blocks, hipStream_t s, bool wide, int phase, const TeamPlan &tp, int64_t bound,
                       bool exact, uint64_t max_slots) -> int {
+        int kernels = 0;
+        auto ran = [&](int wpb, int blocks_, int slots) {
+            PhasePlan &pl = plans[phase];
+            if (pl.launches++ == 0) {
+                pl.ran_wpb = wpb;
+                pl.ran_blocks = blocks_;
+                pl.ran_slots = slots;
+            }
+            ++kernels;
+        };
         if (ws.timing) HIP_TRY(hipEventRecord(ix->ev_start[ev], s));
         const bool team = tp.capacity > 0 && (!exact || bound <= tp.capacity);
         a.min_active = 0;
@@ -974,26 +990,23 @@ int run_search(boa_index *ix, const void *queries, const int32_t *ranges, int64_
             e.prof = tprof;
 #endif
             HIP_TRY(launch_team(e, ix->vec_dtype, tp.parts, (int)tb, s));
+            ran(1 + TEAM_GROUPS * tp.parts, (int)tb, tp.h_slots);
 #ifdef BOA_STAGE_PROFILE
             if (int rc2 = stage_profile_team_end(tprof, tpn, a.L_alloc, (int)tb, tp.h_slots, tp.capacity, s)) return rc2;
 #endif
         }
-        if (!team || bound > tp.capacity) HIP_TRY(launch_phase(a, ix->vec_dtype, blocks, s, wide));
+        if (!team || bound > tp.capacity) {
+            HIP_TRY(launch_phase(a, ix->vec_dtype, blocks, s, wide));
+            ran(a.waves_per_block, blocks, a.vis_bitmap ? 0 : 1 << a.h_log2);
+        }
         if (ws.timing) {
             HIP_TRY(hipEventRecord(ix->ev_end[ev], s));
-            ix->launch_phase.push_back({phase, ev});
+            ix->launched.push_back({phase, ev, kernels});
             ++ev;
         }
         return BOA_OK;
     };
 
-    // the launch shape that teams take, in the search's statistics
-    auto as_team = [&](PhasePlan &pl, const TeamPlan &tp, int64_t bound) {
-        if (tp.capacity < bound) return;
-        pl.wpb = 1 + 3 * tp.parts;
-        pl.blocks = (int32_t)std::min<int64_t>(tp.blocks, bound);
-        pl.h_slots = tp.h_slots;
-    };
     if (rq.one_launch) {
         PhasePlan &pl = plans[0];
         PhaseArgs a = base;
@@ -1022,10 +1035,8 @@ int run_search(boa_index *ix, const void *queries, const int32_t *ranges, int64_
                      rq.warm ? " (warm start)" : "", pl.h_slots, pl.blocks * pl.wpb);
         if (int rc2 = stage_profile_end(prof, pn, Lw, pl.blocks * pl.wpb, st)) return rc2;
 #endif
-        pl.launches = 1;
         if (!rq.fused)   // (served: the phases that had queries)
             for (int32_t ph = 1; ph < n_phases; ++ph) plans[ph].launches = -1;
-        as_team(pl, teams[0], nq);
     } else if (rq.split) {
         // the first phase over every query at its own width ...
         PhasePlan &p0 = plans[0];
@@ -1044,7 +1055,6 @@ int run_search(boa_index *ix, const void *queries, const int32_t *ranges, int64_
         a.waves_per_block = p0.wpb;
         a.slot_base = 0;
         if (int rc = launch(a, p0.blocks, st, false, 0, teams[0], nq, true, ws.slots)) return rc;
-        p0.launches = 1;
         if (n_phases > 1) {
             // ... then its survivors, compacted, through every later width
             CompactArgs ca{};
@@ -1086,16 +1096,11 @@ int run_search(boa_index *ix, const void *queries, const int32_t *ranges, int64_
 #endif
                 const TeamPlan te = rq.team ? plan_team(ix, Lw, S, p->lds_hash_slots, rq.pq_m) : TeamPlan();
                 if (int rc = launch(e, pe.blocks, st, true, 1, te, S, true, ws.slots)) return rc;
-                as_team(pe, te, S);
 #ifdef BOA_STAGE_PROFILE
                 std::fprintf(stderr, "[stage-profile] split escalation: %u survivors, table %d slots, %d waves\n",
                              S, pe.h_slots, pe.blocks * pe.wpb);
                 if (int rc2 = stage_profile_end(prof, pn, Lw, pe.blocks * pe.wpb, st)) return rc2;
 #endif
-                plans[1].launches = 1;
-                plans[1].h_slots = pe.h_slots;
-                plans[1].wpb = pe.wpb;
-                plans[1].blocks = pe.blocks;
             }
         }
     } else if (!rq.plus) {
@@ -1125,7 +1130,6 @@ int run_search(boa_index *ix, const void *queries, const int32_t *ranges, int64_
 #ifdef BOA_STAGE_PROFILE
             if (int rc2 = stage_profile_end(prof, pn, pl.L, pl.blocks * pl.wpb, st)) return rc2;
 #endif
-            pl.launches = 1;
             if (ph + 1 < n_phases) {
                 CompactArgs ca{};
                 ca.in = ws.active[ph & 1];
@@ -1175,7 +1179,6 @@ int run_search(boa_index *ix, const void *queries, const int32_t *ranges, int64_
             const int64_t span = a.t_end - a.t_begin;
             const int blocks = (int)std::min<int64_t>(p0.blocks, (span + p0.wpb - 1) / p0.wpb);
             if (int rc = launch(a, blocks, st, false, 0, teams[0], span, true, half_slots)) return rc;
-            p0.launches += 1;
             AppendArgs ap{};
             ap.in = ws.active[0] + a.t_begin;
             ap.conf = ws.conf + a.t_begin;
@@ -1204,7 +1207,6 @@ int run_search(boa_index *ix, const void *queries, const int32_t *ranges, int64_
                 e.slot_base = (uint32_t)half_slots;   // disjoint spill bitmaps from stream 0
                 if (int rc = launch(e, pe.blocks, ix->aux, false, 1, teams[1], std::min<int64_t>(nq, half * B), false, half_slots))
                     return rc;
-                pe.launches += 1;
             }
         }
         if (n_phases > 1 && nsub > half) {
@@ -1223,7 +1225,6 @@ int run_search(boa_index *ix, const void *queries, const int32_t *ranges, int64_
             e.waves_per_block = pe.wpb;
             e.slot_base = 0;
             if (int rc = launch(e, pe.blocks, st, false, 1, teams[1], nq - half * B, false, half_slots)) return rc;
-            pe.launches += 1;
         }
         if (n_phases > 1) {
             HIP_TRY(hipEventRecord(ix->ev_join, ix->aux));
@@ -1246,13 +1247,13 @@ int run_search(boa_index *ix, const void *queries, const int32_t *ranges, int64_
         ix->last_pq_m = rq.pq_m;
         ix->have_stats = true;
         ix->cum_searches += 1;
-        for (auto &lp : ix->launch_phase) {
+        for (auto &l : ix->launched) {
             float ms = 0.f;
-            HIP_TRY(hipEventElapsedTime(&ms, ix->ev_start[lp.second], ix->ev_end[lp.second]));
+            HIP_TRY(hipEventElapsedTime(&ms, ix->ev_start[l.ev], ix->ev_end[l.ev]));
             ix->cum_kernel_ms += ms;
-            ix->cum_launches += 1;
-            ix->cum_phase_kernel_ms[lp.first] += ms;
-            ix->cum_phase_launches[lp.first] += 1;
+            ix->cum_launches += l.kernels;
+            ix->cum_phase_kernel_ms[l.phase] += ms;
+            ix->cum_phase_launches[l.phase] += l.kernels;
         }
     }
     if (status & BOA_STATUS_OVERFLOW)
@@ -1385,9 +1386,9 @@ extern "C" int boa_get_stats(const boa_index *ix, boa_stats *out)
     const int64_t nq = ix->last_nq;
     const int32_t np = (int32_t)ix->plans.size();
     out->n_phases = np;
-    out->waves_per_block = ix->plans[0].wpb;
-    out->blocks = ix->plans[0].blocks;
-    out->lds_hash_slots = ix->plans[0].h_slots;
+    out->waves_per_block = ix->plans[0].ran_wpb;
+    out->blocks = ix->plans[0].ran_blocks;
+    out->lds_hash_slots = ix->plans[0].ran_slots;
     std::vector<uint8_t> st((size_t)nq * np);
     std::vector<uint32_t> E((size_t)nq * np), S((size_t)nq * np);
     HIP_TRY(hipMemcpy(st.data(), ix->qstat, st.size(), hipMemcpyDeviceToHost));
@@ -1414,10 +1415,10 @@ extern "C" int boa_get_stats(const boa_index *ix, boa_stats *out)
         ps.gathered_bytes = 4.0 * v.R * (double)ps.expansions + per_scored * (double)ps.scored +
                             (v.d * e + 8.0 * v.m + 8.0 * ix->last_k + 4.0) * (double)ps.active;
     }
-    for (auto &lp : ix->launch_phase) {
+    for (auto &l : ix->launched) {
         float ms = 0.f;
-        HIP_TRY(hipEventElapsedTime(&ms, ix->ev_start[lp.second], ix->ev_end[lp.second]));
-        out->phase[lp.first].kernel_ms += ms;
+        HIP_TRY(hipEventElapsedTime(&ms, ix->ev_start[l.ev], ix->ev_end[l.ev]));
+        out->phase[l.phase].kernel_ms += ms;
     }
     float tot = 0.f;
     HIP_TRY(hipEventElapsedTime(&tot, ix->ev_all0, ix->ev_last));

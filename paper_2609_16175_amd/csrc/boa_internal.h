@@ -160,11 +160,12 @@ int phase_occupancy(int vec_dtype, int d, int wpb, size_t lds, bool wide = false
 // per-wave LDS bytes the distance scorer keeps (its copy of the query, or
 // the product-quantisation distance table)
 int scorer_lds_bytes(int vec_dtype, int d, bool wide = false, int pq_m = 0);
-// The launch with a team of waves per query: its LDS per
-// block, resident blocks per CU, and the launch (lds_per_wave carries the
-// block's LDS bytes; a block uses one wave slot).
-// parts: waves that share one node's row (1 or 2; 1 with product
+// The launch with a team of waves per query (one that owns the worklist, and
+// TEAM_GROUPS x parts helpers): its LDS per block, resident blocks per CU, and
+// the launch (lds_per_wave carries the block's LDS bytes; a block uses one wave
+// slot). parts: waves that share one node's row (1 or 2; 1 with product
 // quantisation).
+constexpr int TEAM_GROUPS = 3;   // nodes in work or held at a time
 size_t team_lds_bytes(int32_t L, int parts, uint32_t vis_words, int scorer_lds);
 int team_occupancy(int vec_dtype, int d, int parts, size_t lds, int pq_m);
 hipError_t launch_team(const PhaseArgs &a, int vec_dtype, int parts, int blocks, hipStream_t st);

@@ -1583,7 +1583,6 @@ __global__ void __launch_bounds__(256, Scorer::kWaves) phase_kernel(PhaseArgs a)
 // request, and one follows on every path (the last is TEAM_EXIT); the
 // worklist wave waits only for a helper that holds a request, which ends
 // without waiting for anybody.
-static constexpr int TEAM_GROUPS = 3;   // nodes in work or held at a time
 enum : uint32_t { TEAM_EXPAND = 0, TEAM_SCORE = 1, TEAM_QUERY = 2, TEAM_EXIT = 3 };
 struct TeamWave {        // one helper
     uint64_t req;        // sequence number << 34 | kind << 32 | payload

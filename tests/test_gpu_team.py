@@ -61,3 +61,53 @@ def test_pq_team_equals_one_wave_and_oracle(dtype, d, R, M):
                 got = gpu_search(ix, q, r, k=5, eps=0.02, schedule=[8, 40, 600], pq=True, escalation_waves=waves, **mode)
                 assert_parity(got, ref, f"pq M={M} {mode} nq={nq} escalation_waves={waves}")
     ix.close()
+
+
+def test_statistics_report_what_was_launched():
+    """Shape and number of the launches in the statistics, for teams, for one
+    wave per query, and where the number of a phase's queries is known on the
+    device only and two kernels follow each other. An expansion takes 4 waves
+    of a team here (R <= 32, rows of 128 bytes). Tables of 16,384 slots (32 KB)
+    leave room for 4 teams per CU at width 8 and for 2 at width 2,048, by the
+    160 KB of a CU: 800 queries are then teams in the first phase, and at most
+    512 of them in the second."""
+    import torch
+
+    import paper_2609_16175_amd as boa
+    kw = dict(n=2000, d=32, m=1, R=12, dtype="f32", seed=3)
+    ref_ix = random_index(**kw)
+    ix = boa.Index(*random_arrays(**kw))
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("the capacities are those of 256 CUs")
+
+    def run(nq, **par):
+        q, r = random_queries(ref_ix, nq, 60, nq)
+        ix.reset_counters()
+        gpu_search(ix, q, r, k=5, **par)
+        st = ix.stats()
+        shape = (st["waves_per_block"], st["blocks"], st["lds_hash_slots"])
+        launches = [p["launches"] for p in st["phases"]]
+        assert st["cum_launches"] == sum(st["cum_phase_launches"])
+        return shape, launches, st["cum_phase_launches"], st
+
+    for mode in ({"fixed_L": 16}, {"schedule": [8], "fused": True}):
+        assert run(300, **mode)[:3] == ((4, 300, 0), [1], [1])
+    shape, launches, cum, _ = run(300, fixed_L=16, escalation_waves=1)
+    assert shape[0] <= 4 and shape[0] * shape[1] >= 300 and shape[2] > 0 and launches == cum == [1]
+    # modes 0 and 2 in one launch: its time under phase 0
+    for mode in ({}, {"split": True}):
+        shape, launches, cum, st = run(300, schedule=[8, 24], eps=0.0, **mode)
+        assert shape == (4, 300, 0) and launches == [1, 1] and cum == [1, 0]
+        assert st["phases"][0]["kernel_ms"] > 0 and st["phases"][1]["kernel_ms"] == 0
+    # sub-batches of 100, then a pool of 200 and one of 100
+    shape, launches, cum, _ = run(300, schedule=[8, 24], eps=0.0, boa_plus=True, sub_batches=3)
+    assert shape == (4, 100, 0) and launches == cum == [3, 2]
+    wide = dict(schedule=[8, 2048], eps=0.0, lds_hash_slots=16384)
+    shape, launches, cum, _ = run(800, **wide)
+    assert shape == (4, 800, 16384) and launches == cum == [1, 2]
+    shape, launches, cum, _ = run(800, split=True, **wide)
+    assert shape == (4, 800, 16384) and launches == cum == [1, 1]
+    # more than fit at the narrow width, too
+    shape, launches, cum, _ = run(1100, **wide)
+    assert shape[0] < 4 and shape[2] == 16384 and launches == cum == [1, 2]
+    ix.close()
