@@ -952,6 +952,7 @@ int run_search(boa_index *ix, const void *queries, const int32_t *ranges, int64_
     base.vec_u8 = ix->vec_dtype == BOA_VEC_U8 ? 1 : 0;
     for (int32_t ph = 0; ph < n_phases; ++ph) base.sched[ph] = sched[ph];
     int ev = 0;
+    bool more = rq.plus;   // device work after the last search launch on the stream
     // One search launch over at most `bound` queries (exact: their number),
     // bracketed by HIP events when timing: by a team of waves per query where
     // so few are served, by one wave per query otherwise. Where only the
@@ -1068,6 +1069,7 @@ int run_search(boa_index *ix, const void *queries, const int32_t *ranges, int64_
             HIP_TRY(hipMemcpyAsync(ix->h_back, ws.n_active + 1, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
             HIP_TRY(hipStreamSynchronize(st));
             const uint32_t S = ix->h_back[0];
+            more = S == 0;   // (the compaction)
             if (S > 0) {
                 PhasePlan pe = plan_escalation(ix, Lw, S, p->lds_hash_slots, rq.pq_m);
                 if ((size_t)pe.lds_per_wave > (pe.vis_bitmap ? ix->lds_per_block_hw : ix->lds_per_block_max))
@@ -1234,8 +1236,8 @@ int run_search(boa_index *ix, const void *queries, const int32_t *ranges, int64_
 
     if (ws.timing) {
         // (the last launch's own event, where it is the last on the stream)
-        if (rq.plus) HIP_TRY(hipEventRecord(ix->ev_all1, st));
-        ix->ev_last = rq.plus ? ix->ev_all1 : ix->ev_end[ev - 1];
+        if (more) HIP_TRY(hipEventRecord(ix->ev_all1, st));
+        ix->ev_last = more ? ix->ev_all1 : ix->ev_end[ev - 1];
     }
     HIP_TRY(hipMemcpyAsync(ix->h_back, ws.status, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));

@@ -111,3 +111,23 @@ def test_statistics_report_what_was_launched():
     shape, launches, cum, _ = run(1100, **wide)
     assert shape[0] < 4 and shape[2] == 16384 and launches == cum == [1, 2]
     ix.close()
+
+
+def test_total_time_ends_with_the_last_device_work():
+    """A split search without survivors ends with their compaction: one block
+    over 2^18 flags, 256 steps of at least half a microsecond, beside 10 to
+    20 us for what precedes the search launch."""
+    import paper_2609_16175_amd as boa
+    kw = dict(n=2000, d=16, m=1, R=8, dtype="f32", seed=5)
+    ref_ix = random_index(**kw)
+    ix = boa.Index(*random_arrays(**kw))
+    q, r = random_queries(ref_ix, 1 << 18, 60, 1)
+    r[:, :, 0], r[:, :, 1] = -2**31, 2**31 - 1
+    rest = []
+    for _ in range(3):
+        gpu_search(ix, q, r, k=1, schedule=[4, 8], eps=1.0, split=True)
+        st = ix.stats()
+        assert [p["active"] for p in st["phases"]] == [1 << 18, 0]
+        rest.append(st["total_ms"] - st["phases"][0]["kernel_ms"])
+    assert min(rest) > 0.1, rest
+    ix.close()
