@@ -30,8 +30,6 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
-#include <queue>
-#include <thread>
 #include <vector>
 
 #include "boa_internal.h"
@@ -42,6 +40,7 @@ static constexpr uint64_t BKEY_NONE = ~0ull;
 static constexpr int KNN_LIST = 128;      // most candidates per point
 static constexpr int KNN_LEVELS = 4;      // attribute levels
 static constexpr int KNN_LEVEL_LIST = 32; // most candidates per point and level
+static_assert(KNN_LIST <= 128 && KNN_LEVEL_LIST <= KNN_LIST, "prune_fwd_kernel sorts 128 keys");
 
 __device__ __forceinline__ uint64_t bkey(float d, uint32_t id)
 {
@@ -753,15 +752,14 @@ __device__ void alpha_prune(const BuildView &v, const uint64_t *keys, int cnt, i
 
 __global__ void __launch_bounds__(256) prune_fwd_kernel(PruneArgs a)
 {
-    __shared__ uint64_t keys_s[4][256];
+    __shared__ uint64_t keys_s[4][128];
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     const int64_t u = (int64_t)blockIdx.x * 4 + wid;
     if (u >= a.v.n) return;
     uint64_t *keys = keys_s[wid];
     // the candidates in (distance, id) order, with this pass's own distance
     const uint32_t *cand = a.cand + ((size_t)blockIdx.y * a.v.n + u) * a.K;
-    const int N = a.K <= 128 ? 128 : 256;
-    for (int i = lane; i < N; i += 64) {
+    for (int i = lane; i < 128; i += 64) {
         uint64_t k = BKEY_NONE;
         if (i < a.K) {
             const uint32_t c = cand[i];
@@ -770,9 +768,8 @@ __global__ void __launch_bounds__(256) prune_fwd_kernel(PruneArgs a)
         keys[i] = k;
     }
     wave_fence();
-    if (a.K <= 128) bitonic<128>(keys, lane);
-    else bitonic<256>(keys, lane);
-    alpha_prune(a.v, keys, min(a.K, 256), a.budget, a.alpha2, a.out + ((size_t)blockIdx.y * a.v.n + u) * a.R, a.R, lane);
+    bitonic<128>(keys, lane);
+    alpha_prune(a.v, keys, a.K, a.budget, a.alpha2, a.out + ((size_t)blockIdx.y * a.v.n + u) * a.R, a.R, lane);
 }
 
 // Re-prune each point's forward row together with its reverse neighbours
