@@ -848,8 +848,8 @@ int plan_search(const boa_index *ix, Request &rq, int64_t nq, int32_t forced_h, 
         const bool widest = rq.fused || (rq.plus && ph > 0);
         PhasePlan pl = plan_phase_widest(ix, widest ? Lw : rq.sched[ph], forced_h, nq, false, rq.pq_m);
         if (rq.fused && Lw > 64) {
-            // the wide variant (eight-way worklist search, more rows in
-            // flight) wherever it keeps as many waves resident
+            // the wide variant (more rows in flight) wherever it keeps as many
+            // waves resident
             const PhasePlan w = plan_phase_widest(ix, Lw, forced_h, nq, true, rq.pq_m);
             if (w.capacity >= pl.capacity && (size_t)w.lds_per_wave <= ix->lds_per_block_max) pl = w;
         }

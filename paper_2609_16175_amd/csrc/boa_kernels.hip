@@ -146,7 +146,6 @@ __device__ __forceinline__ float from_lane_minus_f(float v)
 template <int T, int W = 1>
 struct F32Scorer {
     // lane p = lane & 15 accumulates float4 chunks p, p+16, p+32, ...
-    static constexpr bool kWide = W == 2;
     static constexpr bool kSpec = false;
     static constexpr int kSpecMaxR = 0;
     struct RowGather {};
@@ -281,7 +280,6 @@ struct U8Scorer {
     // from unsigned 4-byte dot products: every term is an exact integer
     // (at most 16 * 255^2 per lane), so the result is the exact sum of
     // squared differences.
-    static constexpr bool kWide = W == 2;
     // rows of at most 128 bytes gather every neighbour of an expanded node
     // before its visited test (gather_row / score_row below)
     static constexpr bool kSpec = G <= 8;
@@ -392,7 +390,7 @@ struct U8Scorer {
             if (PER * u >= R) break;   // uniform
             const int32_t acc = dist(rg.x[u], p, nch);
             const int cj = PER * u + g;
-            if (p == G - 1) cd[cj] = (float)acc;   // (cj < 32: slots past R are not read)
+            if (p == G - 1) cd[cj] = (float)acc;   // (cj < 64: slots past R are not read)
         }
     }
 
@@ -428,7 +426,6 @@ struct U8Scorer {
 // round trip, took 11,800 cycles of an expansion at M = 192.)
 template <int T>
 struct PQScorer {
-    static constexpr bool kWide = false;
     static constexpr bool kSpec = false;
     static constexpr int kSpecMaxR = 0;
     static constexpr int kTeamWaves = 4;
