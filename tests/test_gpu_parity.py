@@ -116,42 +116,73 @@ def test_forced_spill_changes_nothing(tiny, slots, mode):
     assert_parity(got, ref, f"spill slots={slots}, repeated")
 
 
+def _tiled(data, times):
+    return np.tile(data.queries, (times, 1)), np.tile(data.ranges, (times, 1, 1))
+
+
+def _tile_ref(ref, times):
+    """The oracle's result of a batch given `times` over (queries are independent)."""
+    rows = lambda a: np.concatenate([a] * times)  # noqa: E731
+    return type(ref)(rows(ref.ids), rows(ref.dists), rows(ref.final_L), rows(ref.expansions), rows(ref.scored),
+                     [{k: v if k == "L" else times * v for k, v in p.items()} for p in ref.phases])
+
+
 @pytest.mark.parametrize("eps", [0.0, 0.005, 0.05])
 def test_split_escalation_bitmap_and_table(tiny, eps):
-    """The split search's escalation launch keeps its visited set as an LDS
-    bitmap over all ids when that fits (10k points: 1.25 KB) and as the
-    hashed table when a table size is forced; both are exact sets, so both
-    equal the oracle, with almost every query escalating at small eps."""
+    """A split search's second launch, over 2,000 queries (more than are
+    resident as teams, so that the search takes two launches): with the visited
+    set as the planner chooses (tables at these survivor counts, or teams with
+    the LDS bitmap over all ids when few enough survive) and with a forced table
+    size; and over 200 queries with one wave each, whose survivors get the LDS
+    bitmap. All are exact sets, so all equal the oracle."""
     wl, d = tiny["wl"], tiny["data"]
     sched = oracle.schedule(wl.L0, 2.0, wl.Lmax)
-    ref = oracle.boa(tiny["orc"], d.queries, d.ranges, wl.k, sched, eps=eps)
-    assert ref.phases[1]["active"] > 0
-    for slots, waves in ((0, 0), (0, 1), (4096, 0)):
-        got = gpu_search(tiny["gpu"], d.queries, d.ranges, k=wl.k, L0=wl.L0, Lmax=wl.Lmax, eps=eps,
+    ref1 = oracle.boa(tiny["orc"], d.queries, d.ranges, wl.k, sched, eps=eps)
+    assert ref1.phases[1]["active"] > 0
+    for times, slots, waves in ((20, 0, 0), (20, 0, 1), (20, 4096, 0), (2, 0, 1)):
+        q, r = _tiled(d, times)
+        tiny["gpu"].reset_counters()
+        got = gpu_search(tiny["gpu"], q, r, k=wl.k, L0=wl.L0, Lmax=wl.Lmax, eps=eps,
                          split=True, lds_hash_slots=slots, escalation_waves=waves)
-        assert_parity(got, ref, f"split eps={eps} slots={slots} escalation_waves={waves}")
+        assert_parity(got, _tile_ref(ref1, times), f"split eps={eps} slots={slots} escalation_waves={waves}")
+        st = tiny["gpu"].stats()
+        assert st["cum_phase_launches"][:2] == [1, 1] and st["cum_launches"] == 2
+        assert st["waves_per_block"] * st["blocks"] >= 200 and st["lds_hash_slots"] > 0   # one wave per query
 
 
-@pytest.mark.parametrize("eps", [0.0, 0.02, 0.05])
-def test_split_two_wave_escalation(tiny, eps):
-    """The escalation launch with two waves per query (one merging the
-    worklist, one expanding the node it expects next and taking the guess
-    back when the selection differs) against the oracle and the one-wave
-    launch. Widths 10, 20, 40, 80: no query is confident at 10 (it needs
-    more than k valid entries), some stop at 20 inside the escalation launch
-    (eps 0.02: 27 of 100), the rest run to 80. Twice with two waves."""
+@pytest.mark.parametrize("eps,times", [(0.0, 1), (0.02, 1), (0.05, 1), (0.02, 20)])
+def test_split_escalation_with_teams(tiny, eps, times):
+    """Split searches whose escalation runs as teams of waves, against the
+    oracle and one wave per query. 100 queries are all resident as teams: one
+    launch carries them through every width (10: no query is confident, it needs
+    more than k valid entries; some stop at 20, eps 0.02: 27; the rest run to 80).
+    2,000 queries are not: one wave each through the first phase, and the
+    survivors (1,020), few enough, as teams in a second launch. Twice with teams."""
     wl, d = tiny["wl"], tiny["data"]
-    sched = [10, 20, 40, 80]
-    ref = oracle.boa(tiny["orc"], d.queries, d.ranges, 10, sched, eps=eps)
-    assert ref.phases[1]["active"] == d.queries.shape[0]
+    sched = [10, 20, 40, 80] if times == 1 else [16, 40, 80]
+    ref1 = oracle.boa(tiny["orc"], d.queries, d.ranges, 10, sched, eps=eps)
+    ref = _tile_ref(ref1, times)
+    q, r = _tiled(d, times)
+    S = ref.phases[1]["active"]
+    if times == 1:
+        assert S == 100
+    else:
+        # the launch of S queries at the widest width is one of teams: 4 waves each
+        assert 0 < S < 2000
+        gpu_search(tiny["gpu"], q[:S], r[:S], k=10, fixed_L=sched[-1])
+        st = tiny["gpu"].stats()
+        assert (st["waves_per_block"], st["blocks"]) == (4, S)
     for waves in (0, 1, 0):
-        got = gpu_search(tiny["gpu"], d.queries, d.ranges, k=10, schedule=sched, eps=eps,
-                         split=True, escalation_waves=waves)
+        tiny["gpu"].reset_counters()
+        got = gpu_search(tiny["gpu"], q, r, k=10, schedule=sched, eps=eps, split=True, escalation_waves=waves)
         assert_parity(got, ref, f"split eps={eps} escalation_waves={waves}")
         st = tiny["gpu"].stats()
         for p, rp in zip(st["phases"], ref.phases):
             assert (p["active"], p["confident"], p["expansions"], p["scored"]) == \
                 (rp["active"], rp["confident"], rp["expansions"], rp["scored"])
+        one_launch = times == 1 and waves == 0
+        assert st["cum_launches"] == (1 if one_launch else 2)
+        assert (st["waves_per_block"] == 4 and st["blocks"] == 100 and st["lds_hash_slots"] == 0) == one_launch
     with pytest.raises(_boa().BoaError):
         gpu_search(tiny["gpu"], d.queries, d.ranges, k=wl.k, split=True, escalation_waves=2)
 
