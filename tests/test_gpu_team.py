@@ -37,6 +37,10 @@ def test_team_equals_one_wave_and_oracle(dtype, d, R, m):
                 for slots in (0, 64) if nq == 300 else (0,):
                     got = gpu_search(ix, q, r, escalation_waves=waves, lds_hash_slots=slots, **par)
                     assert_parity(got, ref, f"{name} nq={nq} escalation_waves={waves} slots={slots}")
+                    if nq == 300:   # the (first) launch is one of teams, 4 or 7 waves each, or is not
+                        st = ix.stats()
+                        team = st["waves_per_block"] in (4, 7) and st["blocks"] == (100 if name == "plus" else 300)
+                        assert team == (waves == 0), (name, slots, st["waves_per_block"], st["blocks"])
     ix.close()
 
 
@@ -60,6 +64,47 @@ def test_pq_team_equals_one_wave_and_oracle(dtype, d, R, M):
             for waves in (0, 1):
                 got = gpu_search(ix, q, r, k=5, eps=0.02, schedule=[8, 40, 600], pq=True, escalation_waves=waves, **mode)
                 assert_parity(got, ref, f"pq M={M} {mode} nq={nq} escalation_waves={waves}")
+    ix.close()
+
+
+def test_teams_with_tables_that_spill():
+    """An index too large for the LDS bitmap over all ids (1.3 million points,
+    162,500 bytes of a block's 163,840): teams, and the phased and split search
+    in one launch, with the automatic hashed table, whose 16,384 slots a query of
+    width 700 overflows into its team's HBM bitmap; and without allocation, where
+    the scratch memory holds bitmaps for fewer teams than there are queries
+    (64 MiB for 388 of 600)."""
+    import paper_2609_16175_amd as boa
+    n, d, R = 1_300_000, 16, 32
+    g = np.random.default_rng(11)
+    x = g.integers(0, 256, size=(n, d)).astype(np.uint8)
+    attrs = g.integers(0, 100, size=(n, 1)).astype(np.int32)
+    steps = np.stack([g.choice(n - 1, R, replace=False) + 1 for _ in range(64)])
+    rows = np.arange(n)
+    adj = ((rows[:, None] + steps[rows % 64]) % n).astype(np.uint32)   # mostly new to a query
+    types = np.zeros(1, dtype=np.int32)
+    ref_ix = oracle.Index(x, attrs, types, adj, 5)
+    ix = boa.Index(x, attrs, types, adj, 5)
+    widths = [8, 40, 700]
+    for nq, eps in ((1, 0.0), (600, 0.05)):
+        q, r = random_queries(ref_ix, nq, 60, nq)
+        ref = oracle.boa(ref_ix, q, r, 5, widths, eps, threads=8)
+        ref_warm = oracle.boa_warm(ref_ix, q, r, 5, widths, eps)
+        assert ref.phases[2]["active"] > 0
+        for name in ("phased", "fused", "warm", "split", "plus"):
+            for no_alloc in (False, True):
+                if name == "plus" and no_alloc:
+                    continue   # (refused: it needs a second stream)
+                ix.reset_counters()
+                got = gpu_search(ix, q, r, k=5, eps=eps, schedule=widths, no_alloc=no_alloc, **MODES[name])
+                assert_parity(got, ref_warm if name == "warm" else ref, f"{name} nq={nq} no_alloc={no_alloc}")
+                if no_alloc:
+                    continue
+                st = ix.stats()
+                assert st["spilled_queries"] > 0
+                if name != "plus":   # one launch of teams of 4 waves
+                    assert (st["waves_per_block"], st["blocks"], st["lds_hash_slots"]) == (4, nq, 16384)
+                    assert st["cum_launches"] == 1
     ix.close()
 
 
