@@ -156,7 +156,8 @@ typedef struct {
                                tau == 0). 0: one launch per phase with device-side
                                compaction between them. Where all queries are resident
                                at once as teams (escalation_waves), 0 (with tau * nq
-                               below 1) and 2 run every phase in one launch as 1 does. */
+                               below 1) and 2 run every phase in one launch as 1 does,
+                               unless lds_hash_slots forces a table. */
     int32_t warm_start;     /* 1: warm-start escalation (Sec. III-A "Redundancy
                                Avoidance"): during a phase of width L the sorted list
                                keeps up to the next phase's width, only its first L
@@ -171,11 +172,12 @@ typedef struct {
                                re-rank the phase's valid worklist entries by exact
                                distance (Sec. III-B step 8); the result and Eq. 3 read
                                the re-ranked entries. k <= 128. 0: exact distances. */
-    int32_t escalation_waves; /* exact distances: 0 (default) a team of waves per query in
-                               launches of as few queries as are then resident at once
-                               (some hundreds): one owns the worklist and the visited set,
-                               the others expand the nodes next in order ahead of their
-                               turn (identical results); 1: one wave per query everywhere. */
+    int32_t escalation_waves; /* 0 (default): a team of waves per query, with exact and with
+                               product-quantised distances, in launches of as few queries
+                               as are then resident at once (256 to 1,536): one owns the
+                               worklist and the visited set, the others expand the nodes
+                               next in order ahead of their turn (identical results);
+                               1: one wave per query everywhere. */
 } boa_params;
 
 void boa_default_params(boa_params *p);

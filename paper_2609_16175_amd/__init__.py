@@ -207,7 +207,7 @@ class Index:
         pq:      traverse with product-quantised distances (set_pq first) and
                  re-rank each phase's valid entries exactly.
         escalation_waves: 0 a team of waves per query in launches of few
-                 queries (exact distances), 1 one wave per query everywhere.
+                 queries, 1 one wave per query everywhere.
         no_alloc: call boa_search_noalloc (the library allocates no device
                  memory for the call; pass preallocated `out` tensors to
                  allocate nothing on the torch side either).

@@ -685,11 +685,19 @@ PhasePlan plan_escalation(const boa_index *ix, int32_t L, int64_t S, int32_t for
 // A launch with a team of waves per query over up to S queries.
 struct TeamPlan {
     // Blocks (queries) resident at once, and so many queries it serves (0: not
-    // available). Beyond that a second round begins, while a launch with one
-    // wave per query takes about as long for 100 queries as for 1,000: 777
-    // queries at width 500 (d = 100) take 1.33 ms in one round of teams, 2.23
-    // in two (512 at once), 2.36 with one wave each; 2,401 at width 512
-    // (d = 96) take 12.6 ms of search in five rounds and 9.5 with one wave.
+    // available). A launch with one wave per query takes about as long for 100
+    // queries as for 1,000, and within one round teams were never slower (1,000
+    // queries, n = 200,000: width 500 1.38 against 2.56 ms for d = 100, 1.58 and
+    // 2.46 for d = 128 uint8; width 16 0.20 and 0.27; 500 of d = 768 at width 16
+    // 0.35 and 0.39). In further rounds it depends on what one wave per query
+    // leaves idle. One wave against teams at width 500: d = 100 2.69 and 1.95 ms
+    // (1,300 queries, two rounds), 3.71 and 3.47 (4,000, four); d = 128 uint8 2.44
+    // and 2.20 (1,300), but 2.67 and 3.20 (2,000) and 3.57 and 4.63 (4,000);
+    // d = 768 2.35 and 2.03 (1,000, two), but 2.57 and 2.75 (1,300, three).
+    // Product-quantised searches gain in every round measured, as LDS admits
+    // one wave or one team alike: M = 192 at width 1,024 7.09 and 4.21 ms (2,000),
+    // 13.1 and 8.0 (4,000, four rounds). The line is drawn at one round, the only
+    // place where no shape loses.
     int64_t capacity = 0;
     int32_t blocks = 0, lds = 0, h_slots = 0, parts = 1;
     uint32_t vis_words = 0;  // LDS words of the visited set; h_slots == 0: a bitmap over all ids

@@ -997,9 +997,13 @@ hipError_t ranks_and_thresholds(const int32_t *h_attrs, int64_t n, int m, uint32
 // Otherwise in tiles of 6,144 rows (24 of the selection's waves per CU) by 6,144
 // columns, 151 MB, which stay in the last cache, the rows' lists kept between
 // them (38 MB): 23.6 ms at n = 60,000 uint8 (4,096 rows 27.0, with twice the
-// columns 24.8; 2,048 rows 34.2). More would be faster by itself (all distances
-// kept: 19 ms), but memory is cleared by the driver before it is handed out
-// again: 25 to 28 ms a gigabyte in programs that build repeatedly.
+// columns 24.8; 2,048 rows 34.2). Just above the line a build takes up to seven
+// times as long (float32, tiles against all kept: n = 12,500 7.6 and 3.5 ms for
+// d = 96, 49 and 8.6 for d = 768; n = 20,000 15 and 8.6, 86 and 16), so a higher
+// one is faster where the memory is at hand, as in a process that only builds
+// (19 against 24 ms at n = 60,000). It stays here because memory that others
+// have used is cleared by the driver before it is handed out again, 25 to 28 ms
+// a gigabyte: that exceeds the gain of narrow rows, not that of wide ones.
 constexpr int64_t WHOLE_BYTES = (int64_t)512 << 20;
 constexpr int64_t PANEL_ROWS = 6144, PANEL_COLS = 48 * DT;
 

@@ -7,8 +7,9 @@
 //   2. gather its adjacency row, one neighbour per lane (one coalesced load);
 //   3. test-and-insert every neighbour into the query's visited set: a
 //      two-choice bucketed table of 16-bit entries in LDS whose overflow
-//      goes to a per-wave bitmap over all points in HBM, or (the escalation
-//      launch of a split search, when it fits) an LDS bitmap over all ids;
+//      goes to a per-wave bitmap over all points in HBM, or an LDS bitmap over
+//      all ids (teams, and the escalation launch of a split search, where it
+//      fits and still lets every query be resident);
 //   4. for the unseen neighbours: gather the attribute cells and count the
 //      violated range predicates (phi, Eq. 2), gather the vector and compute
 //      the squared L2 distance with a 16-lane (float32) or G-lane (uint8)
@@ -141,8 +142,10 @@ __device__ __forceinline__ float from_lane_minus_f(float v)
 // round; rounds are unrolled by RU so that RU rows of loads are in flight.
 
 // W = 2 is the variant for launches that hold few waves per CU (the
-// escalation of a split search): twice the rows in flight per round trip,
-// paid for in registers that such launches do not need for occupancy.
+// escalation of a split search, and fused launches whose LDS admits no more
+// waves than it does): twice the rows in flight per round trip and more, paid
+// for in registers that such launches do not need for occupancy. W = 3 is the
+// one of a team's helpers, between the two.
 template <int T, int W = 1>
 struct F32Scorer {
     // lane p = lane & 15 accumulates float4 chunks p, p+16, p+32, ...
