@@ -156,6 +156,15 @@ def source_digest() -> str:
     return h.hexdigest()
 
 
+def timed_launches(mode: str, phase: int, st: dict) -> int:
+    """Launches that start at a phase, over the accumulated searches, where the
+    two kernels for few and for many queries (one returns at once; later phases
+    of the phased mode, BOA+ pools) count as one."""
+    if phase > 0 and mode in ("phased", "boa_plus"):
+        return st["cum_searches"] * (1 if mode == "phased" else 2)
+    return st["cum_phase_launches"][phase]
+
+
 def recorded_traffic(workload: str):
     """HBM bytes per launch from the committed counter runs, only while the
     library sources are the ones they measured (else None)."""
@@ -499,7 +508,7 @@ def main():
         j = starts[gi + 1] if gi + 1 < len(starts) else nph
         if mode in ("fused", "warm"):
             j = nph
-        nl = st["cum_phase_launches"][i]
+        nl = timed_launches(mode, i, st)
         kms = st["cum_phase_kernel_ms"][i] / nl
         b = sum(gathered_bytes_phase(st, q2) for q2 in range(i, j)) * args.steps / nl
         groups.append(dict(phases=f"{st['phases'][i]['L']}..{st['phases'][j - 1]['L']}", launches=nl,

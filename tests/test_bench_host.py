@@ -141,3 +141,14 @@ def test_exact_filtered_topk_matches_brute_force():
         assert ids[i][fin].tolist() == o[fin].tolist()
         np.testing.assert_allclose(dd[i][fin], dist[o][fin], rtol=1e-12)
         assert np.isinf(dd[i][~fin]).all()
+
+
+def test_a_pair_of_kernels_is_one_timed_launch():
+    """Later phases launch a kernel for few queries and one for many, of which
+    one returns at once: the time of a launch is that of the pair."""
+    st = {"cum_searches": 20, "cum_phase_launches": [20, 40, 20]}
+    assert [bench.timed_launches("phased", i, st) for i in range(3)] == [20, 20, 20]
+    st = {"cum_searches": 20, "cum_phase_launches": [200, 80]}
+    assert [bench.timed_launches("boa_plus", i, st) for i in range(2)] == [200, 40]
+    st = {"cum_searches": 20, "cum_phase_launches": [20, 20]}
+    assert [bench.timed_launches("split", i, st) for i in range(2)] == [20, 20]
